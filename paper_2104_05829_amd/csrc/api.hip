@@ -139,12 +139,11 @@ static int build_level(Level &L, int N, int64_t E, const double *x, const double
     L.np = L.nq * L.nq * L.nq;
     L.E = E;
     L.nL = E * L.np;
-    // D followed by rho (geometry reads rho after D)
+    // D followed by rho (the geometry and the operator read rho after D)
     std::vector<double> hD(L.nq * L.nq + L.nq);
     SEM_TRY(host_gll(N, nullptr, hD.data() + L.nq * L.nq, hD.data()));
     SEM_TRY(alloc_copy((void **)&L.D, hD.data(), sizeof(double) * hD.size(), s));
-    std::vector<float> hD32(L.nq * L.nq);
-    for (int t = 0; t < L.nq * L.nq; ++t) hD32[t] = (float)hD[t];
+    std::vector<float> hD32(hD.begin(), hD.end());  // D, then rho
     SEM_TRY(alloc_copy((void **)&L.D32, hD32.data(), sizeof(float) * hD32.size(), s));
     SEM_HIP(hipStreamSynchronize(s));  // host vectors go out of scope
     SEM_TRY(build_maps(L, gid, dir, x, y, z, bad, s));

@@ -3,20 +3,28 @@
 //
 // Thread layout (the 2D-thread / 1D-register structure of Sec. 3.3): a thread
 // owns one (i,j) column of an element and keeps the k-line of u and of the
-// result in registers; u and the r/s-direction fluxes sit in LDS.  With
-// (N+1)^2 <= 64 every element lives inside one 64-lane wavefront, so LDS
-// traffic of an element is ordered without workgroup barriers and the
-// r-flux can overwrite u plane by plane (8.6 KiB of LDS per element at N=7).
-//   step 1: ur = D1 u, us = D2 u  (LDS rows), ut = D3 u (registers)
+// t-part of the result in registers; the element's u sits in LDS and the k
+// planes are swept one after another:
+//   step 1: ur = D1 u, us = D2 u  (LDS plane k), ut = D3 u (registers)
 //   step 2: (wr, ws, wt) = k G (ur, us, ut), G the symmetric 3x3 per point,
 //           the six factors of a point contiguous ([E][np][6], 48 B, three
 //           16-byte loads per lane, each wavefront reading 3 KiB contiguous
 //           per plane)
-//   step 3: w = D1^T wr + D2^T ws (LDS) + D3^T wt (registers, accumulated
-//           while the k-planes are swept)
-// The grid is persistent (a few workgroups per CU, each sweeping elements
-// with a grid stride) and the next element's u is loaded while the current
-// one is computed.
+//   step 3: plane k of D1^T wr + D2^T ws from two flux planes in LDS, left in
+//           the plane of u that is no longer read; D3^T wt accumulated in
+//           registers over the sweep
+// The flux planes alternate between two buffers, so a plane costs one barrier
+// (none but an ordering of LDS accesses where (N+1)^2 <= 64 and an element is
+// one wavefront).  The plane loop is not unrolled: row k of Dh (the D3
+// coefficients of the plane) then lives in SGPRs for one plane, where holding
+// all (N+1)^2 spilled them.  The next plane's G (and B, k) is loaded while the
+// current one is computed, across elements too; the grid is persistent.
+// D^T comes from the rows of D: GLL quadrature sums the product of two degree-N
+// derivatives exactly, so rho_i D[i][l] + rho_l D[l][i] is 0 but at the end
+// points (-1 for i = l = 0, +1 for i = l = N), and
+//   sum_l D[l][i] f_l = -rho_i sum_l D[i][l] (f_l / rho_l)  +- f_i / rho_i at the ends.
+// With two register rows instead of four the FP64 kernel keeps 3 waves per
+// SIMD at N = 7 and 2-3 up to N = 15 (four rows: 1-2 from N = 11 on).
 // Bytes per point (FP64 Poisson): u 8 + G 48 + w 8 = 64 (+8 for B, +8 for k).
 #pragma once
 #include "sem_internal.h"
@@ -34,7 +42,21 @@ struct AxShape {
     static constexpr int THREADS = EPB * TPE;
     static constexpr bool ONE_WAVE = THREADS <= 64;
     static constexpr int LD = (NQ % 2 == 0) ? NQ + 1 : NQ;    // padded LDS row
+    // block of nw wavefronts with fields of their own
+    static constexpr int threads(int nw) { return nw == 1 ? THREADS : 64 * nw; }
 };
+
+// Waves per SIMD asked of the compiler, FP64 (0.9 M to 2.4 M points, the two
+// forms in us): N = 10 .. 12 fit three with a few spilled registers, which
+// pays (N = 11 Helmholtz with k 39.5 -> 37.2, N = 12 Helmholtz 32.8 -> 27.9);
+// N = 13 with k and N = 15 spill too much at three (34.7 -> 39.1, 29.6 -> 52.5).
+// Below N = 10 the unforced kernel is the fastest form.
+template <int NQ, typename T>
+constexpr int ax_min_waves()
+{
+    if (sizeof(T) == 4 || NQ <= 10) return 1;
+    return NQ <= 13 ? 3 : 2;
+}
 
 template <bool ONE_WAVE>
 __device__ inline void block_sync()
@@ -63,136 +85,354 @@ __device__ inline void load_g6(const float *p, float g[6])
     g[0] = a.x; g[1] = a.y; g[2] = b.x; g[3] = b.y; g[4] = c.x; g[5] = c.y;
 }
 
-template <int NQ, typename T, bool HELM, bool VARK, bool DOT>
-__global__ void __launch_bounds__(AxShape<NQ>::THREADS)
+// Sum over the THREADS threads of a block (or of a field's wavefront) in a
+// fixed order: the lanes of each wavefront by halving strides, then the
+// wavefronts in order; the result is thread 0's.  sh: one slot per wavefront.
+template <int THREADS>
+__device__ inline double ax_block_sum(double x, int tid, double *sh)
+{
+    const int lane = tid & 63, n = min(64, THREADS - (tid & ~63));  // lanes of this wavefront
+#pragma unroll
+    for (int st = 32; st >= 1; st >>= 1) {
+        const double o = __shfl_down(x, st, 64);
+        if (lane + st < n) x += o;
+    }
+    if constexpr (THREADS > 64) {
+        if (lane == 0) sh[tid >> 6] = x;
+        __syncthreads();
+        if (tid == 0)
+#pragma unroll
+            for (int q = 1; q < (THREADS + 63) / 64; ++q) x += sh[q];
+    }
+    return x;
+}
+
+// One element column's constants: its rows of D and the end-point terms of D^T.
+template <int NQ, typename T>
+struct AxCol {
+    T Di[NQ], Dj[NQ];
+    T rhoi, rhoj, ri, rj, bi, bj;  // weights, their inverses, end-point terms
+    __device__ inline AxCol(const T *__restrict__ Dg, int i, int j)
+    {
+#pragma unroll
+        for (int l = 0; l < NQ; ++l) {
+            Di[l] = Dg[i * NQ + l];
+            Dj[l] = Dg[j * NQ + l];
+        }
+        rhoi = Dg[NQ * NQ + i];  // the weights follow D in its buffer
+        rhoj = Dg[NQ * NQ + j];
+        ri = T(1) / rhoi;
+        rj = T(1) / rhoj;
+        bi = i == 0 ? -ri : (i == NQ - 1 ? ri : T(0));
+        bj = j == 0 ? -rj : (j == NQ - 1 ? rj : T(0));
+    }
+};
+
+// (wr, ws, wt) = G (ur, us, ut)
+template <typename T>
+__device__ inline void ax_flux(const T (&g)[6], T ur, T us, T ut, T &wr, T &ws, T &wt)
+{
+    wr = g[0] * ur + g[1] * us + g[2] * ut;
+    ws = g[1] * ur + g[3] * us + g[4] * ut;
+    wt = g[2] * ur + g[4] * us + g[5] * ut;
+}
+
+// the r and s parts of a point's result (ar, as: the rows of D over the scaled
+// fluxes) with the mass term
+template <int NQ, typename T, bool HELM>
+__device__ inline T ax_rs_part(const AxCol<NQ, T> &C, T wr, T ws, T ar, T as, T h1, T h2, T b, T u)
+{
+    T acc = (C.bi * wr - C.rhoi * ar) + (C.bj * ws - C.rhoj * as);
+    acc *= h1;
+    if constexpr (HELM) acc += h2 * b * u;
+    return acc;
+}
+
+// A wavefront (or, for N > 7, a workgroup) computes NI fields of its element
+// plane by plane, and a workgroup holds NW wavefronts with fields of their own.
+// nvb: number of partial sums of u.w; record vb covers the element groups vb,
+// vb + nvb, ...  With several fields fewer workgroups than nvb may run, each
+// taking records in turn, so a field's records are those of a single-field call.
+template <int NQ, typename T, bool HELM, bool VARK, bool DOT, int NW, int NI>
+__global__ void __launch_bounds__((AxShape<NQ>::threads(NW)), (ax_min_waves<NQ, T>()))
 ax_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
           const T *__restrict__ kc, const T *__restrict__ Dg, T h1, T h2,
-          const T *__restrict__ u, T *__restrict__ w, double *__restrict__ partial,
-          const int *__restrict__ skip)
+          const T *__restrict__ u, int64_t ldu, T *__restrict__ w, int64_t ldw, VSet vs,
+          double *__restrict__ partial, int64_t pst, int64_t nvb, const int *__restrict__ skip,
+          int skip_stride)
 {
-    if (skip != nullptr && *skip != 0) return;
     using S = AxShape<NQ>;
     constexpr int TPE = S::TPE, EPB = S::EPB, LD = S::LD;
     constexpr int NP = NQ * NQ * NQ;
-    constexpr bool INPLACE = S::ONE_WAVE;
-    __shared__ T su[EPB][NQ][NQ][LD];
-    __shared__ T sr_[INPLACE ? 1 : EPB][NQ][NQ][LD];
-    __shared__ T ss[EPB][NQ][NQ][LD];
+    __shared__ T su[NW][NI][EPB][NQ][NQ][LD];
+    __shared__ T sr[NW][2][NI][EPB][NQ][LD];
+    __shared__ T ss[NW][2][NI][EPB][NQ][LD];
 
-    const int tid = threadIdx.x;
+    // the wavefront's slot (NW > 1: 64 lanes each), lane in it
+    const int fs = NW == 1 ? 0 : (int)threadIdx.x >> 6;
+    const int tid = NW == 1 ? (int)threadIdx.x : (int)threadIdx.x & 63;
+    if (NW > 1 && tid >= S::THREADS) return;
+    int64_t v[NI];
+    bool live[NI], any = false;
+#pragma unroll
+    for (int q = 0; q < NI; ++q) {
+        v[q] = vs.at(fs * NI + q);
+        live[q] = skip == nullptr || skip[v[q] * skip_stride] == 0;
+        any = any || live[q];
+    }
+    if (!any) return;  // uniform over the wavefronts of these fields
     const int el = (EPB == 1) ? 0 : tid / TPE;  // element slot within the block
     const int ij = (EPB == 1) ? tid : tid - el * TPE;
     const int i = ij % NQ;
     const int j = ij / NQ;
+    const AxCol<NQ, T> C(Dg, i, j);
 
-    T Di[NQ], Dj[NQ], DTi[NQ], DTj[NQ];
-#pragma unroll
-    for (int l = 0; l < NQ; ++l) {
-        Di[l] = Dg[i * NQ + l];
-        Dj[l] = Dg[j * NQ + l];
-        DTi[l] = Dg[l * NQ + i];
-        DTj[l] = Dg[l * NQ + j];
-    }
-
-    double dot = 0.0;
-    T rn[NQ];
-    int64_t g = blockIdx.x;  // element group: elements g*EPB .. g*EPB+EPB-1
+    const int64_t groups = (E + EPB - 1) / EPB;
+    T gn[6], bn = T(0), kn = T(0);
     {
-        const int64_t e0 = g * EPB + el;
-        if (e0 < E) {
-#pragma unroll
-            for (int k = 0; k < NQ; ++k) rn[k] = u[e0 * NP + ij + k * TPE];
-        } else {
-#pragma unroll
-            for (int k = 0; k < NQ; ++k) rn[k] = T(0);
-        }
+        const int64_t e0 = (int64_t)blockIdx.x * EPB + el;
+        const int64_t b0 = (e0 < E ? e0 : 0) * NP + ij;
+        load_g6(G + b0 * 6, gn);
+        if constexpr (HELM) bn = B[b0];
+        if constexpr (VARK) kn = kc[b0];
     }
-    for (; g * EPB < E; g += gridDim.x) {
-        const int64_t e = g * EPB + el;
-        const bool active = e < E;
-        const int64_t base = (active ? e : 0) * NP + ij;
-        T ru[NQ], rw[NQ];
+    for (int64_t vb = blockIdx.x; vb < nvb; vb += gridDim.x) {
+        double dot[NI];
 #pragma unroll
-        for (int k = 0; k < NQ; ++k) {
-            ru[k] = rn[k];
-            su[el][k][j][i] = ru[k];
-            rw[k] = T(0);
-        }
-        {  // next element's u, loaded while this one is computed
-            const int64_t en = (g + gridDim.x) * EPB + el;
-            if (en < E) {
+        for (int q = 0; q < NI; ++q) dot[q] = 0.0;
+        for (int64_t g = vb; g < groups; g += nvb) {  // elements g*EPB .. g*EPB+EPB-1
+            const int64_t e = g * EPB + el;
+            const bool active = e < E;
+            const int64_t base = (active ? e : 0) * NP + ij;
+            const int64_t gx = NW * NI == 1 || g + nvb < groups ? g + nvb : vb + gridDim.x;
+            const int64_t en = gx * EPB + el;
+            const int64_t nbase = (en < E ? en : 0) * NP + ij;
+            T ru[NI][NQ], rw[NI][NQ];
 #pragma unroll
-                for (int k = 0; k < NQ; ++k) rn[k] = u[en * NP + ij + k * TPE];
-            }
-        }
-        block_sync<S::ONE_WAVE>();
+            for (int q = 0; q < NI; ++q)
+#pragma unroll
+                for (int k = 0; k < NQ; ++k) ru[q][k] = u[v[q] * ldu + base + k * TPE];
+#pragma unroll
+            for (int q = 0; q < NI; ++q)
+#pragma unroll
+                for (int k = 0; k < NQ; ++k) {
+                    su[fs][q][el][k][j][i] = ru[q][k];
+                    rw[q][k] = T(0);
+                }
+            // wavefronts with fields of their own meet once per element, which
+            // keeps the factors that one of them fetched in L1 for the others
+            block_sync<S::ONE_WAVE && NW == 1>();
 
-        const T *Ge = G + base * 6;
+#pragma unroll 1
+            for (int k = 0; k < NQ; ++k) {
+                T gg[6];
+                const T bb = bn, c = kn;
 #pragma unroll
-        for (int k = 0; k < NQ; ++k) {
-            T ur = 0, us = 0, ut = 0;
+                for (int q = 0; q < 6; ++q) gg[q] = gn[q];
+                {  // the next plane's factors, loaded while this one is computed
+                    const int64_t nx = k + 1 < NQ ? base + (k + 1) * TPE : nbase;
+                    load_g6(G + nx * 6, gn);
+                    if constexpr (HELM) bn = B[nx];
+                    if constexpr (VARK) kn = kc[nx];
+                }
+                if constexpr (VARK)
 #pragma unroll
-            for (int l = 0; l < NQ; ++l) {
-                ur += Di[l] * su[el][k][j][l];
-                us += Dj[l] * su[el][k][l][i];
-                ut += Dg[k * NQ + l] * ru[l];
+                    for (int q = 0; q < 6; ++q) gg[q] *= c;
+                const T *dk = Dg + k * NQ;
+                T wr[NI], ws[NI], uk[NI];
+#pragma unroll
+                for (int q = 0; q < NI; ++q) {
+                    T ur = 0, us = 0, ut = 0, wt;
+#pragma unroll
+                    for (int l = 0; l < NQ; ++l) {
+                        ur += C.Di[l] * su[fs][q][el][k][j][l];
+                        us += C.Dj[l] * su[fs][q][el][k][l][i];
+                        ut += dk[l] * ru[q][l];
+                    }
+                    ax_flux(gg, ur, us, ut, wr[q], ws[q], wt);
+                    sr[fs][k & 1][q][el][j][i] = wr[q] * C.ri;
+                    ss[fs][k & 1][q][el][j][i] = ws[q] * C.rj;
+                    uk[q] = su[fs][q][el][k][j][i];
+#pragma unroll
+                    for (int m = 0; m < NQ; ++m) rw[q][m] += dk[m] * wt;
+                }
+                // past this barrier plane k of u has been read by every thread;
+                // the other pair of flux planes is written before the next one
+                block_sync<S::ONE_WAVE>();
+#pragma unroll
+                for (int q = 0; q < NI; ++q) {
+                    T ar = 0, as = 0;
+#pragma unroll
+                    for (int l = 0; l < NQ; ++l) {
+                        ar += C.Di[l] * sr[fs][k & 1][q][el][j][l];
+                        as += C.Dj[l] * ss[fs][k & 1][q][el][l][i];
+                    }
+                    // read again by this thread only
+                    su[fs][q][el][k][j][i] =
+                        ax_rs_part<NQ, T, HELM>(C, wr[q], ws[q], ar, as, h1, h2, bb, uk[q]);
+                }
             }
-            T gg[6];
-            load_g6(Ge + k * TPE * 6, gg);
-            if constexpr (VARK) {
-                const T c = kc[base + k * TPE];
 #pragma unroll
-                for (int q = 0; q < 6; ++q) gg[q] *= c;
+            for (int q = 0; q < NI; ++q)
+#pragma unroll
+                for (int k = 0; k < NQ; ++k) {
+                    const T out = su[fs][q][el][k][j][i] + h1 * rw[q][k];
+                    if (active && (NI == 1 || live[q])) w[v[q] * ldw + base + k * TPE] = out;
+                    if constexpr (DOT)
+                        if (active) dot[q] += (double)ru[q][k] * (double)out;
+                }
+        }
+        if constexpr (DOT) {
+            __shared__ double sdot[(S::THREADS + 63) / 64];
+#pragma unroll
+            for (int q = 0; q < NI; ++q) {
+                const double s = ax_block_sum<S::THREADS>(dot[q], tid, sdot);
+                if (tid == 0 && (NI == 1 || live[q])) partial[v[q] * pst + vb] = s;
             }
-            const T wr = gg[0] * ur + gg[1] * us + gg[2] * ut;
-            const T ws = gg[1] * ur + gg[3] * us + gg[4] * ut;
-            const T wt = gg[2] * ur + gg[4] * us + gg[5] * ut;
-            if constexpr (INPLACE)
-                su[el][k][j][i] = wr;  // plane k of u is no longer read
-            else
-                sr_[el][k][j][i] = wr;
-            ss[el][k][j][i] = ws;
-#pragma unroll
-            for (int m = 0; m < NQ; ++m) rw[m] += Dg[k * NQ + m] * wt;
         }
-        block_sync<S::ONE_WAVE>();
-
-#pragma unroll
-        for (int k = 0; k < NQ; ++k) {
-            T acc = rw[k];
-#pragma unroll
-            for (int l = 0; l < NQ; ++l) {
-                acc += DTi[l] * (INPLACE ? su[el][k][j][l] : sr_[el][k][j][l]);
-                acc += DTj[l] * ss[el][k][l][i];
-            }
-            T out = h1 * acc;
-            if constexpr (HELM) out += h2 * B[base + k * TPE] * ru[k];
-            if (active) w[base + k * TPE] = out;
-            if constexpr (DOT)
-                if (active) dot += (double)ru[k] * (double)out;
-        }
-        block_sync<S::ONE_WAVE>();  // LDS is rewritten by the next element
-    }
-
-    if constexpr (DOT) {
-        // deterministic block sum: LDS slots, summed by thread 0 in order
-        __shared__ double sdot[S::THREADS];
-        sdot[tid] = dot;
-        __syncthreads();
-        if (tid == 0) {
-            double s = 0.0;
-            for (int t = 0; t < S::THREADS; ++t) s += sdot[t];
-            partial[blockIdx.x] = s;
-        }
+        if constexpr (NW * NI == 1) break;  // one record per workgroup
     }
 }
 
-// workgroups per CU of the persistent grid, by variant (measured on the 16^3
-// and 32^3 boxes at N=7): FP64 Poisson 8, FP64 with the mass term 12, FP32 16
-template <typename T>
-inline int ax_blocks_per_cu(bool helm)
+// The operator for few elements.  A column thread takes its N + 1 planes one
+// after another, about 6 us at N = 7 however few elements there are; here an
+// element's points are spread over threads that own KPT points each (one up to
+// N = 9), everything is loaded at once, and the three contractions each way
+// read LDS between two barriers.  Dh sits in LDS too.
+template <int NQ>
+struct AxSplitShape {
+    static constexpr int TPE = NQ * NQ, NP = TPE * NQ;
+    static constexpr int KS = NP <= 1024 ? NQ : (NQ == 11 ? 8 : NQ == 12 ? 6 : NQ <= 14 ? 5 : 4);
+    static constexpr int KPT = (NQ + KS - 1) / KS;             // points per thread
+    static constexpr int EPB = NP <= 128 ? 256 / NP : 1;       // elements per block
+    static constexpr int THREADS = EPB * TPE * KS;
+    static constexpr int LD = (NQ % 2 == 0) ? NQ + 1 : NQ;
+};
+
+template <int NQ, typename T, bool HELM, bool VARK, bool DOT>
+__global__ void __launch_bounds__(AxSplitShape<NQ>::THREADS)
+ax_split_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
+                const T *__restrict__ kc, const T *__restrict__ Dg, T h1, T h2,
+                const T *__restrict__ u, int64_t ldu, T *__restrict__ w, int64_t ldw, VSet vs,
+                double *__restrict__ partial, int64_t pst, const int *__restrict__ skip,
+                int skip_stride)
 {
-    return sizeof(T) == 4 ? 16 : (helm ? 12 : 8);
+    using S = AxSplitShape<NQ>;
+    constexpr int TPE = S::TPE, NP = S::NP, KS = S::KS, KPT = S::KPT, EPB = S::EPB, LD = S::LD;
+    __shared__ T sD[NQ][NQ + 1];
+    __shared__ T su[EPB][NQ][NQ][LD], sr[EPB][NQ][NQ][LD], ss[EPB][NQ][NQ][LD], st[EPB][NQ][NQ][LD];
+    const int64_t v = vs.at(blockIdx.y);
+    if (skip != nullptr && skip[v * skip_stride] != 0) return;
+    u += v * ldu;
+    w += v * ldw;
+    const int tid = threadIdx.x;
+    const int el = EPB == 1 ? 0 : tid / (TPE * KS);
+    const int r = EPB == 1 ? tid : tid - el * (TPE * KS);
+    const int kg = r / TPE, ij = r - kg * TPE;
+    const int i = ij % NQ, j = ij / NQ;
+    const int64_t e = (int64_t)blockIdx.x * EPB + el;
+    const bool active = e < E;
+    const int64_t base = (active ? e : 0) * NP + ij;
+    const AxCol<NQ, T> C(Dg, i, j);
+    T uu[KPT], g[KPT][6], bb[HELM ? KPT : 1], cc[VARK ? KPT : 1], wr[KPT], ws[KPT];
+    bb[0] = cc[0] = T(0);
+#pragma unroll
+    for (int p = 0; p < KPT; ++p) {
+        const int k = kg + p * KS;
+        const int64_t q = base + (k < NQ ? k : 0) * TPE;
+        uu[p] = u[q];
+        load_g6(G + q * 6, g[p]);
+        if constexpr (HELM) bb[p] = B[q];
+        if constexpr (VARK) cc[p] = kc[q];
+    }
+    for (int t = tid; t < NQ * NQ; t += S::THREADS) sD[t / NQ][t % NQ] = Dg[t];
+#pragma unroll
+    for (int p = 0; p < KPT; ++p) {
+        const int k = kg + p * KS;
+        if (k < NQ) su[el][k][j][i] = uu[p];
+    }
+    block_sync<(S::THREADS <= 64)>();
+#pragma unroll
+    for (int p = 0; p < KPT; ++p) {
+        const int k = kg + p * KS;
+        if (k < NQ) {
+            T ur = 0, us = 0, ut = 0;
+#pragma unroll
+            for (int l = 0; l < NQ; ++l) {
+                ur += C.Di[l] * su[el][k][j][l];
+                us += C.Dj[l] * su[el][k][l][i];
+                ut += sD[k][l] * su[el][l][j][i];
+            }
+            T wt;
+            if constexpr (VARK)
+#pragma unroll
+                for (int q = 0; q < 6; ++q) g[p][q] *= cc[p];
+            ax_flux(g[p], ur, us, ut, wr[p], ws[p], wt);
+            sr[el][k][j][i] = wr[p] * C.ri;
+            ss[el][k][j][i] = ws[p] * C.rj;
+            st[el][k][j][i] = wt;
+        }
+    }
+    block_sync<(S::THREADS <= 64)>();
+    double dot = 0.0;
+#pragma unroll
+    for (int p = 0; p < KPT; ++p) {
+        const int k = kg + p * KS;
+        if (k < NQ) {
+            T ar = 0, as = 0, at = 0;
+#pragma unroll
+            for (int l = 0; l < NQ; ++l) {
+                ar += C.Di[l] * sr[el][k][j][l];
+                as += C.Dj[l] * ss[el][k][l][i];
+                at += sD[l][k] * st[el][l][j][i];
+            }
+            const T out = ax_rs_part<NQ, T, HELM>(C, wr[p], ws[p], ar, as, h1, h2, bb[HELM ? p : 0],
+                                                  uu[p]) + h1 * at;
+            if (active) {
+                w[base + k * TPE] = out;
+                if constexpr (DOT) dot += (double)uu[p] * (double)out;
+            }
+        }
+    }
+    if constexpr (DOT) {
+        __shared__ double sdot[(S::THREADS + 63) / 64];
+        const double s = ax_block_sum<S::THREADS>(dot, tid, sdot);
+        if (tid == 0) partial[v * pst + blockIdx.x] = s;
+    }
+}
+
+// Several fields of elements of one wavefront (N <= 7): with `inside`, one
+// wavefront computes all of them plane by plane, the factors in registers; else
+// each has a wavefront of its own and the factors come from the caches for the
+// others, more wavefronts but G read once per field from L1 / L2.  Operator and
+// QQ^T together, us, the per-field loop of before / inside / a wavefront each:
+// three FP64 fields at N = 7, 16^3 elements 75 / 71 / 64, 32^3 574 / 564 / 572,
+// N = 5, 30^3 274 / 241 / 270; FP32 16^3 43 / 40 / 39, 32^3 331 / 326 / 344.  Four
+// FP64 fields inside leave one wave per SIMD (24^3: 327 / 353 / 311).  The line
+// lies where the FP64 factors fill half the Infinity Cache.
+template <typename T>
+inline bool ax_fields_inside(int64_t points, int nf)
+{
+    return points > 2500000 && nf <= (sizeof(T) == 4 ? 4 : 3);
+}
+
+// Workgroups per CU of the persistent grid.  One field (operator alone, N = 7,
+// us; 16^3 / 32^3 elements): FP64 Poisson 4, 6, 8, 12: 23.8 / 221, 21.9 / 201,
+// 21.0 / 202, 21.0 / 209; with the mass term 6, 8, 12: 22.7 / 226, 22.8 / 228,
+// 22.7 / 237, and with QQ^T following 31.7 / 298, 32.1 / 302, 32.0 / 309; N = 5
+// with the mass term and QQ^T, 20^3 / 40^3, 6, 8, 10, 12: 33.7 / 287, 29.8 / 266,
+// 29.8 / 255, 28.9 / 257; FP32 8, 12, 16: - / 171, 167, 167 (N = 5, 23^3: 29.9,
+// 27.3, 26.6).  Several fields: a persistent grid whose last workgroups find no
+// room (three wavefronts each do not pack the SIMDs evenly after a preceding
+// kernel) runs a second round, 32^3 with QQ^T at 4 per CU 710 against 590 at 3;
+// many short workgroups (48 per CU inside, 24 else) have no such round.  With
+// partial sums there are at most as many workgroups as records.
+template <int NQ, typename T>
+inline int ax_blocks_per_cu(int nf, bool inside, bool dot)
+{
+    if (nf == 1) return sizeof(T) == 4 ? 16 : (NQ == 8 ? 6 : (NQ < 8 ? 10 : 8));
+    if (inside) return dot ? 7 : 48;
+    return 24;
 }
 
 // Persistent grid over `groups` element groups with at most `cap`
@@ -206,257 +446,128 @@ inline int64_t balanced_grid(int64_t groups, int64_t cap)
     return (groups + per - 1) / per;
 }
 
-// Batched operator for nq <= 8 (an element fits one wavefront): the six
-// geometric factors (and B) of a thread's k-line are loaded into registers
-// once per element and applied to every live vector of the batch in turn, so
-// G is read once for up to kMaxRhs fields (Sec. 3.3, reuse of the geometric
-// factors across the components of a vector field).  Per point the arithmetic
-// is that of ax_kernel, in the same order.  PF: the next vector's u (or the
-// first vector of the next element) is loaded while the current one is
-// computed.  DTL: the rows of D^T come from an LDS table instead of
-// registers (fewer registers per lane, more waves per SIMD).  Without the
-// mass term the launch bound asks for two waves per SIMD: the FP64 form then
-// fits 248 VGPRs (some SGPRs kept in VGPR lanes) instead of 270 at one wave
-// per SIMD, and three fields at 16^3 take 48.5-49.5 instead of 51 us; with the
-// mass term the same bound spills 14 VGPRs and made the 32^3 lockstep p-MG
-// solve 1 ms slower, so that form keeps one wave per SIMD.
-template <int NQ, typename T, bool HELM, bool DOT, bool PF, bool DTL>
-__global__ void __launch_bounds__(AxShape<NQ>::THREADS, HELM ? 1 : 2)
-ax_multi_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
-                const T *__restrict__ Dg, T h1, T h2, const T *__restrict__ u, int64_t ldu,
-                T *__restrict__ w, int64_t ldw, VSet vs, double *__restrict__ partial, int64_t pst,
-                const int *__restrict__ skip, int skip_stride)
+// The spread form is used up to 2^18 points over all fields and N = 11 (us,
+// column form against spread form, each launch in a replayed graph: N = 7,
+// 64 elements 6.1 / 3.6, 216 with the mass term 5.2 / 3.9, 512 with k 5.8 / 5.7,
+// 729 6.3 / 7.5; N = 5, 1000 elements 5.3 / 4.7; N = 3, 4096 3.9 / 4.1; N = 9,
+// 216 9.1 / 6.7, 343 10.2 / 11.2; N = 11, 216 12.6 / 11.8; N = 13, 27
+// 13.8 / 22.4; three fields at N = 7, 64 6.5 / 3.9, 216 7.0 / 7.3).  The two
+// forms give the same bits per point.  Their partial sums cover different
+// points, and a batch has to have those of its single fields: with partial
+// sums the line lies at 2^17 points for any number of fields.
+template <int NQ>
+inline bool ax_spread(const Level &L, int nf, bool dot)
 {
-    using S = AxShape<NQ>;
-    static_assert(S::ONE_WAVE, "the batched operator keeps one element group per wavefront");
-    constexpr int TPE = S::TPE, EPB = S::EPB, LD = S::LD;
-    constexpr int NP = NQ * NQ * NQ;
-    __shared__ T su[EPB][NQ][NQ][LD];
-    __shared__ T ss[EPB][NQ][NQ][LD];
-    __shared__ T sdt[DTL ? NQ : 1][NQ];  // sdt[a][b] = D[b][a]
-    __shared__ double sdot[DOT ? kMaxRhs : 1][S::THREADS];
-
-    uint32_t pack;
-    const int na = live_vectors(vs, skip, skip_stride, &pack);
-    if (na == 0) return;  // uniform over the grid
-
-    const int tid = threadIdx.x;
-    const int el = (EPB == 1) ? 0 : tid / TPE;
-    const int ij = (EPB == 1) ? tid : tid - el * TPE;
-    const int i = ij % NQ;
-    const int j = ij / NQ;
-
-    T Di[NQ], Dj[NQ], DTi[DTL ? 1 : NQ], DTj[DTL ? 1 : NQ];
-#pragma unroll
-    for (int l = 0; l < NQ; ++l) {
-        Di[l] = Dg[i * NQ + l];
-        Dj[l] = Dg[j * NQ + l];
-        if constexpr (!DTL) {
-            DTi[l] = Dg[l * NQ + i];
-            DTj[l] = Dg[l * NQ + j];
-        }
-    }
-    if constexpr (DTL)
-        if (tid < NQ * NQ) sdt[tid / NQ][tid % NQ] = Dg[(tid % NQ) * NQ + tid / NQ];
-    if constexpr (DOT)
-#pragma unroll
-        for (int q = 0; q < kMaxRhs; ++q) sdot[q][tid] = 0.0;
-    block_sync<true>();
-
-    T rn[PF ? NQ : 1];
-    int64_t g = blockIdx.x;  // element group: elements g*EPB .. g*EPB+EPB-1
-    if constexpr (PF) {
-        const int64_t e0 = g * EPB + el;
-        const int64_t v0 = pack & 255u;
-#pragma unroll
-        for (int k = 0; k < NQ; ++k) rn[k] = e0 < E ? u[v0 * ldu + e0 * NP + ij + k * TPE] : T(0);
-    }
-    for (; g * EPB < E; g += gridDim.x) {
-        const int64_t e = g * EPB + el;
-        const bool active = e < E;
-        const int64_t base = (active ? e : 0) * NP + ij;
-        T gr[NQ][6];
-        T bm[HELM ? NQ : 1];
-#pragma unroll
-        for (int k = 0; k < NQ; ++k) {
-            load_g6(G + (base + k * TPE) * 6, gr[k]);
-            if constexpr (HELM) bm[k] = B[base + k * TPE];
-        }
-#pragma unroll 1
-        for (int q = 0; q < na; ++q) {
-            const int64_t v = (pack >> (8 * q)) & 255u;
-            T ru[NQ], rw[NQ];
-            if constexpr (PF) {
-#pragma unroll
-                for (int k = 0; k < NQ; ++k) ru[k] = rn[k];
-                const bool last = q + 1 == na;
-                const int64_t en = (last ? g + gridDim.x : g) * EPB + el;
-                if (en < E) {
-                    const int64_t vn = (pack >> (8 * (last ? 0 : q + 1))) & 255u;
-#pragma unroll
-                    for (int k = 0; k < NQ; ++k) rn[k] = u[vn * ldu + en * NP + ij + k * TPE];
-                }
-            } else {
-#pragma unroll
-                for (int k = 0; k < NQ; ++k) ru[k] = u[v * ldu + base + k * TPE];
-            }
-#pragma unroll
-            for (int k = 0; k < NQ; ++k) {
-                su[el][k][j][i] = ru[k];
-                rw[k] = T(0);
-            }
-            block_sync<true>();
-#pragma unroll
-            for (int k = 0; k < NQ; ++k) {
-                T ur = 0, us = 0, ut = 0;
-#pragma unroll
-                for (int l = 0; l < NQ; ++l) {
-                    ur += Di[l] * su[el][k][j][l];
-                    us += Dj[l] * su[el][k][l][i];
-                    ut += Dg[k * NQ + l] * ru[l];
-                }
-                const T wr = gr[k][0] * ur + gr[k][1] * us + gr[k][2] * ut;
-                const T ws = gr[k][1] * ur + gr[k][3] * us + gr[k][4] * ut;
-                const T wt = gr[k][2] * ur + gr[k][4] * us + gr[k][5] * ut;
-                su[el][k][j][i] = wr;
-                ss[el][k][j][i] = ws;
-#pragma unroll
-                for (int m = 0; m < NQ; ++m) rw[m] += Dg[k * NQ + m] * wt;
-            }
-            block_sync<true>();
-            double dot = 0.0;
-            if constexpr (DOT) dot = sdot[q][tid];
-#pragma unroll
-            for (int k = 0; k < NQ; ++k) {
-                T acc = rw[k];
-#pragma unroll
-                for (int l = 0; l < NQ; ++l) {
-                    T dti, dtj;
-                    if constexpr (DTL) {
-                        dti = sdt[i][l];
-                        dtj = sdt[j][l];
-                    } else {
-                        dti = DTi[l];
-                        dtj = DTj[l];
-                    }
-                    acc += dti * su[el][k][j][l];
-                    acc += dtj * ss[el][k][l][i];
-                }
-                T out = h1 * acc;
-                if constexpr (HELM) out += h2 * bm[k] * ru[k];
-                if (active) w[v * ldw + base + k * TPE] = out;
-                if constexpr (DOT)
-                    if (active) dot += (double)ru[k] * (double)out;
-            }
-            if constexpr (DOT) sdot[q][tid] = dot;
-            block_sync<true>();  // LDS is rewritten by the next vector
-        }
-    }
-
-    if constexpr (DOT) {
-        // deterministic block sums, one thread per live vector
-        __syncthreads();
-        if (tid < na) {
-            double s = 0.0;
-            for (int t = 0; t < S::THREADS; ++t) s += sdot[tid][t];
-            partial[(int64_t)((pack >> (8 * tid)) & 255u) * pst + blockIdx.x] = s;
-        }
-    }
+    const int64_t points = L.nL, blocks = points / (AxSplitShape<NQ>::EPB * AxSplitShape<NQ>::NP) + 1;
+    // the buffer of partial sums is sized by the CUs
+    if (dot && blocks > (int64_t)(L.n_cu > 0 ? L.n_cu : 256) * kAxMaxBlocksPerCU) return false;
+    return NQ <= 12 && (dot ? points <= (1 << 17) : points * nf <= (1 << 18));
 }
 
-// batched-operator variant and workgroups per CU of its grid (measured on
-// the 16^3 and 32^3 boxes at N=7 with three fields: prefetch on, D^T in
-// registers, 12 workgroups per CU for FP64 and FP32)
-constexpr bool kAxMultiPrefetch = true;
-constexpr bool kAxMultiDtLds = false;
-template <typename T>
-inline int ax_multi_blocks_per_cu(bool helm)
-{
-    (void)helm;
-    return 12;
-}
+// the compiled forms: mass term, coefficient (one field), partial sums (FP64)
+#define SEM_AX_FORMS(VARK_)                                                                    \
+    if constexpr (sizeof(T) == 8) {                                                            \
+        if (partial != nullptr) {                                                              \
+            if constexpr (VARK_) {                                                             \
+                if (vark && helm) SEM_AX_LAUNCH(true, true, true);                             \
+                if (vark && !helm) SEM_AX_LAUNCH(false, true, true);                           \
+            }                                                                                  \
+            if (!vark && helm) SEM_AX_LAUNCH(true, false, true);                               \
+            if (!vark && !helm) SEM_AX_LAUNCH(false, false, true);                             \
+            SEM_HIP(hipGetLastError());                                                        \
+            return SEM_OK;                                                                     \
+        }                                                                                      \
+    }                                                                                          \
+    if constexpr (VARK_) {                                                                     \
+        if (vark && helm) SEM_AX_LAUNCH(true, true, false);                                    \
+        if (vark && !helm) SEM_AX_LAUNCH(false, true, false);                                  \
+    }                                                                                          \
+    if (!vark && helm) SEM_AX_LAUNCH(true, false, false);                                      \
+    if (!vark && !helm) SEM_AX_LAUNCH(false, false, false);
 
 template <int NQ, typename T>
-static int ax_dispatch(const Level &L, const T *G, const T *B, const T *D, const T *u, T *w,
-                       double h1, double h2, const T *k, double *partial, int64_t *nblocks,
-                       hipStream_t s, const int *skip)
+static int ax_split_launch(const Level &L, const T *G, const T *B, const T *D, const T *u, int64_t ldu,
+                           T *w, int64_t ldw, const VSet &vs, double h1, double h2, const T *k,
+                           double *partial, int64_t pst, int64_t *nblocks, hipStream_t s,
+                           const int *skip, int skip_stride)
 {
-    using S = AxShape<NQ>;
-    const int64_t groups = (L.E + S::EPB - 1) / S::EPB;
-    const bool helm_ = h2 != 0.0;
-    const int64_t cap = (int64_t)(L.n_cu > 0 ? L.n_cu : 256) * ax_blocks_per_cu<T>(helm_);
-    const int64_t nb = balanced_grid(groups, cap);
+    using S = AxSplitShape<NQ>;
+    const int64_t nb = (L.E + S::EPB - 1) / S::EPB;
+    const bool helm = h2 != 0.0, vark = k != nullptr, dot = partial != nullptr;
     if (nblocks) *nblocks = nb;
-    if (nb == 0) return SEM_OK;
-    const bool helm = h2 != 0.0;
-    const bool vark = k != nullptr;
-    const bool dot = partial != nullptr;
-    dim3 grid((unsigned)nb), block(S::THREADS);
-#define SEM_AX_LAUNCH(H, V, P)                                                              \
-    hipLaunchKernelGGL((ax_kernel<NQ, T, H, V, P>), grid, block, 0, s, L.E, G, B, k, D,    \
-                       (T)h1, (T)h2, u, w, partial, skip)
-    if (helm) {
-        if (vark) { if (dot) SEM_AX_LAUNCH(true, true, true); else SEM_AX_LAUNCH(true, true, false); }
-        else { if (dot) SEM_AX_LAUNCH(true, false, true); else SEM_AX_LAUNCH(true, false, false); }
-    } else {
-        if (vark) { if (dot) SEM_AX_LAUNCH(false, true, true); else SEM_AX_LAUNCH(false, true, false); }
-        else { if (dot) SEM_AX_LAUNCH(false, false, true); else SEM_AX_LAUNCH(false, false, false); }
-    }
+    const dim3 grid((unsigned)nb, (unsigned)vs.n), block(S::THREADS);
+#define SEM_AX_LAUNCH(H, V, P)                                                                 \
+    hipLaunchKernelGGL((ax_split_kernel<NQ, T, H, V, P>), grid, block, 0, s, L.E, G, B, k, D, \
+                       (T)h1, (T)h2, u, ldu, w, ldw, vs, partial, pst, skip, skip_stride)
+    SEM_AX_FORMS(true)
 #undef SEM_AX_LAUNCH
     SEM_HIP(hipGetLastError());
     return SEM_OK;
 }
 
-template <typename T>
-int launch_ax(const Level &L, const T *G, const T *B, const T *D, const T *u, T *w, double h1,
-              double h2, const T *k, double *partial, int64_t *nblocks, hipStream_t s,
-              const int *skip)
+// One launch for the NF vectors of vs (one, or up to kMaxRhs with nq <= 8).
+// Every field's arithmetic is that of a single-field call.
+template <int NQ, typename T, int NW, int NI>
+static int ax_launch(const Level &L, const T *G, const T *B, const T *D, const T *u, int64_t ldu,
+                     T *w, int64_t ldw, const VSet &vs, double h1, double h2, const T *k,
+                     double *partial, int64_t pst, int64_t *nblocks, hipStream_t s, const int *skip,
+                     int skip_stride)
 {
-    switch (L.nq) {
-    case 2: return ax_dispatch<2, T>(L, G, B, D, u, w, h1, h2, k, partial, nblocks, s, skip);
-    case 3: return ax_dispatch<3, T>(L, G, B, D, u, w, h1, h2, k, partial, nblocks, s, skip);
-    case 4: return ax_dispatch<4, T>(L, G, B, D, u, w, h1, h2, k, partial, nblocks, s, skip);
-    case 5: return ax_dispatch<5, T>(L, G, B, D, u, w, h1, h2, k, partial, nblocks, s, skip);
-    case 6: return ax_dispatch<6, T>(L, G, B, D, u, w, h1, h2, k, partial, nblocks, s, skip);
-    case 7: return ax_dispatch<7, T>(L, G, B, D, u, w, h1, h2, k, partial, nblocks, s, skip);
-    case 8: return ax_dispatch<8, T>(L, G, B, D, u, w, h1, h2, k, partial, nblocks, s, skip);
-    case 9: return ax_dispatch<9, T>(L, G, B, D, u, w, h1, h2, k, partial, nblocks, s, skip);
-    case 10: return ax_dispatch<10, T>(L, G, B, D, u, w, h1, h2, k, partial, nblocks, s, skip);
-    case 11: return ax_dispatch<11, T>(L, G, B, D, u, w, h1, h2, k, partial, nblocks, s, skip);
-    case 12: return ax_dispatch<12, T>(L, G, B, D, u, w, h1, h2, k, partial, nblocks, s, skip);
-    case 13: return ax_dispatch<13, T>(L, G, B, D, u, w, h1, h2, k, partial, nblocks, s, skip);
-    case 14: return ax_dispatch<14, T>(L, G, B, D, u, w, h1, h2, k, partial, nblocks, s, skip);
-    case 15: return ax_dispatch<15, T>(L, G, B, D, u, w, h1, h2, k, partial, nblocks, s, skip);
-    case 16: return ax_dispatch<16, T>(L, G, B, D, u, w, h1, h2, k, partial, nblocks, s, skip);
-    default: set_error("ax: unsupported order N=%d", L.N); return SEM_EINVAL;
-    }
+    using S = AxShape<NQ>;
+    constexpr int NF = NW * NI;
+    const int64_t groups = (L.E + S::EPB - 1) / S::EPB;
+    const bool helm = h2 != 0.0, vark = k != nullptr, dot = partial != nullptr;
+    const int64_t cu = L.n_cu > 0 ? L.n_cu : 256;
+    const int64_t nvb = balanced_grid(groups, cu * ax_blocks_per_cu<NQ, T>(1, false, dot));  // records
+    const int64_t nb = NF == 1 ? nvb : balanced_grid(dot ? nvb : groups,
+                                                     cu * ax_blocks_per_cu<NQ, T>(NF, NI > 1, dot));
+    if (nblocks) *nblocks = nvb;
+    if (nb == 0) return SEM_OK;
+    const dim3 grid((unsigned)nb), block(S::threads(NW));
+#define SEM_AX_LAUNCH(H, V, P)                                                                 \
+    hipLaunchKernelGGL((ax_kernel<NQ, T, H, V, P, NW, NI>), grid, block, 0, s, L.E, G, B, k,  \
+                       D, (T)h1, (T)h2, u, ldu, w, ldw, vs, partial, pst, dot ? nvb : nb,     \
+                       skip, skip_stride)
+    SEM_AX_FORMS(NF == 1)
+#undef SEM_AX_LAUNCH
+    SEM_HIP(hipGetLastError());
+    return SEM_OK;
 }
 
 template <int NQ, typename T>
-static int ax_multi_dispatch(const Level &L, const T *G, const T *B, const T *D, const T *u,
-                             int64_t ldu, T *w, int64_t ldw, const VSet &vs, double h1, double h2,
-                             double *partial, int64_t pst, int64_t *nblocks, hipStream_t s,
-                             const int *skip, int skip_stride)
+static int ax_dispatch(const Level &L, const T *G, const T *B, const T *D, const T *u, int64_t ldu,
+                       T *w, int64_t ldw, const VSet &vs, double h1, double h2, const T *k,
+                       double *partial, int64_t pst, int64_t *nblocks, hipStream_t s, const int *skip,
+                       int skip_stride)
 {
-    using S = AxShape<NQ>;
-    const int64_t groups = (L.E + S::EPB - 1) / S::EPB;
-    const bool helm = h2 != 0.0;
-    const int64_t cap = (int64_t)(L.n_cu > 0 ? L.n_cu : 256) * ax_multi_blocks_per_cu<T>(helm);
-    const int64_t nb = balanced_grid(groups, cap);
-    if (nblocks) *nblocks = nb;
-    if (nb == 0) return SEM_OK;
-    constexpr bool PF = kAxMultiPrefetch, DTL = kAxMultiDtLds;
-    dim3 grid((unsigned)nb), block(S::THREADS);
-#define SEM_AXM_LAUNCH(H, P)                                                                \
-    hipLaunchKernelGGL((ax_multi_kernel<NQ, T, H, P, PF, DTL>), grid, block, 0, s, L.E, G, B, \
-                       D, (T)h1, (T)h2, u, ldu, w, ldw, vs, partial, pst, skip, skip_stride)
-    if (helm) {
-        if (partial) SEM_AXM_LAUNCH(true, true); else SEM_AXM_LAUNCH(true, false);
-    } else {
-        if (partial) SEM_AXM_LAUNCH(false, true); else SEM_AXM_LAUNCH(false, false);
+    if (ax_spread<NQ>(L, vs.n, partial != nullptr))
+        return ax_split_launch<NQ, T>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, k, partial, pst, nblocks, s,
+                                      skip, skip_stride);
+#define SEM_AX_NF(NW, NI)                                                                      \
+    return ax_launch<NQ, T, NW, NI>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, k, partial, pst,  \
+                                    nblocks, s, skip, skip_stride)
+    if (vs.n == 1) SEM_AX_NF(1, 1);
+    if constexpr (NQ <= 8) {
+        if (k == nullptr) {
+            if (ax_fields_inside<T>(L.nL, vs.n)) {
+                if (vs.n == 2) SEM_AX_NF(1, 2);
+                if (vs.n == 3) SEM_AX_NF(1, 3);
+                if constexpr (sizeof(T) == 4)
+                    if (vs.n == 4) SEM_AX_NF(1, 4);
+            }
+            if (vs.n == 2) SEM_AX_NF(2, 1);
+            if (vs.n == 3) SEM_AX_NF(3, 1);
+            if (vs.n == 4) SEM_AX_NF(4, 1);
+        }
     }
-#undef SEM_AXM_LAUNCH
-    SEM_HIP(hipGetLastError());
+#undef SEM_AX_NF
+    // one field at a time (variable coefficient, or elements wider than a wavefront)
+    for (int q = 0; q < vs.n; ++q) {
+        VSet one{0, 0u};
+        one.push(vs.at(q));
+        SEM_TRY((ax_launch<NQ, T, 1, 1>(L, G, B, D, u, ldu, w, ldw, one, h1, h2, k, partial, pst, nblocks,
+                                     s, skip, skip_stride)));
+    }
     return SEM_OK;
 }
 
@@ -466,26 +577,30 @@ int launch_ax_multi(const Level &L, const T *G, const T *B, const T *D, const T 
                     int64_t pst, int64_t *nblocks, hipStream_t s, const int *skip, int skip_stride)
 {
     if (vs.n <= 0) return SEM_OK;
-    if (vs.n == 1 || k != nullptr || L.nq > 8) {
-        // one field at a time (variable coefficient, or elements wider than a wavefront)
-        for (int q = 0; q < vs.n; ++q) {
-            const int64_t v = vs.at(q);
-            SEM_TRY(launch_ax<T>(L, G, B, D, u + v * ldu, w + v * ldw, h1, h2, k,
-                                 partial ? partial + v * pst : nullptr, nblocks, s,
-                                 skip ? skip + v * skip_stride : nullptr));
-        }
-        return SEM_OK;
+    if (sizeof(T) == 4 && partial != nullptr) {
+        set_error("ax: partial sums are formed in FP64 only");
+        return SEM_EINVAL;
     }
+#define SEM_AX_CASE(NQ)                                                                        \
+    case NQ:                                                                                   \
+        return ax_dispatch<NQ, T>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, k, partial, pst,    \
+                                  nblocks, s, skip, skip_stride);
     switch (L.nq) {
-    case 2: return ax_multi_dispatch<2, T>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, partial, pst, nblocks, s, skip, skip_stride);
-    case 3: return ax_multi_dispatch<3, T>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, partial, pst, nblocks, s, skip, skip_stride);
-    case 4: return ax_multi_dispatch<4, T>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, partial, pst, nblocks, s, skip, skip_stride);
-    case 5: return ax_multi_dispatch<5, T>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, partial, pst, nblocks, s, skip, skip_stride);
-    case 6: return ax_multi_dispatch<6, T>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, partial, pst, nblocks, s, skip, skip_stride);
-    case 7: return ax_multi_dispatch<7, T>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, partial, pst, nblocks, s, skip, skip_stride);
-    case 8: return ax_multi_dispatch<8, T>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, partial, pst, nblocks, s, skip, skip_stride);
+        SEM_AX_CASE(2) SEM_AX_CASE(3) SEM_AX_CASE(4) SEM_AX_CASE(5) SEM_AX_CASE(6)
+        SEM_AX_CASE(7) SEM_AX_CASE(8) SEM_AX_CASE(9) SEM_AX_CASE(10) SEM_AX_CASE(11)
+        SEM_AX_CASE(12) SEM_AX_CASE(13) SEM_AX_CASE(14) SEM_AX_CASE(15) SEM_AX_CASE(16)
     default: set_error("ax: unsupported order N=%d", L.N); return SEM_EINVAL;
     }
+#undef SEM_AX_CASE
+}
+
+template <typename T>
+int launch_ax(const Level &L, const T *G, const T *B, const T *D, const T *u, T *w, double h1,
+              double h2, const T *k, double *partial, int64_t *nblocks, hipStream_t s,
+              const int *skip)
+{
+    return launch_ax_multi<T>(L, G, B, D, u, 0, w, 0, VSet::one(), h1, h2, k, partial, 0, nblocks, s,
+                              skip, 0);
 }
 
 }  // namespace semx

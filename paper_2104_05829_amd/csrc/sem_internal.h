@@ -124,7 +124,7 @@ struct Level {
     // starts a segment, -1 past the chunk's end
     int32_t *chunk_perm = nullptr;
     int32_t *over = nullptr;                          // segments longer than 64 copies
-    double *D = nullptr;   // Dh [nq][nq] (row = point)
+    double *D = nullptr;   // Dh [nq][nq] (row = point), then the weights rho [nq]
     float *D32 = nullptr;
     // interpolation from the next coarser level's nodes to this level's
     // points: J [nq][nq_coarse]; null on the coarsest level
