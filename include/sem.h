@@ -225,7 +225,8 @@ typedef struct {
      * consecutive phase boundaries on the stream, launch gaps included, summed
      * over the iteration (for sem_pcg_solve_multi the phases serve every
      * system at once and each record holds the same totals):
-     *   ms_ax     element operator applications of the outer iteration
+     *   ms_ax     element operator applications of the outer iteration (with
+     *             Jacobi, the direction update and decision folded into them)
      *   ms_gs     their gather-scatter QQ^T
      *   ms_vec    vector updates, inner products and convergence decisions
      *             of the outer iteration (with Jacobi, the preconditioner too)

@@ -25,7 +25,7 @@ static void free_level(Level &L)
     free_schwarz(L);
     free_coarse_csr(L);
     void *ptrs[] = {L.G, L.B, L.G32, L.B32, L.W, L.W32, L.gid, L.dir, L.perm, L.offs,
-                    L.chunk_perm, L.over,
+                    L.chunk_perm, L.over, L.nb8, L.cnt8,
                     L.D, L.D32, L.Jc, L.Jc32, L.Dinv, L.Dinv32};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -214,6 +214,7 @@ static int setup_impl(const sem_mesh *m, const sem_setup_opts *o, hipStream_t s,
         rc = build_level(h->lv[0], N, E, x, y, z, gid, dir, f32_fine, bad, s);
         gid = nullptr;  // owned by the level from here on, also on failure
         dir = nullptr;
+        if (rc == SEM_OK) rc = build_copy_lists(h->lv[0], s);
         if (rc != SEM_OK) break;
         // coarse levels: coordinates interpolated from the finer level,
         // pointers by the line map.  px/py/pz hold the finer level's

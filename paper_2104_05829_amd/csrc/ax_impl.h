@@ -107,6 +107,72 @@ __device__ inline double ax_block_sum(double x, int tid, double *sh)
     return x;
 }
 
+// Decision and beta after an update (PcgDir), the same in every workgroup: the
+// first N = min(64, THREADS) lanes of the block (or of a field's wavefront) add
+// the records t, t + N, ... in order, eight loads in flight, then halve.
+// False: the vector's iteration has ended.  record: this block notes it.
+template <int THREADS>
+__device__ inline bool pcg_direction(const PcgDir &d, int64_t v, int tid, bool record, double *sh, double *beta)
+{
+    constexpr int N = THREADS < 64 ? THREADS : 64;
+    KrylovScalars *sc = d.sc + v;
+    // issued ahead of the records, waited for after them
+    const double tol2 = sc->tol2, rz_old = sc->rz2[d.parity];
+    const int maxit = sc->maxit, done = sc->done;
+    double rz = 0.0, rr = 0.0;
+    if (tid < N) {
+        const double2 *pr = reinterpret_cast<const double2 *>(d.pu + v * d.pst);
+        int64_t b = tid;
+        for (; b + 7 * N < d.nb; b += 8 * N) {
+            double2 x[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) x[q] = pr[b + q * N];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                rz += x[q].x;
+                rr += x[q].y;
+            }
+        }
+        for (; b < d.nb; b += N) {
+            const double2 x = pr[b];
+            rz += x.x;
+            rr += x.y;
+        }
+#pragma unroll
+        for (int st = 32; st >= 1; st >>= 1) {
+            const double a = __shfl_down(rz, st, 64), c = __shfl_down(rr, st, 64);
+            if (tid + st < N) {
+                rz += a;
+                rr += c;
+            }
+        }
+        rz = __shfl(rz, 0, 64);
+        rr = __shfl(rr, 0, 64);
+    }
+    if constexpr (THREADS > 64) {
+        if (tid == 0) {
+            sh[0] = rz;
+            sh[1] = rr;
+        }
+        __syncthreads();
+        rz = sh[0];
+        rr = sh[1];
+    }
+    if (done) return false;
+    const bool bad = !isfinite(rz) || !isfinite(rr);
+    const bool stop = bad || rr <= tol2 || d.iter >= maxit;
+    *beta = rz / rz_old;
+    if (record && tid == 0) {
+        sc->iters = d.iter;
+        sc->rr = rr;
+        sc->rz = rz;
+        sc->rz2[d.parity ^ 1] = rz;
+        if (bad) sc->status = SEM_EBREAKDOWN;
+        if (stop) sc->done = 1;
+    }
+    return !stop;
+}
+
 // One element column's constants: its rows of D and the end-point terms of D^T.
 template <int NQ, typename T>
 struct AxCol {
@@ -157,9 +223,9 @@ template <int NQ, typename T, bool HELM, bool VARK, bool DOT, int NW, int NI>
 __global__ void __launch_bounds__((AxShape<NQ>::threads(NW)), (ax_min_waves<NQ, T>()))
 ax_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
           const T *__restrict__ kc, const T *__restrict__ Dg, T h1, T h2,
-          const T *__restrict__ u, int64_t ldu, T *__restrict__ w, int64_t ldw, VSet vs,
+          const T *u, int64_t ldu, T *__restrict__ w, int64_t ldw, VSet vs,
           double *__restrict__ partial, int64_t pst, int64_t nvb, const int *__restrict__ skip,
-          int skip_stride)
+          int skip_stride, PcgDir dir)
 {
     using S = AxShape<NQ>;
     constexpr int TPE = S::TPE, EPB = S::EPB, LD = S::LD;
@@ -196,6 +262,44 @@ ax_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
         if constexpr (HELM) bn = B[b0];
         if constexpr (VARK) kn = kc[b0];
     }
+    // With a direction update a column needs p, r and Dinv.  Where the registers
+    // allow they are loaded ahead of their element, the first ahead of the sums
+    // that give beta (512 elements, N = 7: 10.6 -> 9.5 us); else a few planes at a
+    // time, since all three lines in flight would spill.
+    constexpr bool AHEAD = DOT && NQ <= 8 && NI == 1;
+    constexpr int CH = 4;
+    T rn[AHEAD ? NQ : 1];
+    double rr[AHEAD ? NQ : 1], dv[AHEAD ? NQ : 1];
+    bool dirn = false;
+    if constexpr (DOT) dirn = dir.sc != nullptr;
+    auto load_column = [&](int64_t o) {
+#pragma unroll
+        for (int k = 0; k < (AHEAD ? NQ : 1); ++k) rn[k] = u[v[0] * ldu + o + k * TPE];
+        if (dirn) {
+#pragma unroll
+            for (int k = 0; k < (AHEAD ? NQ : 1); ++k) {
+                dv[k] = dir.Dinv[o + k * TPE];
+                rr[k] = dir.r[v[0] * ldu + o + k * TPE];
+            }
+        }
+    };
+    if constexpr (AHEAD) {
+        const int64_t e0 = (int64_t)blockIdx.x * EPB + el;
+        load_column((e0 < E ? e0 : 0) * NP + ij);
+    }
+    double beta[NI];
+    if constexpr (DOT) {
+        if (dirn) {
+            __shared__ double sh[2];
+            any = false;
+#pragma unroll
+            for (int q = 0; q < NI; ++q) {
+                if (live[q]) live[q] = pcg_direction<S::THREADS>(dir, v[q], tid, blockIdx.x == 0, sh, &beta[q]);
+                any = any || live[q];
+            }
+            if (!any) return;
+        }
+    }
     for (int64_t vb = blockIdx.x; vb < nvb; vb += gridDim.x) {
         double dot[NI];
 #pragma unroll
@@ -208,10 +312,40 @@ ax_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
             const int64_t en = gx * EPB + el;
             const int64_t nbase = (en < E ? en : 0) * NP + ij;
             T ru[NI][NQ], rw[NI][NQ];
+            if constexpr (AHEAD) {
 #pragma unroll
-            for (int q = 0; q < NI; ++q)
+                for (int k = 0; k < NQ; ++k) ru[0][k] = rn[k];
+                if (dirn) {
 #pragma unroll
-                for (int k = 0; k < NQ; ++k) ru[q][k] = u[v[q] * ldu + base + k * TPE];
+                    for (int k = 0; k < NQ; ++k) ru[0][k] = dv[k] * rr[k] + beta[0] * ru[0][k];
+                    if (active)
+#pragma unroll
+                        for (int k = 0; k < NQ; ++k) dir.p[v[0] * ldu + base + k * TPE] = ru[0][k];
+                }
+            } else if (DOT && dirn) {
+#pragma unroll
+                for (int c = 0; c < NQ; c += CH) {
+                    double dk[CH];
+#pragma unroll
+                    for (int k = c; k < c + CH && k < NQ; ++k) dk[k - c] = dir.Dinv[base + k * TPE];
+#pragma unroll
+                    for (int q = 0; q < NI; ++q) {
+                        const int64_t o = v[q] * ldu + base;
+#pragma unroll
+                        for (int k = c; k < c + CH && k < NQ; ++k)
+                            ru[q][k] = dk[k - c] * dir.r[o + k * TPE] + beta[q] * dir.p[o + k * TPE];
+                        if (active && live[q])
+#pragma unroll
+                            for (int k = c; k < c + CH && k < NQ; ++k) dir.p[o + k * TPE] = ru[q][k];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < NI; ++q)
+#pragma unroll
+                    for (int k = 0; k < NQ; ++k) ru[q][k] = u[v[q] * ldu + base + k * TPE];
+            }
 #pragma unroll
             for (int q = 0; q < NI; ++q)
 #pragma unroll
@@ -281,6 +415,8 @@ ax_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
                     if constexpr (DOT)
                         if (active) dot[q] += (double)ru[q][k] * (double)out;
                 }
+            if constexpr (AHEAD)
+                if (gx < groups) load_column(nbase);
         }
         if constexpr (DOT) {
             __shared__ double sdot[(S::THREADS + 63) / 64];
@@ -315,14 +451,17 @@ ax_split_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
                 const T *__restrict__ kc, const T *__restrict__ Dg, T h1, T h2,
                 const T *__restrict__ u, int64_t ldu, T *__restrict__ w, int64_t ldw, VSet vs,
                 double *__restrict__ partial, int64_t pst, const int *__restrict__ skip,
-                int skip_stride)
+                int skip_stride, PcgDir dir)
 {
     using S = AxSplitShape<NQ>;
     constexpr int TPE = S::TPE, NP = S::NP, KS = S::KS, KPT = S::KPT, EPB = S::EPB, LD = S::LD;
     __shared__ T sD[NQ][NQ + 1];
     __shared__ T su[EPB][NQ][NQ][LD], sr[EPB][NQ][NQ][LD], ss[EPB][NQ][NQ][LD], st[EPB][NQ][NQ][LD];
     const int64_t v = vs.at(blockIdx.y);
-    if (skip != nullptr && skip[v * skip_stride] != 0) return;
+    // with a direction update the flag is looked at after the loads below
+    bool ahead = false;
+    if constexpr (DOT) ahead = dir.sc != nullptr;
+    if (!ahead && skip != nullptr && skip[v * skip_stride] != 0) return;
     u += v * ldu;
     w += v * ldw;
     const int tid = threadIdx.x;
@@ -335,17 +474,39 @@ ax_split_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
     const int64_t base = (active ? e : 0) * NP + ij;
     const AxCol<NQ, T> C(Dg, i, j);
     T uu[KPT], g[KPT][6], bb[HELM ? KPT : 1], cc[VARK ? KPT : 1], wr[KPT], ws[KPT];
+    double rr[DOT ? KPT : 1], dv[DOT ? KPT : 1];
     bb[0] = cc[0] = T(0);
 #pragma unroll
     for (int p = 0; p < KPT; ++p) {
         const int k = kg + p * KS;
         const int64_t q = base + (k < NQ ? k : 0) * TPE;
-        uu[p] = u[q];
+        if constexpr (DOT) {
+            uu[p] = dir.sc != nullptr ? dir.p[v * ldu + q] : u[q];
+            if (dir.sc != nullptr) {
+                rr[p] = dir.r[v * ldu + q];
+                dv[p] = dir.Dinv[q];
+            }
+        } else {
+            uu[p] = u[q];
+        }
         load_g6(G + q * 6, g[p]);
         if constexpr (HELM) bb[p] = B[q];
         if constexpr (VARK) cc[p] = kc[q];
     }
     for (int t = tid; t < NQ * NQ; t += S::THREADS) sD[t / NQ][t % NQ] = Dg[t];
+    if constexpr (DOT) {
+        if (dir.sc != nullptr) {
+            __shared__ double sh[2];
+            double beta;
+            if (!pcg_direction<S::THREADS>(dir, v, tid, blockIdx.x == 0, sh, &beta)) return;
+#pragma unroll
+            for (int p = 0; p < KPT; ++p) {
+                const int k = kg + p * KS;
+                uu[p] = dv[p] * rr[p] + beta * uu[p];
+                if (active && k < NQ) dir.p[v * ldu + base + k * TPE] = uu[p];
+            }
+        }
+    }
 #pragma unroll
     for (int p = 0; p < KPT; ++p) {
         const int k = kg + p * KS;
@@ -454,7 +615,8 @@ inline int64_t balanced_grid(int64_t groups, int64_t cap)
 // 13.8 / 22.4; three fields at N = 7, 64 6.5 / 3.9, 216 7.0 / 7.3).  The two
 // forms give the same bits per point.  Their partial sums cover different
 // points, and a batch has to have those of its single fields: with partial
-// sums the line lies at 2^17 points for any number of fields.
+// sums the line lies at 2^17 points for any number of fields (with the direction
+// update, 512 elements at N = 7: 10.6 / 13.2).
 template <int NQ>
 inline bool ax_spread(const Level &L, int nf, bool dot)
 {
@@ -489,7 +651,7 @@ template <int NQ, typename T>
 static int ax_split_launch(const Level &L, const T *G, const T *B, const T *D, const T *u, int64_t ldu,
                            T *w, int64_t ldw, const VSet &vs, double h1, double h2, const T *k,
                            double *partial, int64_t pst, int64_t *nblocks, hipStream_t s,
-                           const int *skip, int skip_stride)
+                           const int *skip, int skip_stride, const PcgDir &dir)
 {
     using S = AxSplitShape<NQ>;
     const int64_t nb = (L.E + S::EPB - 1) / S::EPB;
@@ -498,7 +660,7 @@ static int ax_split_launch(const Level &L, const T *G, const T *B, const T *D, c
     const dim3 grid((unsigned)nb, (unsigned)vs.n), block(S::THREADS);
 #define SEM_AX_LAUNCH(H, V, P)                                                                 \
     hipLaunchKernelGGL((ax_split_kernel<NQ, T, H, V, P>), grid, block, 0, s, L.E, G, B, k, D, \
-                       (T)h1, (T)h2, u, ldu, w, ldw, vs, partial, pst, skip, skip_stride)
+                       (T)h1, (T)h2, u, ldu, w, ldw, vs, partial, pst, skip, skip_stride, dir)
     SEM_AX_FORMS(true)
 #undef SEM_AX_LAUNCH
     SEM_HIP(hipGetLastError());
@@ -511,7 +673,7 @@ template <int NQ, typename T, int NW, int NI>
 static int ax_launch(const Level &L, const T *G, const T *B, const T *D, const T *u, int64_t ldu,
                      T *w, int64_t ldw, const VSet &vs, double h1, double h2, const T *k,
                      double *partial, int64_t pst, int64_t *nblocks, hipStream_t s, const int *skip,
-                     int skip_stride)
+                     int skip_stride, const PcgDir &dir)
 {
     using S = AxShape<NQ>;
     constexpr int NF = NW * NI;
@@ -527,7 +689,7 @@ static int ax_launch(const Level &L, const T *G, const T *B, const T *D, const T
 #define SEM_AX_LAUNCH(H, V, P)                                                                 \
     hipLaunchKernelGGL((ax_kernel<NQ, T, H, V, P, NW, NI>), grid, block, 0, s, L.E, G, B, k,  \
                        D, (T)h1, (T)h2, u, ldu, w, ldw, vs, partial, pst, dot ? nvb : nb,     \
-                       skip, skip_stride)
+                       skip, skip_stride, dir)
     SEM_AX_FORMS(NF == 1)
 #undef SEM_AX_LAUNCH
     SEM_HIP(hipGetLastError());
@@ -538,14 +700,14 @@ template <int NQ, typename T>
 static int ax_dispatch(const Level &L, const T *G, const T *B, const T *D, const T *u, int64_t ldu,
                        T *w, int64_t ldw, const VSet &vs, double h1, double h2, const T *k,
                        double *partial, int64_t pst, int64_t *nblocks, hipStream_t s, const int *skip,
-                       int skip_stride)
+                       int skip_stride, const PcgDir &dir)
 {
     if (ax_spread<NQ>(L, vs.n, partial != nullptr))
         return ax_split_launch<NQ, T>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, k, partial, pst, nblocks, s,
-                                      skip, skip_stride);
+                                      skip, skip_stride, dir);
 #define SEM_AX_NF(NW, NI)                                                                      \
     return ax_launch<NQ, T, NW, NI>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, k, partial, pst,  \
-                                    nblocks, s, skip, skip_stride)
+                                    nblocks, s, skip, skip_stride, dir)
     if (vs.n == 1) SEM_AX_NF(1, 1);
     if constexpr (NQ <= 8) {
         if (k == nullptr) {
@@ -566,7 +728,7 @@ static int ax_dispatch(const Level &L, const T *G, const T *B, const T *D, const
         VSet one{0, 0u};
         one.push(vs.at(q));
         SEM_TRY((ax_launch<NQ, T, 1, 1>(L, G, B, D, u, ldu, w, ldw, one, h1, h2, k, partial, pst, nblocks,
-                                     s, skip, skip_stride)));
+                                     s, skip, skip_stride, dir)));
     }
     return SEM_OK;
 }
@@ -574,7 +736,8 @@ static int ax_dispatch(const Level &L, const T *G, const T *B, const T *D, const
 template <typename T>
 int launch_ax_multi(const Level &L, const T *G, const T *B, const T *D, const T *u, int64_t ldu, T *w,
                     int64_t ldw, const VSet &vs, double h1, double h2, const T *k, double *partial,
-                    int64_t pst, int64_t *nblocks, hipStream_t s, const int *skip, int skip_stride)
+                    int64_t pst, int64_t *nblocks, hipStream_t s, const int *skip, int skip_stride,
+                    const PcgDir &dir)
 {
     if (vs.n <= 0) return SEM_OK;
     if (sizeof(T) == 4 && partial != nullptr) {
@@ -584,7 +747,7 @@ int launch_ax_multi(const Level &L, const T *G, const T *B, const T *D, const T 
 #define SEM_AX_CASE(NQ)                                                                        \
     case NQ:                                                                                   \
         return ax_dispatch<NQ, T>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, k, partial, pst,    \
-                                  nblocks, s, skip, skip_stride);
+                                  nblocks, s, skip, skip_stride, dir);
     switch (L.nq) {
         SEM_AX_CASE(2) SEM_AX_CASE(3) SEM_AX_CASE(4) SEM_AX_CASE(5) SEM_AX_CASE(6)
         SEM_AX_CASE(7) SEM_AX_CASE(8) SEM_AX_CASE(9) SEM_AX_CASE(10) SEM_AX_CASE(11)

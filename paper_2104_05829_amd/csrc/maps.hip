@@ -252,4 +252,52 @@ int build_gs_chunks(Level &L, hipStream_t s)
     return SEM_OK;
 }
 
+// the copies of every copy of a segment (one thread per segment); *longest
+// receives the largest segment
+__global__ void copy_lists_kernel(int64_t nseg, int64_t nL, const int32_t *__restrict__ perm,
+                                  const int32_t *__restrict__ offs, const double *__restrict__ W,
+                                  int32_t *__restrict__ nb8, uint8_t *__restrict__ cnt8, int *longest)
+{
+    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= nseg) return;
+    const int a = offs[q], len = offs[q + 1] - a;
+    if (len > 8) {
+        atomicMax(longest, len);
+        return;
+    }
+    for (int o = 0; o < len; ++o) {
+        const int l = perm[a + o];
+        if (!(W[l] > 0.0)) return;  // Dirichlet: the sum is not used
+        cnt8[l] = (uint8_t)len;
+        for (int c = 0; c < len; ++c) nb8[c * nL + l] = perm[a + c];
+    }
+}
+
+int build_copy_lists(Level &L, hipStream_t s)
+{
+    if (L.nL > kFewPoints) return SEM_OK;
+    DevBuf longest;
+    SEM_HIP(hipMalloc(&longest.p, sizeof(int)));
+    SEM_HIP(hipMemsetAsync(longest.p, 0, sizeof(int), s));
+    SEM_HIP(hipMalloc(&L.nb8, sizeof(int32_t) * 8 * L.nL));
+    SEM_HIP(hipMalloc(&L.cnt8, L.nL));
+    SEM_HIP(hipMemsetAsync(L.nb8, 0xFF, sizeof(int32_t) * 8 * L.nL, s));
+    SEM_HIP(hipMemsetAsync(L.cnt8, 1, L.nL, s));
+    int h = 0;
+    if (L.nseg > 0) {
+        hipLaunchKernelGGL(copy_lists_kernel, dim3((unsigned)((L.nseg + 255) / 256)), dim3(256), 0, s, L.nseg,
+                           L.nL, L.perm, L.offs, L.W, L.nb8, L.cnt8, (int *)longest.p);
+        SEM_HIP(hipGetLastError());
+    }
+    SEM_HIP(hipMemcpyAsync(&h, longest.p, sizeof(int), hipMemcpyDeviceToHost, s));
+    SEM_HIP(hipStreamSynchronize(s));
+    if (h > 8) {
+        SEM_HIP(hipFree(L.nb8));
+        L.nb8 = nullptr;
+        SEM_HIP(hipFree(L.cnt8));
+        L.cnt8 = nullptr;
+    }
+    return SEM_OK;
+}
+
 }  // namespace semx

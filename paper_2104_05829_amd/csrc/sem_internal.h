@@ -38,6 +38,9 @@ constexpr int kMaxGauss = 16;
 // (the operator's partial-sum buffer holds one value per workgroup)
 constexpr int kAxMaxBlocksPerCU = 16;
 constexpr int kMaxLevels = 4;
+// level-0 points up to which a Jacobi-PCG update sums the copies of each node
+// itself instead of following a gather-scatter pass
+constexpr int64_t kFewPoints = 1 << 18;
 // largest number of vectors one batched operator / gather-scatter / solve
 // call processes together
 constexpr int kMaxRhs = SEM_MAX_RHS;
@@ -104,6 +107,20 @@ struct KrylovScalars {
     int maxit;
 };
 
+// The direction update of a Jacobi-PCG iteration, folded into the operator of
+// the next one: the operator forms p = Dinv r + beta p as it reads p, and
+// writes it back.  beta and the convergence decision come from the partial
+// sums (W r Dinv r, W r r) of the update, summed in one order by every
+// workgroup.  p and r have the leading dimension of the operator's input.
+struct PcgDir {
+    KrylovScalars *sc = nullptr;  // null: no direction update
+    const double *pu = nullptr;   // vector v's records at pu + v * pst
+    int64_t pst = 0, nb = 0;
+    const double *r = nullptr, *Dinv = nullptr;
+    double *p = nullptr;
+    int parity = 0, iter = 0;     // of the iteration the update belongs to (1-based)
+};
+
 // One polynomial order of the discretisation on the handle's mesh.
 struct Level {
     int N = 0, nq = 0, np = 0;
@@ -124,6 +141,11 @@ struct Level {
     // starts a segment, -1 past the chunk's end
     int32_t *chunk_perm = nullptr;
     int32_t *over = nullptr;                          // segments longer than 64 copies
+    // level 0, up to kFewPoints points with at most 8 copies of a node: copies of
+    // each copy's node in ascending order, nb8 [8][nL] (-1 past the last), and
+    // their number cnt8 [nL] (1 on unshared and Dirichlet copies)
+    int32_t *nb8 = nullptr;
+    uint8_t *cnt8 = nullptr;
     double *D = nullptr;   // Dh [nq][nq] (row = point), then the weights rho [nq]
     float *D32 = nullptr;
     // interpolation from the next coarser level's nodes to this level's
@@ -221,6 +243,7 @@ struct Workspace {
     int vg_next = 0;
     bool vg_broken = false;  // capture failed once: launch kernel by kernel
     hipStream_t cap = nullptr;
+    hipEvent_t chk[2] = {};  // scalars of a batch of iterations copied to the host
     PhaseClock clk;
 };
 
@@ -277,11 +300,13 @@ int launch_gs_op(const Level &L, T *v, int op, hipStream_t s);
 // one launch for the whole batch; the element operator reads each element's
 // geometric factors once for all vectors.  skip (nullable) + v * skip_stride
 // is vector v's flag: vectors flagged at launch time are left untouched.
-// Operator partial sums of u_v.w_v go to partial[v * pst + block].
+// Operator partial sums of u_v.w_v go to partial[v * pst + block].  dir (FP64,
+// with partial sums): u is dir.p, updated on the way.
 template <typename T>
 int launch_ax_multi(const Level &L, const T *G, const T *B, const T *D, const T *u, int64_t ldu, T *w,
                     int64_t ldw, const VSet &vs, double h1, double h2, const T *k, double *partial,
-                    int64_t pst, int64_t *nblocks, hipStream_t s, const int *skip, int skip_stride);
+                    int64_t pst, int64_t *nblocks, hipStream_t s, const int *skip, int skip_stride,
+                    const PcgDir &dir = PcgDir{});
 
 template <typename T>
 int launch_gs_multi(const Level &L, T *v, int64_t ld, const VSet &vs, hipStream_t s,
@@ -346,6 +371,7 @@ int launch_schwarz(const Level &L, bool ras, const float *r, const float *t, flo
 int build_maps(Level &L, const int64_t *gid_dev, const uint8_t *dir_dev, const double *x,
                const double *y, const double *z, int *bad_dev, hipStream_t s);
 int build_gs_chunks(Level &L, hipStream_t s);
+int build_copy_lists(Level &L, hipStream_t s);
 
 int host_gll(int N, double *xi, double *rho, double *D);
 void host_interp(int ns, const double *xs, int nt, const double *xt, double *J);

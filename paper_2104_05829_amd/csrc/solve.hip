@@ -322,6 +322,94 @@ __global__ void pcg_update_fused_kernel(int64_t n, VSet vs, int64_t ld, int64_t 
     block_sum_store<2>(s, partial + v * pst);
 }
 
+// The same update for few points, on the unassembled w = A_L p: a thread takes
+// PPT copies and sums the copies of each one's node (as QQ^T does, from 0 in
+// ascending order), so no gather-scatter pass runs between the operator and
+// the update; cnt8 null: w is assembled.  All loads are issued before the
+// operator's partials are summed: the kernel is one chain of copy list,
+// gathered values and reduction.
+template <int PPT>
+__global__ void __launch_bounds__(kRB)
+pcg_update_few_kernel(int64_t n, VSet vs, int64_t ld, int64_t ldx, KrylovScalars *sc, int parity,
+                      const double *__restrict__ pax, int64_t pst_ax, int64_t nbax,
+                      const double *__restrict__ p, const double *__restrict__ w,
+                      const int32_t *__restrict__ nb8, const uint8_t *__restrict__ cnt8,
+                      const double *__restrict__ Dinv, const double *__restrict__ W,
+                      double *__restrict__ x, double *__restrict__ r, double *__restrict__ partial,
+                      int64_t pst)
+{
+    const int64_t v = vsel(vs);
+    sc += v;
+    const int done = sc->done;  // looked at with the sum of the partials
+    const double rz = sc->rz2[parity];
+    p += v * ld;
+    w += v * ld;
+    r += v * ld;
+    x += v * ldx;
+    int64_t at[PPT];
+    bool act[PPT];
+    int cnt[PPT];
+    double pi[PPT], xi[PPT], r0[PPT], di[PPT], wi[PPT], ws[PPT], w1[PPT];
+#pragma unroll
+    for (int q = 0; q < PPT; ++q) {
+        const int64_t i = ((int64_t)blockIdx.x * PPT + q) * kRB + threadIdx.x;
+        act[q] = i < n;
+        at[q] = act[q] ? i : 0;
+        cnt[q] = act[q] && cnt8 ? cnt8[at[q]] : 1;
+        pi[q] = p[at[q]];
+        xi[q] = x[at[q]];
+        r0[q] = r[at[q]];
+        di[q] = Dinv[at[q]];
+        wi[q] = W[at[q]];
+        w1[q] = w[at[q]];
+    }
+#pragma unroll
+    for (int q = 0; q < PPT; ++q) {
+        ws[q] = w1[q];
+        if (cnt[q] > 1) {
+            int32_t id[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) id[c] = c < cnt[q] ? nb8[c * n + at[q]] : 0;
+            double wv[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) wv[c] = c < cnt[q] ? w[id[c]] : 0.0;
+            ws[q] = 0.0;
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                if (c < cnt[q]) ws[q] += wv[c];
+        }
+    }
+    double res[1];
+    sum_partials<1>(pax + v * pst_ax, nbax, res);
+    if (done) return;
+    const double pw = res[0];
+    if (!(pw > 0.0) || !isfinite(pw)) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            sc->pw = pw;
+            sc->status = SEM_EBREAKDOWN;
+            sc->done = 1;
+        }
+        return;
+    }
+    const double a = rz / pw;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        sc->pw = pw;
+        sc->alpha = a;
+    }
+    double s[2] = {0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < PPT; ++q)
+        if (act[q]) {
+            x[at[q]] = xi[q] + a * pi[q];
+            const double ri = r0[q] - a * ws[q];
+            r[at[q]] = ri;
+            const double wr = wi[q] * ri;
+            s[0] += wr * di[q] * ri;
+            s[1] += wr * ri;
+        }
+    block_sum_store<2>(s, partial + v * pst);
+}
+
 // Jacobi-PCG direction update with beta and the convergence decision taken
 // by every block from the update's partials (identical in all blocks);
 // block 0 records them.  `iter` is the 1-based number of this iteration.
@@ -883,6 +971,8 @@ void free_workspace(sem_handle h)
     for (auto &g : w.vg)
         if (g.exec) (void)hipGraphExecDestroy(g.exec);
     if (w.cap) (void)hipStreamDestroy(w.cap);
+    for (auto &e : w.chk)
+        if (e) (void)hipEventDestroy(e);
     free_vectors(w);
     free_projection(w);
     if (w.sz_U) (void)hipFree(w.sz_U);
@@ -1250,35 +1340,82 @@ static PcgBufs ws_bufs(sem_handle h, const Level &L)
     return PcgBufs{h->ws.partial, h->ws.pst, h->ws.partial_ax, h->ws.pst_ax, L.Dinv};
 }
 
+// Convergence decision after the last update of a batch of iterations (one
+// block per vector), for the host; the next operator takes it again by itself.
+__global__ void pcg_decide_kernel(VSet vs, KrylovScalars *sc, int iter, const double *__restrict__ pu,
+                                  int64_t pst, int64_t nbu)
+{
+    const int64_t v = vsel(vs);
+    sc += v;
+    if (sc->done) return;
+    double res[2];
+    sum_partials<2>(pu + v * pst, nbu, res);
+    if (threadIdx.x == 0) {
+        const bool bad = !isfinite(res[0]) || !isfinite(res[1]);
+        sc->iters = iter;
+        sc->rr = res[1];
+        sc->rz = res[0];
+        if (bad) sc->status = SEM_EBREAKDOWN;
+        if (bad || res[1] <= sc->tol2 || iter >= sc->maxit) sc->done = 1;
+    }
+}
+
 // enqueue Jacobi-PCG iterations first_iter .. first_iter+iters-1 (1-based)
-// on level L for the batch vs: operator with fused (p, A_L p), QQ^T, update
-// with alpha, and direction update with beta and the convergence decision --
-// four kernels per iteration, no single-block reduction kernels
+// on level L for the batch vs: operator with the direction update and decision
+// of the iteration before and the partial sums of (p, A_L p), QQ^T, update with
+// alpha -- three kernels per iteration (two where the update sums the copies
+// itself), and one for the decision of the last
 static int pcg_iterations(sem_handle h, const Level &L, const VSet &vs, const double *k, double h1,
                           double h2, const KrylovVecs &kv, const PcgBufs &pb, int first_iter,
                           int iters, hipStream_t s, bool timed = false)
 {
     Workspace &ws = h->ws;
     const int64_t n = L.nL;
-    const int nbv = red_grid(n);
+    const bool few = L.nb8 != nullptr;  // the update sums the copies itself
+    // one copy per thread up to 2^16 points, two above (512 elements at N = 7:
+    // half as many records for every workgroup of the next operator to sum)
+    const int ppt = n > (1 << 16) ? 2 : 1;
+    const int nbv = few ? (int)((n + kRB * ppt - 1) / (kRB * ppt)) : red_grid(n);
     const int *skip = &kv.sc[0].done;
     for (int c = 0; c < iters; ++c) {
         const int it = first_iter + c;
         const int parity = (it - 1) & 1;
         int64_t nbax = 0;
+        PcgDir dir;
+        if (it > 1) {
+            dir.sc = kv.sc;
+            dir.pu = pb.partial;
+            dir.pst = pb.pst;
+            dir.nb = nbv;
+            dir.r = kv.r;
+            dir.Dinv = pb.Dinv;
+            dir.p = kv.p;
+            dir.parity = parity ^ 1;
+            dir.iter = it - 1;
+        }
         SEM_TRY(launch_ax_multi<double>(L, L.G, L.B, L.D, kv.p, n, kv.w, n, vs, h1, h2, k,
-                                        pb.partial_ax, pb.pst_ax, &nbax, s, skip, kScStride));
+                                        pb.partial_ax, pb.pst_ax, &nbax, s, skip, kScStride, dir));
         if (timed) SEM_TRY(clock_mark(ws, kPhaseAx, s));
-        SEM_TRY(launch_gs_multi<double>(L, kv.w, n, vs, s, skip, kScStride));
-        if (timed) SEM_TRY(clock_mark(ws, kPhaseGs, s));
-        LAUNCH_B(pcg_update_fused_kernel, n, vs, s, n, vs, n, kv.ldx, kv.sc, parity,
-                 (const double *)pb.partial_ax, pb.pst_ax, nbax, (const double *)kv.p,
-                 (const double *)kv.w, pb.Dinv, L.W, kv.x, kv.r, pb.partial, pb.pst);
-        LAUNCH_B(pcg_p_fused_kernel, n, vs, s, n, vs, n, kv.sc, parity, it,
-                 (const double *)pb.partial, pb.pst, (int64_t)nbv, pb.Dinv, (const double *)kv.r,
-                 kv.p);
+        const bool apart = !few || (timed && ws.clk.on);  // timers: QQ^T as a pass of its own
+        if (apart) {
+            SEM_TRY(launch_gs_multi<double>(L, kv.w, n, vs, s, skip, kScStride));
+            if (timed) SEM_TRY(clock_mark(ws, kPhaseGs, s));
+        }
+        if (few) {
+            auto kern = ppt == 2 ? pcg_update_few_kernel<2> : pcg_update_few_kernel<1>;
+            hipLaunchKernelGGL(kern, dim3((unsigned)nbv, (unsigned)vs.n), dim3(kRB), 0, s, n, vs, n, kv.ldx, kv.sc, parity, (const double *)pb.partial_ax, pb.pst_ax, nbax,
+                               (const double *)kv.p, (const double *)kv.w, (const int32_t *)L.nb8,
+                               apart ? (const uint8_t *)nullptr : L.cnt8, pb.Dinv, L.W, kv.x, kv.r, pb.partial, pb.pst);
+            SEM_HIP(hipGetLastError());
+        } else {
+            LAUNCH_B(pcg_update_fused_kernel, n, vs, s, n, vs, n, kv.ldx, kv.sc, parity,
+                     (const double *)pb.partial_ax, pb.pst_ax, nbax, (const double *)kv.p,
+                     (const double *)kv.w, pb.Dinv, L.W, kv.x, kv.r, pb.partial, pb.pst);
+        }
         if (timed) SEM_TRY(clock_mark(ws, kPhaseVec, s));
     }
+    LAUNCH_1B(pcg_decide_kernel, vs, s, vs, kv.sc, first_iter + iters - 1, (const double *)pb.partial,
+              pb.pst, (int64_t)nbv);
     return SEM_OK;
 }
 
@@ -1531,6 +1668,45 @@ static int coarse_csr_solve(sem_handle h, const Level &L, const VSet &vs, const 
     }
 #undef LAUNCH_NB
     LAUNCH_B(csr_scatter_kernel, n, vs, s, n, vs, (const int32_t *)L.cs_uid, (const double *)L.cs_xu, nf, x, n);
+    return SEM_OK;
+}
+
+// Jacobi-PCG iterations in batches of check_every until every vector of `all`
+// is done, the next batch enqueued before the host reads the scalars of the
+// one before: the GPU does not wait for the host (64 elements at N = 7: 19 us
+// of every batch of eight, 88 us of kernels), and the batch enqueued past the
+// end finds the flags set.  On return host_sc holds the final scalars.
+static int pcg_batches(sem_handle h, const Level &F, const VSet &all, const sem_solve_opts *o,
+                       const SolveCfg &cfg, const KrylovVecs &kv, hipStream_t s)
+{
+    Workspace &w = h->ws;
+    const size_t bytes = kMaxRhs * sizeof(KrylovScalars);
+    for (auto &e : w.chk)
+        if (!e) SEM_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    KrylovScalars *slot[2] = {w.host_sc, w.host_sc + kMaxRhs};
+    auto post = [&](int q) -> int {
+        SEM_HIP(hipMemcpyAsync(slot[q], w.sc, bytes, hipMemcpyDeviceToHost, s));
+        SEM_HIP(hipEventRecord(w.chk[q], s));
+        return SEM_OK;
+    };
+    VSet act = all;
+    int it = 0, q = 0;
+    SEM_TRY(post(q));  // the scalars of the start
+    for (;;) {
+        SEM_TRY(pcg_iterations(h, F, act, o->k, o->h1, o->h2, kv, ws_bufs(h, F), it + 1, cfg.check_every, s));
+        it += cfg.check_every;
+        SEM_TRY(post(q ^ 1));
+        SEM_HIP(hipEventSynchronize(w.chk[q]));
+        VSet left{0, 0u};
+        for (int m = 0; m < act.n; ++m)
+            if (!slot[q][act.at(m)].done) left.push(act.at(m));
+        if (left.n == 0) break;
+        act = left;
+        q ^= 1;
+    }
+    // the copy still in flight ends with the same scalars
+    SEM_HIP(hipEventSynchronize(w.chk[q ^ 1]));
+    if (q != 0) std::copy(slot[1], slot[1] + kMaxRhs, slot[0]);
     return SEM_OK;
 }
 
@@ -2029,15 +2205,19 @@ int pcg_solve(sem_handle h, int nv, const double *b, double *x, int64_t ld, cons
         SEM_TRY(pcg_start(F, all, o->k, o->h1, o->h2, bs, ldbs, kv, ws_bufs(h, F), zero, o->tol,
                           o->maxit, ref, s));
         SEM_TRY(clock_mark(w, kPhaseVec, s));
-        SEM_TRY(sync_point(false));
-        VSet act = live_set(w, all);
-        int it = 0;
-        while (act.n > 0) {
-            SEM_TRY(pcg_iterations(h, F, act, o->k, o->h1, o->h2, kv, ws_bufs(h, F), it + 1,
-                                   cfg.check_every, s, true));
-            it += cfg.check_every;
+        if (w.clk.on) {
             SEM_TRY(sync_point(false));
-            act = live_set(w, act);
+            VSet act = live_set(w, all);
+            int it = 0;
+            while (act.n > 0) {
+                SEM_TRY(pcg_iterations(h, F, act, o->k, o->h1, o->h2, kv, ws_bufs(h, F), it + 1,
+                                       cfg.check_every, s, true));
+                it += cfg.check_every;
+                SEM_TRY(sync_point(false));
+                act = live_set(w, act);
+            }
+        } else {
+            SEM_TRY(pcg_batches(h, F, all, o, cfg, kv, s));
         }
     } else {
         // r = b - A x ; z = M r ; p = z ; rz = (z, r)
