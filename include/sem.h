@@ -437,14 +437,13 @@ SEM_API int sem_gll(int N, double *xi, double *rho, double *D);
  * v_L . out_L = sum over elements and Gauss points of rho~ |det X| v c.grad w,
  * exact for polynomial integrands of degree <= 2M - 1 per variable.
  *
- * sem_advect_setup: builds J, Jd and the metric factors for the rule
+ * sem_advect_setup: builds J and Jd and checks the element maps for the rule
  *   (M = 0: the smallest rule exact for degree 3N, M = ceil((3N+1)/2)); M must
  *   be N+1..16 and, for the compiled kernels, one of the two rules
  *   ceil((3N+1)/2) or ceil((3N+1)/2) + 1, with N <= 7; *M_used (nullable)
  *   receives M.  variant picks the element kernel (the 2D and 3D thread blocks
  *   of Sec. 3.3, enum sem_advect_variant); both give the same result up to
- *   rounding order.  Device memory 72 M^3 bytes per element (freed by sem_free or
- *   a new setup).  Synchronises `stream`.  SEM_EMESH if det X <= 0 at a Gauss
+ *   rounding order.  Synchronises `stream`.  SEM_EMESH if det X <= 0 at a Gauss
  *   point.
  * sem_advect_velocity: ct [E][3][M^3] (point index a + M b + M^2 c, a along r)
  *   from the velocity c (three level-0 L-vectors at c + d * ldc, d = x, y, z;

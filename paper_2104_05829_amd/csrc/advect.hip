@@ -7,9 +7,8 @@
 // Per element, with the M-point Gauss rule in each direction:
 //   J [M][nq]  interpolation from the GLL nodes to the Gauss points,
 //   Jd = J Dh  derivative of the interpolant at the Gauss points,
-//   F [9][M^3] = rho~ |det X| dr_q/dx_d (index 3 q + d), X = dx/dr of the
-//              interpolated element map (built once per mesh),
-//   ct [3][M^3] = F . (J3 c)     (once per velocity field),
+//   ct [3][M^3] = rho~ |det X| dr_q/dx . (J3 c), X = dx/dr of the interpolated
+//              element map (once per velocity field),
 //   out = J3^T sum_q ct_q d_q(J3 w)   (every advected field).
 //
 // Thread layout (one workgroup per element, M^2 lanes rounded up to whole
@@ -19,8 +18,7 @@
 // j-contraction on the columns with the lane's rows of J and Jd in registers,
 // and the k-contractions forward and back run entirely in registers, the
 // transposed interpolation along c being accumulated point by point so the
-// Gauss-point integrand is never stored.  Two LDS buffers alternate between
-// the stages.
+// Gauss-point integrand is never stored.
 #include <algorithm>
 #include <vector>
 
@@ -35,60 +33,16 @@ struct AdvShape {
     static constexpr int NP = NQ * NQ * NQ;
     static constexpr int MM = M * M;
     static constexpr int M3 = MM * M;
-    static constexpr int SA = (2 * NQ * NQ * M > NQ * MM) ? 2 * NQ * NQ * M : NQ * MM;
-    static constexpr int SB = NQ * NQ * M;  // >= NP since M >= NQ
     static constexpr int THREADS = ((MM + 63) / 64) * 64;
 };
 
-// stage 1: rows (k, j) of u in LDS (sU [k][j][i]) -> sP [k][j][a] = J u,
-// sQ [k][j][a] = Jd u (contraction over i)
-template <int NQ, int M>
-__device__ __forceinline__ void stage_rows(const double *__restrict__ J, const double *__restrict__ Jd,
-                                           const double *sU, double *sP, double *sQ)
-{
-    const int t = threadIdx.x;
-    if (t < NQ * NQ) {
-        const int j = t % NQ, k = t / NQ;
-        double r[NQ];
-#pragma unroll
-        for (int i = 0; i < NQ; ++i) r[i] = sU[(k * NQ + j) * NQ + i];
-#pragma unroll
-        for (int a = 0; a < M; ++a) {
-            double p = 0.0, q = 0.0;
-#pragma unroll
-            for (int i = 0; i < NQ; ++i) {
-                p += J[a * NQ + i] * r[i];
-                q += Jd[a * NQ + i] * r[i];
-            }
-            sP[(k * NQ + j) * M + a] = p;
-            sQ[(k * NQ + j) * M + a] = q;
-        }
-    }
-}
-
-// stage 2 on the lane's Gauss column (b, a): Tr[k] = (J_b . sQ)[k], Ts[k] =
-// (Jd_b . sP)[k], Tt[k] = (J_b . sP)[k] (contraction over j)
-template <int NQ, int M>
-__device__ __forceinline__ void stage_cols(const double *Jb, const double *Jdb, int a, const double *sP,
-                                           const double *sQ, double *Tr, double *Ts, double *Tt)
-{
-#pragma unroll
-    for (int k = 0; k < NQ; ++k) {
-        double xr = 0.0, xs = 0.0, xt = 0.0;
-#pragma unroll
-        for (int j = 0; j < NQ; ++j) {
-            const double p = sP[(k * NQ + j) * M + a];
-            const double q = sQ[(k * NQ + j) * M + a];
-            xr += Jb[j] * q;
-            xs += Jdb[j] * p;
-            xt += Jb[j] * p;
-        }
-        Tr[k] = xr;
-        Ts[k] = xs;
-        Tt[k] = xt;
-    }
-}
-
+// The stages of a field and the last one of the field before share the
+// intervals between barriers, three a field (six when every stage waited for
+// the one before in two shared buffers): stage, barrier, i-contraction on the
+// first wavefront beside the previous field's a -> i on the last, barrier, the
+// columns, barrier, b -> j (24^3 elements, M = 11, three fields 268 -> 253 us).  A
+// workgroup of one wavefront (M <= 8) ends each field before the next, which
+// costs it nothing (deferred: M = 8 61 -> 64 us).
 template <int NQ, int M>
 __global__ void __launch_bounds__((AdvShape<NQ, M>::THREADS)) __attribute__((amdgpu_waves_per_eu(1, 8)))
     advect_kernel(int64_t E, const double *__restrict__ J, const double *__restrict__ Jd,
@@ -96,14 +50,13 @@ __global__ void __launch_bounds__((AdvShape<NQ, M>::THREADS)) __attribute__((amd
                   double *__restrict__ out, int64_t ldo)
 {
     using S = AdvShape<NQ, M>;
-    constexpr int NP = S::NP, MM = S::MM, M3 = S::M3, TH = S::THREADS;
-    __shared__ double sA[S::SA];
-    __shared__ double sB[S::SB];
-    double *sP = sA, *sQ = sA + NQ * NQ * M, *sG = sA;
-    double *sU = sB, *sH = sB;
+    constexpr int NP = S::NP, MM = S::MM, M3 = S::M3, TH = S::THREADS, RM = NQ * NQ * M;
+    __shared__ double sU[NP], sP[RM], sQ[RM], sG[NQ * MM], sH[RM];
     const int t = threadIdx.x;
     const bool col = t < MM;
     const int a = col ? t % M : 0, b = col ? t / M : 0;
+    constexpr bool PIPE = TH >= 128;             // more than one wavefront
+    const int t5 = PIPE ? t - (TH - 64) : t;  // lanes of the last contraction
     double Jb[NQ], Jdb[NQ];
 #pragma unroll
     for (int j = 0; j < NQ; ++j) {
@@ -121,6 +74,24 @@ __global__ void __launch_bounds__((AdvShape<NQ, M>::THREADS)) __attribute__((amd
             un[q] = i < NP ? w[blockIdx.x * (int64_t)NP + i] : 0.0;
         }
     }
+    // contraction over a -> i on GLL rows (k, j) of the field whose sH is ready
+    auto finish = [&](double *o5) {
+        if (t5 >= 0 && t5 < NQ * NQ) {
+            double h[M];
+#pragma unroll
+            for (int a2 = 0; a2 < M; ++a2) h[a2] = sH[t5 * M + a2];
+            double o[NQ];
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) o[i] = 0.0;
+#pragma unroll
+            for (int a2 = 0; a2 < M; ++a2)
+#pragma unroll
+                for (int i = 0; i < NQ; ++i) o[i] += J[a2 * NQ + i] * h[a2];
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) o5[t5 * NQ + i] = o[i];
+        }
+    };
+    double *prev = nullptr;
     for (int64_t e = blockIdx.x; e < E; e += gridDim.x) {
         double c0[M], c1[M], c2[M];
         for (int f = 0; f < nf; ++f) {
@@ -154,13 +125,12 @@ __global__ void __launch_bounds__((AdvShape<NQ, M>::THREADS)) __attribute__((amd
                     }
                 }
             }
-            __syncthreads();
+            __syncthreads();  // sU staged; the previous field's sH complete
             // contraction over i on GLL rows (k, j)
             if (t < NQ * NQ) {
-                const int j = t % NQ, k = t / NQ;
                 double r[NQ];
 #pragma unroll
-                for (int i = 0; i < NQ; ++i) r[i] = sU[(k * NQ + j) * NQ + i];
+                for (int i = 0; i < NQ; ++i) r[i] = sU[t * NQ + i];
 #pragma unroll
                 for (int a2 = 0; a2 < M; ++a2) {
                     double p = 0.0, q = 0.0;
@@ -169,12 +139,13 @@ __global__ void __launch_bounds__((AdvShape<NQ, M>::THREADS)) __attribute__((amd
                         p += J[a2 * NQ + i] * r[i];
                         q += Jd[a2 * NQ + i] * r[i];
                     }
-                    sP[(k * NQ + j) * M + a2] = p;
-                    sQ[(k * NQ + j) * M + a2] = q;
+                    sP[t * M + a2] = p;
+                    sQ[t * M + a2] = q;
                 }
             }
+            if constexpr (PIPE)
+                if (prev) finish(prev);
             __syncthreads();
-            double G[NQ];
             if (col) {
                 // contraction over j on the lane's Gauss column
                 double Tr[NQ], Ts[NQ], Tt[NQ];
@@ -194,6 +165,7 @@ __global__ void __launch_bounds__((AdvShape<NQ, M>::THREADS)) __attribute__((amd
                 }
                 // over k: derivatives at the Gauss points, integrand, and the
                 // transposed interpolation back along k, point by point
+                double G[NQ];
 #pragma unroll
                 for (int k = 0; k < NQ; ++k) G[k] = 0.0;
 #pragma unroll
@@ -209,16 +181,13 @@ __global__ void __launch_bounds__((AdvShape<NQ, M>::THREADS)) __attribute__((amd
 #pragma unroll
                     for (int k = 0; k < NQ; ++k) G[k] += J[c * NQ + k] * fv;
                 }
-            }
-            __syncthreads();  // every lane is done reading sP / sQ
-            if (col) {
 #pragma unroll
-                for (int k = 0; k < NQ; ++k) sG[(k * M + b) * M + a] = G[k];
+                for (int k = 0; k < NQ; ++k) sG[k * MM + t] = G[k];
             }
             __syncthreads();
             // contraction over b -> j on lanes (a, k)
-            if (t < NQ * M) {
-                const int a2 = t % M, k = t / M;
+            for (int r = t; r < NQ * M; r += TH) {
+                const int a2 = r % M, k = r / M;
                 double H[NQ];
 #pragma unroll
                 for (int j = 0; j < NQ; ++j) H[j] = 0.0;
@@ -231,26 +200,18 @@ __global__ void __launch_bounds__((AdvShape<NQ, M>::THREADS)) __attribute__((amd
 #pragma unroll
                 for (int j = 0; j < NQ; ++j) sH[(k * NQ + j) * M + a2] = H[j];
             }
-            __syncthreads();
-            // contraction over a -> i on GLL rows (k, j)
-            if (t < NQ * NQ) {
-                const int j = t % NQ, k = t / NQ;
-                double h[M];
-#pragma unroll
-                for (int a2 = 0; a2 < M; ++a2) h[a2] = sH[(k * NQ + j) * M + a2];
-                double o[NQ];
-#pragma unroll
-                for (int i = 0; i < NQ; ++i) o[i] = 0.0;
-#pragma unroll
-                for (int a2 = 0; a2 < M; ++a2)
-#pragma unroll
-                    for (int i = 0; i < NQ; ++i) o[i] += J[a2 * NQ + i] * h[a2];
-                double *op = out + f * ldo + e * NP + (k * NQ + j) * NQ;
-#pragma unroll
-                for (int i = 0; i < NQ; ++i) op[i] = o[i];
+            double *o5 = out + f * ldo + e * NP;
+            if constexpr (PIPE) {
+                prev = o5;
+            } else {
+                __syncthreads();
+                finish(o5);
             }
-            __syncthreads();  // sH is read before the next field is staged into sB
         }
+    }
+    if constexpr (PIPE) {
+        __syncthreads();
+        if (prev) finish(prev);
     }
 }
 
@@ -372,163 +333,157 @@ __global__ void __launch_bounds__((Adv3Shape<NQ, M>::THREADS))
     }
 }
 
-// Reference gradients out[e * ostride + q * M^3 + p], q = r, s, t, of the
-// interpolant of the L-vector u at the Gauss points p = a + M b + M^2 c.
-template <int NQ, int M>
-__global__ void __launch_bounds__(256)
-    fine_grad_kernel(int64_t E, const double *__restrict__ J, const double *__restrict__ Jd,
-                     const double *__restrict__ u, double *__restrict__ out, int64_t ostride)
-{
-    using S = AdvShape<NQ, M>;
-    __shared__ double sA[S::SA];
-    __shared__ double sB[S::SB];
-    double *sP = sA, *sQ = sA + NQ * NQ * M;
-    double *sU = sB;
-    const int t = threadIdx.x;
-    const bool col = t < S::MM;
-    const int a = col ? t % M : 0, b = col ? t / M : 0;
-    double Jb[NQ], Jdb[NQ];
-#pragma unroll
-    for (int j = 0; j < NQ; ++j) {
-        Jb[j] = J[b * NQ + j];
-        Jdb[j] = Jd[b * NQ + j];
-    }
-    for (int64_t e = blockIdx.x; e < E; e += gridDim.x) {
-        const double *ue = u + e * S::NP;
-        for (int i = t; i < S::NP; i += blockDim.x) sU[i] = ue[i];
-        __syncthreads();
-        stage_rows<NQ, M>(J, Jd, sU, sP, sQ);
-        __syncthreads();
-        if (col) {
-            double *oe = out + e * ostride + t;
-            double Tr[NQ], Ts[NQ], Tt[NQ];
-            stage_cols<NQ, M>(Jb, Jdb, a, sP, sQ, Tr, Ts, Tt);
-#pragma unroll
-            for (int c = 0; c < M; ++c) {
-                double dr = 0.0, ds = 0.0, dt = 0.0;
-#pragma unroll
-                for (int k = 0; k < NQ; ++k) {
-                    dr += J[c * NQ + k] * Tr[k];
-                    ds += J[c * NQ + k] * Ts[k];
-                    dt += Jd[c * NQ + k] * Tt[k];
-                }
-                oe[c * S::MM] = dr;
-                oe[S::M3 + c * S::MM] = ds;
-                oe[2 * S::M3 + c * S::MM] = dt;
-            }
-        }
-        __syncthreads();  // sU / sP are rewritten for the next element
-    }
-}
-
-// F [E][9][M^3]: raw derivatives X[d][q] = dx_d/dr_q at index 3 d + q on
-// entry; rho~ |det X| dr_q/dx_d = rho~ sign(det X) adj(X)[q][d] at index
-// 3 q + d on exit.  bad |= 1 where det X <= 0.
-__global__ void metric_kernel(int64_t E, int M, const double *__restrict__ wq, double *__restrict__ F,
-                              int *bad)
-{
-    const int64_t M3 = (int64_t)M * M * M;
-    const int64_t n = E * M3;
-    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < n;
-         g += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t e = g / M3, p = g % M3;
-        double *Fe = F + e * 9 * M3 + p;
-        double X[9];
-#pragma unroll
-        for (int m = 0; m < 9; ++m) X[m] = Fe[m * M3];
-        // X[3 d + q]: rows d = x, y, z; columns q = r, s, t
-        double A[9];  // adjugate, A[3 q + d]
-        A[0] = X[4] * X[8] - X[5] * X[7];
-        A[1] = X[2] * X[7] - X[1] * X[8];
-        A[2] = X[1] * X[5] - X[2] * X[4];
-        A[3] = X[5] * X[6] - X[3] * X[8];
-        A[4] = X[0] * X[8] - X[2] * X[6];
-        A[5] = X[2] * X[3] - X[0] * X[5];
-        A[6] = X[3] * X[7] - X[4] * X[6];
-        A[7] = X[1] * X[6] - X[0] * X[7];
-        A[8] = X[0] * X[4] - X[1] * X[3];
-        const double det = X[0] * A[0] + X[1] * A[3] + X[2] * A[6];
-        if (!(det > 0.0)) atomicOr(bad, 1);
-        const int ia = (int)(p % M), ib = (int)((p / M) % M), ic = (int)(p / ((int64_t)M * M));
-        const double rho = wq[ia] * wq[ib] * wq[ic] * (det < 0.0 ? -1.0 : 1.0);
-#pragma unroll
-        for (int m = 0; m < 9; ++m) Fe[m * M3] = rho * A[m];
-    }
-}
-
-// ct[e][q][p] = sum_d F[e][3 q + d][p] (J3 c_d)[p]: the three velocity
-// components interpolated to the Gauss points and turned contravariant in one
-// pass.  Lane t = a + M b owns the Gauss column (b, a) as in the advection
-// kernel; the components go through LDS one after another (contraction over
-// i on GLL rows, then over j and k on the column in registers), the lane
-// keeps its 3 M interpolated values in registers, and the column's nine
-// factors are read and the three products written point by point, so the
-// interpolated velocity never reaches memory.
-template <int NQ, int M>
-__global__ void __launch_bounds__((AdvShape<NQ, M>::THREADS))
-    velocity_kernel(int64_t E, const double *__restrict__ J, const double *__restrict__ F,
-                    const double *__restrict__ c, int64_t ldc, double *__restrict__ ct)
+// ct[e][q][p] = rho~ (cofactor of dx/dr . J3 c): the contravariant velocity at
+// the Gauss points from the element's coordinates and velocity alone.  The
+// metric factors rho~ |det X| dr_q/dx_d are 72 M^3 bytes an element when kept
+// (96 KB at M = 11, of 140 KB that the transform then moved: 0.955 ms = 4.8 TB/s
+// on 32^3 elements); formed here from the 12 KB of coordinates they cost
+// arithmetic that hides behind the 44 KB left.
+// Lane t = a + M b owns the Gauss column (b, a) as in the advection kernel.  The
+// three velocity components, then the three coordinates go through LDS one after
+// another (contraction over i on GLL rows, over j on the column); a column keeps
+// its nine derivative lines along k in registers, its three velocity lines in
+// LDS, and walks the M points: derivatives, the three cofactor rows as cross
+// products, and their products with the velocity.
+// CHECK: no velocity, bad |= 1 where det dx/dr <= 0.
+template <int NQ, int M, bool CHECK>
+__global__ void __launch_bounds__((AdvShape<NQ, M>::THREADS), 2)
+    velocity_kernel(int64_t E, const double *__restrict__ J, const double *__restrict__ Jd,
+                    const double *__restrict__ wq, const double *__restrict__ x,
+                    const double *__restrict__ y, const double *__restrict__ z,
+                    const double *__restrict__ cv, int64_t ldc, double *__restrict__ ct, int *bad)
 {
     using S = AdvShape<NQ, M>;
     constexpr int NP = S::NP, MM = S::MM, M3 = S::M3, TH = S::THREADS;
+    constexpr int F0 = CHECK ? 3 : 0, PFN = (NP + TH - 1) / TH;
     __shared__ double sU[NP];
-    __shared__ double sP[NQ * NQ * M];
+    __shared__ double sP[NQ * NQ * M], sQ[NQ * NQ * M];
+    __shared__ double sV[CHECK ? 1 : 3 * NQ][MM];
+    __shared__ double sJ[M][NQ + 1], sJd[M][NQ + 1];
     const int t = threadIdx.x;
     const bool col = t < MM;
     const int a = col ? t % M : 0, b = col ? t / M : 0;
-    double Jb[NQ];
+    for (int i = t; i < M * NQ; i += TH) {
+        sJ[i / NQ][i % NQ] = J[i];
+        sJd[i / NQ][i % NQ] = Jd[i];
+    }
+    const double wab = wq[a] * wq[b];
+    double un[PFN];
+    auto fetch = [&](int f, int64_t e) {
+        const double *p = (f < 3 ? cv + f * ldc : f == 3 ? x : f == 4 ? y : z) + e * NP;
 #pragma unroll
-    for (int j = 0; j < NQ; ++j) Jb[j] = J[b * NQ + j];
+        for (int q = 0; q < PFN; ++q) {
+            const int i = t + q * TH;
+            un[q] = i < NP ? p[i] : 0.0;
+        }
+    };
+    if (blockIdx.x < E) fetch(F0, blockIdx.x);
     for (int64_t e = blockIdx.x; e < E; e += gridDim.x) {
-        double v[3][M];
+        double T[3][3][NQ];  // T[d][q]: line of dx_d/dr_q before the k contraction
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const double *ue = c + d * ldc + e * NP;
-            for (int i = t; i < NP; i += TH) sU[i] = ue[i];
-            __syncthreads();
-            // over i on GLL rows (k, j): sP[k][j][a] = (J u)[k][j][a]
-            for (int r = t; r < NQ * NQ; r += TH) {
-                double ri[NQ];
+        for (int f = F0; f < 6; ++f) {
 #pragma unroll
-                for (int i = 0; i < NQ; ++i) ri[i] = sU[r * NQ + i];
+            for (int q = 0; q < PFN; ++q) {
+                const int i = t + q * TH;
+                if (i < NP) sU[i] = un[q];
+            }
+            if (f < 5)
+                fetch(f + 1, e);
+            else if (e + gridDim.x < E)
+                fetch(F0, e + gridDim.x);
+            __syncthreads();  // also: the columns of the field before are done with sP, sQ
+            // over i on GLL rows (k, j): J u, and for a coordinate Jd u
+            if (t < NQ * NQ) {
+                double r[NQ];
+#pragma unroll
+                for (int i = 0; i < NQ; ++i) r[i] = sU[t * NQ + i];
 #pragma unroll
                 for (int a2 = 0; a2 < M; ++a2) {
-                    double p = 0.0;
+                    double p = 0.0, q = 0.0;
 #pragma unroll
-                    for (int i = 0; i < NQ; ++i) p += J[a2 * NQ + i] * ri[i];
-                    sP[r * M + a2] = p;
+                    for (int i = 0; i < NQ; ++i) {
+                        p += J[a2 * NQ + i] * r[i];
+                        if (f >= 3) q += Jd[a2 * NQ + i] * r[i];
+                    }
+                    sP[t * M + a2] = p;
+                    if (f >= 3) sQ[t * M + a2] = q;
                 }
             }
             __syncthreads();
             if (col) {
-                double Tt[NQ];
+                if (f >= 3) {
+                    double(&Tf)[3][NQ] = T[f < 3 ? 0 : f - 3];
 #pragma unroll
-                for (int k = 0; k < NQ; ++k) {
-                    double x = 0.0;
+                    for (int k = 0; k < NQ; ++k) Tf[0][k] = Tf[1][k] = Tf[2][k] = 0.0;
 #pragma unroll
-                    for (int j = 0; j < NQ; ++j) x += Jb[j] * sP[(k * NQ + j) * M + a];
-                    Tt[k] = x;
-                }
+                    for (int j = 0; j < NQ; ++j) {
+                        const double jb = sJ[b][j], jd = sJd[b][j];
 #pragma unroll
-                for (int cc = 0; cc < M; ++cc) {
-                    double x = 0.0;
+                        for (int k = 0; k < NQ; ++k) {
+                            const double p = sP[(k * NQ + j) * M + a], q = sQ[(k * NQ + j) * M + a];
+                            Tf[0][k] += jb * q;
+                            Tf[1][k] += jd * p;
+                            Tf[2][k] += jb * p;
+                        }
+                    }
+                } else {
+                    double Vf[NQ];
 #pragma unroll
-                    for (int k = 0; k < NQ; ++k) x += J[cc * NQ + k] * Tt[k];
-                    v[d][cc] = x;
+                    for (int k = 0; k < NQ; ++k) Vf[k] = 0.0;
+#pragma unroll
+                    for (int j = 0; j < NQ; ++j) {
+                        const double jb = sJ[b][j];
+#pragma unroll
+                        for (int k = 0; k < NQ; ++k) Vf[k] += jb * sP[(k * NQ + j) * M + a];
+                    }
+#pragma unroll
+                    for (int k = 0; k < NQ; ++k) sV[CHECK ? 0 : f * NQ + k][t] = Vf[k];
                 }
             }
-            __syncthreads();  // sU and sP are rewritten for the next component
         }
         if (col) {
-            const double *Fe = F + e * 9 * M3 + t;
-            double *ce = ct + e * 3 * M3 + t;
+            double *ce = CHECK ? nullptr : ct + e * 3 * M3 + t;
+#pragma unroll 1
+            for (int c = 0; c < M; ++c) {
+                const double *Jc = J + c * NQ, *Jdc = Jd + c * NQ;
+                double X[3][3];  // X[d][q] = dx_d/dr_q
 #pragma unroll
-            for (int cc = 0; cc < M; ++cc) {
-                const int p = cc * MM;
+                for (int d = 0; d < 3; ++d) {
+                    X[d][0] = X[d][1] = X[d][2] = 0.0;
 #pragma unroll
-                for (int q = 0; q < 3; ++q)
-                    ce[q * M3 + p] = Fe[(3 * q) * M3 + p] * v[0][cc] + Fe[(3 * q + 1) * M3 + p] * v[1][cc] +
-                                     Fe[(3 * q + 2) * M3 + p] * v[2][cc];
+                    for (int k = 0; k < NQ; ++k) {
+                        X[d][0] += Jc[k] * T[d][0][k];
+                        X[d][1] += Jc[k] * T[d][1][k];
+                        X[d][2] += Jdc[k] * T[d][2][k];
+                    }
+                }
+                // cofactor rows: A[q] = dx/dr_{q+1} x dx/dr_{q+2}
+                double A[3][3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const int q1 = (q + 1) % 3, q2 = (q + 2) % 3;
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) {
+                        const int d1 = (d + 1) % 3, d2 = (d + 2) % 3;
+                        A[q][d] = X[d1][q1] * X[d2][q2] - X[d2][q1] * X[d1][q2];
+                    }
+                }
+                if constexpr (CHECK) {
+                    const double det = X[0][0] * A[0][0] + X[1][0] * A[0][1] + X[2][0] * A[0][2];
+                    if (!(det > 0.0)) atomicOr(bad, 1);
+                } else {
+                    double v[3];
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) {
+                        v[d] = 0.0;
+#pragma unroll
+                        for (int k = 0; k < NQ; ++k) v[d] += Jc[k] * sV[d * NQ + k][t];
+                    }
+                    const double rho = wab * wq[c];
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+                        ce[q * M3 + c * MM] = rho * (A[q][0] * v[0] + A[q][1] * v[1] + A[q][2] * v[2]);
+                }
             }
         }
     }
@@ -544,42 +499,27 @@ constexpr int kAdv3AutoMaxM = 0;
 
 bool rule_supported(int N, int M) { return N >= 1 && N <= 7 && (M == rule_default(N) || M == rule_default(N) + 1); }
 
-int64_t adv_grid(const Level &L)
-{
-    const int64_t cap = (int64_t)(L.n_cu > 0 ? L.n_cu : 256) * 8;
-    return std::max<int64_t>(1, std::min<int64_t>(L.E, cap));
-}
-
 // dispatch over the compiled (nq, M) pairs: M = ceil((3N+1)/2) and one more
 #define SEM_ADV_PAIRS(X) \
     X(2, 2) X(2, 3) X(3, 4) X(3, 5) X(4, 5) X(4, 6) X(5, 7) X(5, 8) X(6, 8) X(6, 9) X(7, 10) X(7, 11) X(8, 11) X(8, 12)
 
-int launch_fine_grad(const Level &L, int M, const double *J, const double *Jd, const double *u, double *out,
-                     int64_t ostride, hipStream_t s)
+// ct from the velocity c, or with bad the check of the element map
+int launch_velocity(sem_handle h, int M, const double *J, const double *Jd, const double *wq, const double *c,
+                    int64_t ldc, double *ct, int *bad, hipStream_t s)
 {
-    const dim3 grid((unsigned)adv_grid(L));
-#define SEM_FG(NQ_, M_)                                                                              \
-    if (L.nq == NQ_ && M == M_) {                                                                    \
-        hipLaunchKernelGGL((fine_grad_kernel<NQ_, M_>), grid, dim3(AdvShape<NQ_, M_>::THREADS), 0, s, L.E, J, \
-                           Jd, u, out, ostride);                                                     \
-        SEM_HIP(hipGetLastError());                                                                  \
-        return SEM_OK;                                                                               \
-    }
-    SEM_ADV_PAIRS(SEM_FG)
-#undef SEM_FG
-    set_error("advection: no kernel for N = %d, M = %d", L.N, M);
-    return SEM_EINVAL;
-}
-
-int launch_velocity(const Level &L, int M, const double *J, const double *F, const double *c, int64_t ldc,
-                    double *ct, hipStream_t s)
-{
-    const int64_t cap = (int64_t)(L.n_cu > 0 ? L.n_cu : 256) * 16;
+    const Level &L = h->lv[0];
+    // as many workgroups as are resident (24^3 elements, 4 / 8 / 16 per CU: M = 11
+    // 292 / 313 / 313 us, two waves a SIMD; M = 8 149 / 111 / 115, M = 7 99 / 76 / 77)
+    const int64_t cap = (int64_t)(L.n_cu > 0 ? L.n_cu : 256) * (M >= 10 ? 4 : 8);
     const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(L.E, cap)));
 #define SEM_VEL(NQ_, M_)                                                                            \
     if (L.nq == NQ_ && M == M_) {                                                                   \
-        hipLaunchKernelGGL((velocity_kernel<NQ_, M_>), grid, dim3(AdvShape<NQ_, M_>::THREADS), 0, s, \
-                           L.E, J, F, c, ldc, ct);                                                  \
+        if (bad)                                                                                    \
+            hipLaunchKernelGGL((velocity_kernel<NQ_, M_, true>), grid, dim3(AdvShape<NQ_, M_>::THREADS), 0, \
+                               s, L.E, J, Jd, wq, h->cx, h->cy, h->cz, c, ldc, ct, bad);            \
+        else                                                                                        \
+            hipLaunchKernelGGL((velocity_kernel<NQ_, M_, false>), grid, dim3(AdvShape<NQ_, M_>::THREADS), 0, \
+                               s, L.E, J, Jd, wq, h->cx, h->cy, h->cz, c, ldc, ct, bad);            \
         SEM_HIP(hipGetLastError());                                                                 \
         return SEM_OK;                                                                              \
     }
@@ -618,9 +558,10 @@ int launch_advect(const Level &L, int M, int variant, const double *J, const dou
         set_error("advection: no 3D kernel for N = %d, M = %d", L.N, M);
         return SEM_EINVAL;
     }
-    // 16 workgroups per CU (measured at N = 7, M = 11: 4 per CU 712 us, 16 per
-    // CU 623 us for three fields on 32^3 elements)
-    const int64_t cap = (int64_t)(L.n_cu > 0 ? L.n_cu : 256) * 16;
+    // workgroups per CU, 16 / 32 / 64 (us): M = 11 254 / 248 / 250 and M = 7
+    // 63 / 55 / 56 for three fields on 24^3 elements; small rules behind the
+    // velocity transform, M = 5 on 30^3 106 / 122 / 122, M = 4 on 40^3 240 / 263 / 255
+    const int64_t cap = (int64_t)(L.n_cu > 0 ? L.n_cu : 256) * (M >= 7 ? 32 : 16);
     const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(L.E, cap)));
 #define SEM_ADV(NQ_, M_)                                                                             \
     if (L.nq == NQ_ && M == M_) {                                                                    \
@@ -660,25 +601,15 @@ int advect_setup(sem_handle h, int M, hipStream_t s)
     SEM_TRY(alloc_upload(&A.J, J));
     SEM_TRY(alloc_upload(&A.Jd, Jd));
     SEM_TRY(alloc_upload(&A.wq, wq));
-    const int64_t M3 = (int64_t)M * M * M;
-    SEM_HIP(hipMalloc(&A.F, sizeof(double) * 9 * M3 * L.E));
-    const double *X[3] = {h->cx, h->cy, h->cz};
-    for (int d = 0; d < 3; ++d)
-        SEM_TRY(launch_fine_grad(L, M, A.J, A.Jd, X[d], A.F + 3 * d * M3, 9 * M3, s));
     int *bad = nullptr;
     SEM_HIP(hipMalloc(&bad, sizeof(int)));
     int hbad = 0;
     int rc = SEM_OK;
     if (hipMemsetAsync(bad, 0, sizeof(int), s) != hipSuccess) rc = SEM_EHIP;
-    if (rc == SEM_OK) {
-        const int64_t n = L.E * M3;
-        const unsigned blocks = (unsigned)std::min<int64_t>((n + 255) / 256, 65536);
-        hipLaunchKernelGGL(metric_kernel, dim3(blocks), dim3(256), 0, s, L.E, M, A.wq, A.F, bad);
-        if (hipGetLastError() != hipSuccess ||
-            hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            rc = SEM_EHIP;
-    }
+    if (rc == SEM_OK) rc = launch_velocity(h, M, A.J, A.Jd, A.wq, nullptr, 0, nullptr, bad, s);
+    if (rc == SEM_OK && (hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||
+                         hipStreamSynchronize(s) != hipSuccess))
+        rc = SEM_EHIP;
     (void)hipFree(bad);
     if (rc != SEM_OK) {
         set_error("advection setup: %s", hipGetErrorString(hipGetLastError()));
@@ -697,7 +628,7 @@ int advect_setup(sem_handle h, int M, hipStream_t s)
 void free_advect(sem_handle h)
 {
     auto &A = h->adv;
-    void *ptrs[] = {A.J, A.Jd, A.wq, A.F};
+    void *ptrs[] = {A.J, A.Jd, A.wq};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     A = sem_handle_s::Advect{};
@@ -764,7 +695,7 @@ int sem_advect_velocity(sem_handle h, const double *c, int64_t ldc, double *ct, 
         return SEM_EINVAL;
     }
     const hipStream_t s = (hipStream_t)stream;
-    return launch_velocity(L, A.M, A.J, A.F, c, ldc, ct, s);
+    return launch_velocity(h, A.M, A.J, A.Jd, A.wq, c, ldc, ct, nullptr, s);
 }
 
 int sem_advect(sem_handle h, const double *ct, int nf, const double *w, int64_t ldw, double *out, int64_t ldo,

@@ -265,12 +265,11 @@ struct sem_handle_s {
     // level-0 coordinates [nL] each (kept for the advection metrics)
     double *cx = nullptr, *cy = nullptr, *cz = nullptr;
     // dealiased advection on the M-point Gauss rule: interpolation J and
-    // derivative Jd = J Dh [M][nq], weights wq [M], metric factors
-    // F [E][9][M^3] = rho~ |det X| dr_q/dx_d at index 3 q + d
+    // derivative Jd = J Dh [M][nq], weights wq [M]
     struct Advect {
         int M = 0;
         int variant = 0;  // SEM_ADVECT_2D or SEM_ADVECT_3D
-        double *J = nullptr, *Jd = nullptr, *wq = nullptr, *F = nullptr;
+        double *J = nullptr, *Jd = nullptr, *wq = nullptr;
     } adv;
     semx::Workspace ws;
     semx::PrecondKey key;

@@ -508,7 +508,7 @@ class Sem:
 
     # -- dealiased advection ----------------------------------------------
     def advect_setup(self, M=None, variant="auto"):
-        """Metric factors for the M-point Gauss rule (None: the smallest rule
+        """Set up the M-point Gauss rule (None: the smallest rule
         exact for degree 3N) and the element kernel ("auto", "2d", "3d");
         returns M."""
         m = ctypes.c_int(0)
