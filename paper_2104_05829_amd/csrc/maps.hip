@@ -69,13 +69,14 @@ __global__ void run_fill_kernel(int64_t nruns, const int64_t *__restrict__ key,
 
 __global__ void weights_kernel(int64_t nL, const int32_t *__restrict__ mult,
                                const uint8_t *__restrict__ dir, double *__restrict__ W,
-                               float *__restrict__ W32)
+                               float *__restrict__ W32, uint8_t *__restrict__ mc)
 {
     const int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (l >= nL) return;
     const double w = (dir && dir[l]) ? 0.0 : 1.0 / (double)mult[l];
     W[l] = w;
     if (W32) W32[l] = (float)w;
+    mc[l] = (dir && dir[l]) ? 0 : (uint8_t)min(mult[l], 255);
 }
 
 namespace {
@@ -193,8 +194,9 @@ int build_maps(Level &L, const int64_t *gid, const uint8_t *dir, const double *x
     SEM_HIP(hipMemcpyAsync(L.offs + L.nseg, &last, sizeof(int32_t), hipMemcpyHostToDevice, s));
     SEM_HIP(hipMalloc(&L.W, sizeof(double) * nL));
     SEM_HIP(hipMalloc(&L.W32, sizeof(float) * nL));
+    SEM_HIP(hipMalloc(&L.mc, nL));
     hipLaunchKernelGGL(weights_kernel, dim3(nbL), dim3(bs), 0, s, nL, (const int32_t *)mult.p, dir,
-                       L.W, L.W32);
+                       L.W, L.W32, L.mc);
     SEM_HIP(hipGetLastError());
     SEM_HIP(hipStreamSynchronize(s));
     return build_gs_chunks(L, s);
@@ -223,8 +225,10 @@ int build_gs_chunks(Level &L, hipStream_t s)
     std::vector<int32_t> cp;  // padded chunk lists
     std::vector<int32_t> over;
     int32_t used = 64;  // lanes filled in the open chunk (64: none open)
+    int32_t longest = 0;
     for (int64_t q = 0; q < L.nseg; ++q) {
         const int32_t a = offs[q], len = offs[q + 1] - offs[q];
+        longest = std::max(longest, len);
         if (len > 64) {
             over.push_back((int32_t)q);
             continue;
@@ -236,6 +240,10 @@ int build_gs_chunks(Level &L, hipStream_t s)
         int32_t *lanes = cp.data() + cp.size() - 64;
         for (int32_t o = 0; o < len; ++o) lanes[used + o] = perm[a + o] | (o == 0 ? kGsSegStart : 0);
         used += len;
+    }
+    if (longest > 255 && L.mc) {  // the multiplicity does not fit a byte
+        SEM_HIP(hipFree(L.mc));
+        L.mc = nullptr;
     }
     const int64_t nch = (int64_t)cp.size() / 64;
     L.nchunks = nch;

@@ -132,6 +132,9 @@ struct Level {
     float *G32 = nullptr, *B32 = nullptr;
     double *W = nullptr;   // counting weight, 0 on Dirichlet copies
     float *W32 = nullptr;
+    // the weight in a byte: multiplicity of the copy's node, 0 on Dirichlet
+    // copies (W = 1 / mc); null if a node has more than 255 copies
+    uint8_t *mc = nullptr;
     int64_t *gid = nullptr;
     uint8_t *dir = nullptr;
     int32_t *perm = nullptr, *offs = nullptr;

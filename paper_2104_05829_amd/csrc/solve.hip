@@ -153,6 +153,44 @@ __device__ inline void st2(float *p, int64_t g, const float (&o)[2])
     reinterpret_cast<float2 *>(p)[g] = make_float2(o[0], o[1]);
 }
 
+// The counting weight of a copy in the streaming kernels: from W, or (MC) from
+// the byte mc through a table of the reciprocals, the same value in one byte
+// instead of eight of the 64 (Jacobi-PCG update), 60 and 28 (flexible CG update
+// and inner products) that a point moves.
+template <bool MC>
+struct Weight {
+    const double *W;
+    const uint8_t *mc;
+    const double *tab;
+    __device__ inline Weight(const double *W_, const uint8_t *mc_) : W(W_), mc(mc_), tab(nullptr)
+    {
+        if constexpr (MC) {
+            __shared__ double t[kRB];
+            static_assert(kRB == 256, "one reciprocal per thread");
+            t[threadIdx.x] = threadIdx.x ? 1.0 / (double)threadIdx.x : 0.0;
+            __syncthreads();
+            tab = t;
+        }
+    }
+    __device__ inline double at(int64_t i) const
+    {
+        if constexpr (MC)
+            return tab[mc[i]];
+        else
+            return W[i];
+    }
+    __device__ inline void pair(int64_t g, double (&o)[2]) const
+    {
+        if constexpr (MC) {
+            const uchar2 m = reinterpret_cast<const uchar2 *>(mc)[g];
+            o[0] = tab[m.x];
+            o[1] = tab[m.y];
+        } else {
+            ld2(W, g, o);
+        }
+    }
+};
+
 // ------------------------------------------------------------------ vectors
 // Kernels over a batch of vectors take the batch `vs` and the leading
 // dimension of each array; grid.y runs over the vectors of the batch, and
@@ -278,14 +316,15 @@ __global__ void fin_init_kernel(VSet vs, const double *partial, int64_t pst, int
 // (p, A_L p) in the same fixed order, so all blocks hold the same alpha;
 // x += alpha p; r -= alpha QQ^T(A_L p) (w already assembled); partials
 // (W r Dinv r, W r r).  rz2[parity] is the current (r, z).
+template <bool MC>
 __global__ void pcg_update_fused_kernel(int64_t n, VSet vs, int64_t ld, int64_t ldx,
                                         KrylovScalars *sc, int parity,
                                         const double *__restrict__ pax, int64_t pst_ax, int64_t nbax,
                                         const double *__restrict__ p, const double *__restrict__ w,
                                         const double *__restrict__ Dinv,
-                                        const double *__restrict__ W, double *__restrict__ x,
-                                        double *__restrict__ r, double *__restrict__ partial,
-                                        int64_t pst)
+                                        const double *__restrict__ W, const uint8_t *__restrict__ mc,
+                                        double *__restrict__ x, double *__restrict__ r,
+                                        double *__restrict__ partial, int64_t pst)
 {
     const int64_t v = vsel(vs);
     sc += v;
@@ -294,6 +333,7 @@ __global__ void pcg_update_fused_kernel(int64_t n, VSet vs, int64_t ld, int64_t 
     w += v * ld;
     r += v * ld;
     x += v * ldx;
+    const Weight<MC> wt(W, mc);
     double res[1];
     sum_partials<1>(pax + v * pst_ax, nbax, res);
     const double pw = res[0];
@@ -315,7 +355,7 @@ __global__ void pcg_update_fused_kernel(int64_t n, VSet vs, int64_t ld, int64_t 
         x[i] += a * p[i];
         const double ri = r[i] - a * w[i];
         r[i] = ri;
-        const double wr = W[i] * ri;
+        const double wr = wt.at(i) * ri;
         s[0] += wr * Dinv[i] * ri;
         s[1] += wr * ri;
     }
@@ -444,14 +484,14 @@ __global__ void pcg_p_fused_kernel(int64_t n, VSet vs, int64_t ld, KrylovScalars
 // flexible-CG update: alpha from the operator partials, x += alpha p,
 // r -= alpha QQ^T(A_L p), r32 = FP32 copy of r (the V-cycle input);
 // partial (W r r)
-template <bool PAIR>
+template <bool PAIR, bool MC>
 __global__ void fcg_update_fused_kernel(int64_t n, VSet vs, int64_t ld, int64_t ldx,
                                         KrylovScalars *sc, int parity,
                                         const double *__restrict__ pax, int64_t pst_ax, int64_t nbax,
                                         const double *__restrict__ p, const double *__restrict__ w,
-                                        const double *__restrict__ W, double *__restrict__ x,
-                                        double *__restrict__ r, float *__restrict__ r32,
-                                        double *__restrict__ partial, int64_t pst)
+                                        const double *__restrict__ W, const uint8_t *__restrict__ mc,
+                                        double *__restrict__ x, double *__restrict__ r,
+                                        float *__restrict__ r32, double *__restrict__ partial, int64_t pst)
 {
     const int64_t v = vsel(vs);
     sc += v;
@@ -461,6 +501,7 @@ __global__ void fcg_update_fused_kernel(int64_t n, VSet vs, int64_t ld, int64_t 
     r += v * ld;
     r32 += v * ld;
     x += v * ldx;
+    const Weight<MC> wgt(W, mc);
     double res[1];
     sum_partials<1>(pax + v * pst_ax, nbax, res);
     const double pw = res[0];
@@ -486,7 +527,7 @@ __global__ void fcg_update_fused_kernel(int64_t n, VSet vs, int64_t ld, int64_t 
             ld2(w, g, ww);
             ld2(x, g, xx);
             ld2(r, g, rr);
-            ld2(W, g, wt);
+            wgt.pair(g, wt);
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 xx[k] += a * pp[k];
@@ -505,7 +546,7 @@ __global__ void fcg_update_fused_kernel(int64_t n, VSet vs, int64_t ld, int64_t 
             const double ri = r[i] - a * w[i];
             r[i] = ri;
             r32[i] = (float)ri;
-            s[0] += W[i] * ri * ri;
+            s[0] += wgt.at(i) * ri * ri;
         }
     }
     block_sum_store<1>(s, partial + v * pst);
@@ -513,8 +554,10 @@ __global__ void fcg_update_fused_kernel(int64_t n, VSet vs, int64_t ld, int64_t 
 
 // (z, w)_W and (z, r)_W for assembled w, z the FP32 V-cycle output taken to
 // FP64 (W = 0 on Dirichlet copies applies the restriction)
+template <bool MC>
 __global__ void dot_zw_kernel(int64_t n, VSet vs, int64_t ld, const KrylovScalars *sc,
-                              const double *__restrict__ W, const float *__restrict__ z,
+                              const double *__restrict__ W, const uint8_t *__restrict__ mc,
+                              const float *__restrict__ z,
                               const double *__restrict__ wa, const double *__restrict__ r,
                               double *__restrict__ partial, int64_t pst)
 {
@@ -523,9 +566,10 @@ __global__ void dot_zw_kernel(int64_t n, VSet vs, int64_t ld, const KrylovScalar
     z += v * ld;
     wa += v * ld;
     r += v * ld;
+    const Weight<MC> wt(W, mc);
     double s[2] = {0.0, 0.0};
     GRID_LOOP(i, n) {
-        const double wz = W[i] * (double)z[i];
+        const double wz = wt.at(i) * (double)z[i];
         s[0] += wz * wa[i];
         s[1] += wz * r[i];
     }
@@ -538,11 +582,11 @@ __global__ void dot_zw_kernel(int64_t n, VSet vs, int64_t ld, const KrylovScalar
 // reading p (on the first iteration p is uninitialised memory, and a 0 * p
 // term would turn any NaN bit pattern it holds into a NaN direction).  z is
 // the FP32 V-cycle output, zero on Dirichlet copies (mask W32 > 0).
-template <bool PAIR>
+template <bool PAIR, bool MC>
 __global__ void fcg_p_fused_kernel(int64_t n, VSet vs, int64_t ld, KrylovScalars *sc, int parity,
                                    const double *__restrict__ pz, int64_t pst, int64_t nbz,
                                    const float *__restrict__ z, const float *__restrict__ W32,
-                                   double *__restrict__ p, int first)
+                                   const uint8_t *__restrict__ mc, double *__restrict__ p, int first)
 {
     const int64_t v = vsel(vs);
     sc += v;
@@ -567,21 +611,31 @@ __global__ void fcg_p_fused_kernel(int64_t n, VSet vs, int64_t ld, KrylovScalars
     if (bad) return;
     if constexpr (PAIR) {
         GRID_LOOP(g, n >> 1) {
-            float zz[2], wt[2];
+            float zz[2];
+            bool on[2];
             double pp[2] = {0.0, 0.0};
             ld2(z, g, zz);
-            ld2(W32, g, wt);
+            if constexpr (MC) {
+                const uchar2 m = reinterpret_cast<const uchar2 *>(mc)[g];
+                on[0] = m.x != 0;
+                on[1] = m.y != 0;
+            } else {
+                float wt[2];
+                ld2(W32, g, wt);
+                on[0] = wt[0] > 0.0f;
+                on[1] = wt[1] > 0.0f;
+            }
             if (!first) ld2(p, g, pp);
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
-                const double zk = wt[k] > 0.0f ? (double)zz[k] : 0.0;
+                const double zk = on[k] ? (double)zz[k] : 0.0;
                 pp[k] = first ? zk : zk + be * pp[k];
             }
             st2(p, g, pp);
         }
     } else {
         GRID_LOOP(i, n) {
-            const double zi = W32[i] > 0.0f ? (double)z[i] : 0.0;
+            const double zi = (MC ? mc[i] != 0 : W32[i] > 0.0f) ? (double)z[i] : 0.0;
             p[i] = first ? zi : zi + be * p[i];
         }
     }
@@ -849,16 +903,6 @@ __global__ void axpby_kernel(int64_t n, const double *x, double a, double b, dou
         hipLaunchKernelGGL(kern, dim3(red_grid(len_), (unsigned)(vs_).n), dim3(kRB), 0, s_, \
                            __VA_ARGS__);                                                    \
         SEM_HIP(hipGetLastError());                                                         \
-    } while (0)
-// the vectorised form of a vector kernel (kern<true>) when ok_, else the
-// one-value form; the grid (and so the number of partial records) is the same
-// for both
-#define LAUNCH_B_VEC(ok_, kern, len_, vs_, s_, ...)                                          \
-    do {                                                                                    \
-        if (ok_)                                                                            \
-            LAUNCH_B(kern<true>, len_, vs_, s_, __VA_ARGS__);                               \
-        else                                                                                \
-            LAUNCH_B(kern<false>, len_, vs_, s_, __VA_ARGS__);                              \
     } while (0)
 #define LAUNCH_1B(kern, vs_, s_, ...)                                                       \
     do {                                                                                    \
@@ -1408,9 +1452,10 @@ static int pcg_iterations(sem_handle h, const Level &L, const VSet &vs, const do
                                apart ? (const uint8_t *)nullptr : L.cnt8, pb.Dinv, L.W, kv.x, kv.r, pb.partial, pb.pst);
             SEM_HIP(hipGetLastError());
         } else {
-            LAUNCH_B(pcg_update_fused_kernel, n, vs, s, n, vs, n, kv.ldx, kv.sc, parity,
-                     (const double *)pb.partial_ax, pb.pst_ax, nbax, (const double *)kv.p,
-                     (const double *)kv.w, pb.Dinv, L.W, kv.x, kv.r, pb.partial, pb.pst);
+            auto kern = L.mc ? pcg_update_fused_kernel<true> : pcg_update_fused_kernel<false>;
+            LAUNCH_B(kern, n, vs, s, n, vs, n, kv.ldx, kv.sc, parity, (const double *)pb.partial_ax,
+                     pb.pst_ax, nbax, (const double *)kv.p, (const double *)kv.w, pb.Dinv, L.W,
+                     (const uint8_t *)L.mc, kv.x, kv.r, pb.partial, pb.pst);
         }
         if (timed) SEM_TRY(clock_mark(ws, kPhaseVec, s));
     }
@@ -1660,9 +1705,10 @@ static int coarse_csr_solve(sem_handle h, const Level &L, const VSet &vs, const 
                            nf, (const int32_t *)L.cs_row, (const int32_t *)L.cs_col, (const double *)L.cs_val,
                            (const double *)kv.p, kv.w, w.partial_ax, w.pst_ax, (const KrylovScalars *)kv.sc);
         SEM_HIP(hipGetLastError());
-        LAUNCH_NB(pcg_update_fused_kernel, nf, vs, nf, kv.ldx, kv.sc, parity, (const double *)w.partial_ax,
+        LAUNCH_NB(pcg_update_fused_kernel<false>, nf, vs, nf, kv.ldx, kv.sc, parity, (const double *)w.partial_ax,
                   w.pst_ax, (int64_t)nbax, (const double *)kv.p, (const double *)kv.w,
-                  (const double *)L.cs_dinv, (const double *)L.cs_one, kv.x, kv.r, w.partial, w.pst);
+                  (const double *)L.cs_dinv, (const double *)L.cs_one, (const uint8_t *)nullptr, kv.x, kv.r, w.partial,
+                  w.pst);
         LAUNCH_NB(pcg_p_fused_kernel, nf, vs, nf, kv.sc, parity, it, (const double *)w.partial, w.pst,
                   (int64_t)nbv, (const double *)L.cs_dinv, (const double *)kv.r, kv.p);
     }
@@ -2241,17 +2287,24 @@ int pcg_solve(sem_handle h, int nv, const double *b, double *x, int64_t ld, cons
         VSet act = live_set(w, all);
         const int nbv = red_grid(n);
         const int *skip = &w.sc[0].done;
-        const bool vec = vec_ok(n, ld, {x}) && vec_ok(n, n, {w.r, w.p, w.w, r32, z32, F.W, F.W32});
+        const bool vec = vec_ok(n, ld, {x}) && vec_ok(n, n, {w.r, w.p, w.w, r32, z32, F.W, F.W32, F.mc});
+        const bool mc = F.mc != nullptr;
+        auto update = vec ? (mc ? fcg_update_fused_kernel<true, true> : fcg_update_fused_kernel<true, false>)
+                          : (mc ? fcg_update_fused_kernel<false, true> : fcg_update_fused_kernel<false, false>);
+        auto direct = vec ? (mc ? fcg_p_fused_kernel<true, true> : fcg_p_fused_kernel<true, false>)
+                          : (mc ? fcg_p_fused_kernel<false, true> : fcg_p_fused_kernel<false, false>);
+        auto dots = mc ? dot_zw_kernel<true> : dot_zw_kernel<false>;
+        const uint8_t *fmc = F.mc;
         VSet cycled{0, 0u};  // vectors whose coarse counts are still to be read
         if (act.n > 0) {
             SEM_TRY(vcycle_run(h, act, cfg, o->use_graphs != 0, s));
             SEM_TRY(clock_mark(w, kPhasePrec, s));
-            LAUNCH_B(dot_zw_kernel, n, act, s, n, act, n, (const KrylovScalars *)w.sc, F.W,
+            LAUNCH_B(dots, n, act, s, n, act, n, (const KrylovScalars *)w.sc, F.W, fmc,
                      (const float *)z32, (const double *)w.r, (const double *)w.r, w.partial,
                      w.pst);
-            LAUNCH_B_VEC(vec, fcg_p_fused_kernel, n, act, s, n, act, n, w.sc, 1,
+            LAUNCH_B(direct, n, act, s, n, act, n, w.sc, 1,
                         (const double *)w.partial, w.pst, (int64_t)nbv, (const float *)z32, F.W32,
-                        w.p, 1);
+                        fmc, w.p, 1);
             SEM_TRY(clock_mark(w, kPhaseVec, s));
             cycled = act;
         }
@@ -2264,9 +2317,9 @@ int pcg_solve(sem_handle h, int nv, const double *b, double *x, int64_t ld, cons
             SEM_TRY(clock_mark(w, kPhaseAx, s));
             SEM_TRY(launch_gs_multi<double>(F, w.w, n, act, s, skip, kScStride));
             SEM_TRY(clock_mark(w, kPhaseGs, s));
-            LAUNCH_B_VEC(vec, fcg_update_fused_kernel, n, act, s, n, act, n, ld, w.sc, parity,
+            LAUNCH_B(update, n, act, s, n, act, n, ld, w.sc, parity,
                         (const double *)w.partial_ax, w.pst_ax, nbax, (const double *)w.p,
-                        (const double *)w.w, F.W, x, w.r, r32, w.partial, w.pst);
+                        (const double *)w.w, F.W, fmc, x, w.r, r32, w.partial, w.pst);
             LAUNCH_1B(fin_conv_kernel, act, s, act, (const double *)w.partial, w.pst, (int64_t)nbv,
                       w.sc);
             SEM_TRY(clock_mark(w, kPhaseVec, s));
@@ -2280,12 +2333,12 @@ int pcg_solve(sem_handle h, int nv, const double *b, double *x, int64_t ld, cons
             if (act.n == 0) break;
             SEM_TRY(vcycle_run(h, act, cfg, o->use_graphs != 0, s));
             SEM_TRY(clock_mark(w, kPhasePrec, s));
-            LAUNCH_B(dot_zw_kernel, n, act, s, n, act, n, (const KrylovScalars *)w.sc, F.W,
+            LAUNCH_B(dots, n, act, s, n, act, n, (const KrylovScalars *)w.sc, F.W, fmc,
                      (const float *)z32, (const double *)w.w, (const double *)w.r, w.partial,
                      w.pst);
-            LAUNCH_B_VEC(vec, fcg_p_fused_kernel, n, act, s, n, act, n, w.sc, parity,
+            LAUNCH_B(direct, n, act, s, n, act, n, w.sc, parity,
                         (const double *)w.partial, w.pst, (int64_t)nbv, (const float *)z32, F.W32,
-                        w.p, 0);
+                        fmc, w.p, 0);
             SEM_TRY(clock_mark(w, kPhaseVec, s));
             cycled = act;
         }

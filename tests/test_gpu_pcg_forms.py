@@ -66,3 +66,22 @@ def test_maxit_and_small_steps():
         xo, ito, _ = solvers.pcg_jacobi(lv, b, tol=1e-14, maxit=maxit)
         assert np.max(np.abs(ref[maxit].cpu().numpy() - xo)) <= 1e-10 * np.max(np.abs(xo))
     s.free()
+
+
+@pytest.mark.parametrize("precond", ["jacobi", "pmg"])
+def test_multiplicity_beyond_a_byte(precond):
+    """300 coincident elements: the counting weight no longer fits a byte and
+    is read in full (8 of its copies beyond 255 would lose 15% of each sum)."""
+    print(f"[gpu] pcg 300 copies {precond}", flush=True)
+    xi, _ = oracle.gll(3)
+    one = inputs.box_mesh(1, 1, 1, xi)
+    rep = lambda a: np.repeat(a, 300, axis=0)  # noqa: E731
+    m = inputs.BoxMesh(N=3, shape=(300, 1, 1), x=rep(one.x), y=rep(one.y), z=rep(one.z), gid=rep(one.gid),
+                       dirichlet=rep(one.dirichlet))
+    lv = solvers.Level(3, m.x, m.y, m.z, m.gid, m.dirichlet, 1.0, 10.0)
+    b = lv.rhs(inputs.gaussian_per_node(m.gid, 5))
+    xo, _, _ = solvers.pcg_jacobi(lv, b, tol=1e-13)
+    s = Sem(m, levels=(3, 1))
+    x, st, rc = s.solve(_dev(b), tol=1e-12, h2=10.0, precond=precond)
+    assert rc == 0 and np.max(np.abs(x.cpu().numpy() - xo)) <= 1e-9 * np.max(np.abs(xo)), st
+    s.free()
