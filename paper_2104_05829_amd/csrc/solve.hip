@@ -641,16 +641,19 @@ __global__ void fcg_p_fused_kernel(int64_t n, VSet vs, int64_t ld, KrylovScalars
     }
 }
 
-// Chebyshev step on assembled t = QQ^T A_L x (t null when x = 0):
-// res = r - t, d = c1 d + c2 Dinv res, x += d (x = d when `init`)
-// One Chebyshev-Jacobi point update (res = r - t, or r when t is absent).
-__device__ inline void cheb_pt(float r, float t, bool has_t, float dinv, float &d, float &x,
-                               float c1, float c2, int init)
+// Chebyshev step on z = Dinv (r - t), t = QQ^T A_L x assembled (null when x = 0),
+// or with the Schwarz smoother z = wgt o acc: d = c1 d + c2 z, x += d.
+// Of d and x only what a step needs moves: the first step has no d (c1 = 0),
+// after a first step from x = 0 d is x, and the last step's d is not kept.
+enum ChebD { kChebNone = 0, kChebOwn = 1, kChebX = 2 };  // where d comes from
+
+// z = g res
+__device__ inline void cheb_pt(float g, float res, float &d, float &x, float c1, float c2, int din, bool zero)
 {
-    const float res = has_t ? r - t : r;
-    const float di = (init ? 0.0f : c1 * d) + c2 * dinv * res;
+    const float d0 = din == kChebX ? x : d;
+    const float di = (din == kChebNone ? 0.0f : c1 * d0) + c2 * g * res;
     d = di;
-    x = init ? di : x + di;
+    x = zero ? di : x + di;
 }
 
 // FP32 streaming kernels take 16 bytes per lane (float4) when V4: n and ld
@@ -658,11 +661,12 @@ __device__ inline void cheb_pt(float r, float t, bool has_t, float dinv, float &
 // arithmetic per point is the same as in the one-float form.
 #define FLOAT4_AT(p, i) (reinterpret_cast<const float4 *>(p)[i])
 
+// zero: x = 0 on entry (x is written, not read); dout: d is kept
 template <bool V4>
 __global__ void cheb_fused_kernel(int64_t n, VSet vs, int64_t ld, const float *__restrict__ r,
                                   const float *__restrict__ t, const float *__restrict__ Dinv,
                                   float *__restrict__ d, float *__restrict__ x, float c1, float c2,
-                                  int init)
+                                  int din, int dout, int zero)
 {
     const int64_t v = vsel(vs);
     r += v * ld;
@@ -670,68 +674,59 @@ __global__ void cheb_fused_kernel(int64_t n, VSet vs, int64_t ld, const float *_
     d += v * ld;
     x += v * ld;
     const bool ht = t != nullptr;
+    auto res = [&](float rr, float tt) { return ht ? rr - tt : rr; };
     if constexpr (V4) {
         GRID_LOOP(i, n >> 2) {
             const float4 rv = FLOAT4_AT(r, i), gv = FLOAT4_AT(Dinv, i);
             const float4 tv = ht ? FLOAT4_AT(t, i) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             float4 dv = make_float4(0.0f, 0.0f, 0.0f, 0.0f), xv = dv;
-            if (!init) {
-                dv = FLOAT4_AT(d, i);
-                xv = FLOAT4_AT(x, i);
-            }
-            cheb_pt(rv.x, tv.x, ht, gv.x, dv.x, xv.x, c1, c2, init);
-            cheb_pt(rv.y, tv.y, ht, gv.y, dv.y, xv.y, c1, c2, init);
-            cheb_pt(rv.z, tv.z, ht, gv.z, dv.z, xv.z, c1, c2, init);
-            cheb_pt(rv.w, tv.w, ht, gv.w, dv.w, xv.w, c1, c2, init);
-            reinterpret_cast<float4 *>(d)[i] = dv;
+            if (din == kChebOwn) dv = FLOAT4_AT(d, i);
+            if (!zero) xv = FLOAT4_AT(x, i);
+            cheb_pt(gv.x, res(rv.x, tv.x), dv.x, xv.x, c1, c2, din, zero);
+            cheb_pt(gv.y, res(rv.y, tv.y), dv.y, xv.y, c1, c2, din, zero);
+            cheb_pt(gv.z, res(rv.z, tv.z), dv.z, xv.z, c1, c2, din, zero);
+            cheb_pt(gv.w, res(rv.w, tv.w), dv.w, xv.w, c1, c2, din, zero);
+            if (dout) reinterpret_cast<float4 *>(d)[i] = dv;
             reinterpret_cast<float4 *>(x)[i] = xv;
         }
     } else {
         GRID_LOOP(i, n) {
-            float di = init ? 0.0f : d[i], xi = init ? 0.0f : x[i];
-            cheb_pt(r[i], ht ? t[i] : 0.0f, ht, Dinv[i], di, xi, c1, c2, init);
-            d[i] = di;
+            float di = din == kChebOwn ? d[i] : 0.0f, xi = zero ? 0.0f : x[i];
+            cheb_pt(Dinv[i], res(r[i], ht ? t[i] : 0.0f), di, xi, c1, c2, din, zero);
+            if (dout) d[i] = di;
             x[i] = xi;
         }
     }
 }
 
-// Chebyshev step with the Schwarz smoother: z = wgt o acc (acc = QQ^T of the
-// combined local solutions), d = c1 d + c2 z, x += d (x = d when `init`)
+// the Schwarz form: acc = QQ^T of the combined local solutions
 template <bool V4>
 __global__ void cheb_w_kernel(int64_t n, VSet vs, int64_t ld, const float *__restrict__ wgt,
                               const float *__restrict__ acc, float *__restrict__ d,
-                              float *__restrict__ x, float c1, float c2, int init)
+                              float *__restrict__ x, float c1, float c2, int din, int dout, int zero)
 {
     const int64_t v = vsel(vs);
     acc += v * ld;
     d += v * ld;
     x += v * ld;
-    auto pt = [&](float wg, float ac, float &dd, float &xx) {
-        const float di = (init ? 0.0f : c1 * dd) + c2 * wg * ac;
-        dd = di;
-        xx = init ? di : xx + di;
-    };
     if constexpr (V4) {
         GRID_LOOP(i, n >> 2) {
             const float4 wv = FLOAT4_AT(wgt, i), av = FLOAT4_AT(acc, i);
             float4 dv = make_float4(0.0f, 0.0f, 0.0f, 0.0f), xv = dv;
-            if (!init) {
-                dv = FLOAT4_AT(d, i);
-                xv = FLOAT4_AT(x, i);
-            }
-            pt(wv.x, av.x, dv.x, xv.x);
-            pt(wv.y, av.y, dv.y, xv.y);
-            pt(wv.z, av.z, dv.z, xv.z);
-            pt(wv.w, av.w, dv.w, xv.w);
-            reinterpret_cast<float4 *>(d)[i] = dv;
+            if (din == kChebOwn) dv = FLOAT4_AT(d, i);
+            if (!zero) xv = FLOAT4_AT(x, i);
+            cheb_pt(wv.x, av.x, dv.x, xv.x, c1, c2, din, zero);
+            cheb_pt(wv.y, av.y, dv.y, xv.y, c1, c2, din, zero);
+            cheb_pt(wv.z, av.z, dv.z, xv.z, c1, c2, din, zero);
+            cheb_pt(wv.w, av.w, dv.w, xv.w, c1, c2, din, zero);
+            if (dout) reinterpret_cast<float4 *>(d)[i] = dv;
             reinterpret_cast<float4 *>(x)[i] = xv;
         }
     } else {
         GRID_LOOP(i, n) {
-            float di = init ? 0.0f : d[i], xi = init ? 0.0f : x[i];
-            pt(wgt[i], acc[i], di, xi);
-            d[i] = di;
+            float di = din == kChebOwn ? d[i] : 0.0f, xi = zero ? 0.0f : x[i];
+            cheb_pt(wgt[i], acc[i], di, xi, c1, c2, din, zero);
+            if (dout) d[i] = di;
             x[i] = xi;
         }
     }
@@ -1213,18 +1208,20 @@ static int apply_f32(const Level &L, const VSet &vs, const float *x, float *t, d
 // Dinv A x = Dinv r) with `deg` updates; x == 0 on entry when `zero`.
 // one smoothing correction of the batch: with Jacobi, d = c1 d + c2 Dinv (r - t)
 // fused; with Schwarz, the local FDM solutions of r - t combined, QQ^T and
-// weighted, then d = c1 d + c2 z.  t null: x = 0 (res = r).
+// weighted, then d = c1 d + c2 z.  t null: x = 0 (res = r).  din, dout: ChebD.
 static int smooth_step(const Level &L, int l, sem_handle h, const VSet &vs, int smoother,
                        const float *r, const float *t, float *d, float *x, float c1, float c2,
-                       int init, double h1, double h2, hipStream_t s)
+                       int din, int dout, double h1, double h2, hipStream_t s)
 {
     const int64_t n = L.nL;
+    const int zero = t == nullptr;
     if (smoother == SEM_SMOOTH_JACOBI) {
         if (vec_ok(n, n, {r, t, L.Dinv32, d, x}))
-            LAUNCH_B(cheb_fused_kernel<true>, n / 4, vs, s, n, vs, n, r, t, L.Dinv32, d, x, c1, c2,
-                     init);
+            LAUNCH_B(cheb_fused_kernel<true>, n / 4, vs, s, n, vs, n, r, t, L.Dinv32, d, x, c1, c2, din,
+                     dout, zero);
         else
-            LAUNCH_B(cheb_fused_kernel<false>, n, vs, s, n, vs, n, r, t, L.Dinv32, d, x, c1, c2, init);
+            LAUNCH_B(cheb_fused_kernel<false>, n, vs, s, n, vs, n, r, t, L.Dinv32, d, x, c1, c2, din, dout,
+                     zero);
         return SEM_OK;
     }
     Workspace &w = h->ws;
@@ -1235,10 +1232,10 @@ static int smooth_step(const Level &L, int l, sem_handle h, const VSet &vs, int 
     const float *wgt = ras ? L.W32 : L.sz_w;
     if (vec_ok(n, n, {wgt, acc, d, x}))
         LAUNCH_B(cheb_w_kernel<true>, n / 4, vs, s, n, vs, n, wgt, (const float *)acc, d, x, c1, c2,
-                 init);
+                 din, dout, zero);
     else
         LAUNCH_B(cheb_w_kernel<false>, n, vs, s, n, vs, n, wgt, (const float *)acc, d, x, c1, c2,
-                 init);
+                 din, dout, zero);
     return SEM_OK;
 }
 
@@ -1255,18 +1252,19 @@ static int chebyshev(const Level &L, int l, sem_handle h, const VSet &vs, int sm
     const double sigma = theta / delta;
     double rho_prev = 1.0 / sigma;
     if (zero) {
-        SEM_TRY(smooth_step(L, l, h, vs, smoother, r, nullptr, d, x, 0.0f, (float)(1.0 / theta), 1, h1,
-                            h2, s));
+        SEM_TRY(smooth_step(L, l, h, vs, smoother, r, nullptr, d, x, 0.0f, (float)(1.0 / theta), kChebNone, 0,
+                            h1, h2, s));
     } else {
         SEM_TRY(apply_f32(L, vs, x, t, h1, h2, s));
-        SEM_TRY(smooth_step(L, l, h, vs, smoother, r, t, d, x, 0.0f, (float)(1.0 / theta), 0, h1, h2,
-                            s));
+        SEM_TRY(smooth_step(L, l, h, vs, smoother, r, t, d, x, 0.0f, (float)(1.0 / theta), kChebNone, deg > 1,
+                            h1, h2, s));
     }
     for (int k = 1; k < deg; ++k) {
         const double rho = 1.0 / (2.0 * sigma - rho_prev);
         SEM_TRY(apply_f32(L, vs, x, t, h1, h2, s));
         SEM_TRY(smooth_step(L, l, h, vs, smoother, r, t, d, x, (float)(rho * rho_prev),
-                            (float)(2.0 * rho / delta), 0, h1, h2, s));
+                            (float)(2.0 * rho / delta), zero && k == 1 ? kChebX : kChebOwn, k + 1 < deg, h1,
+                            h2, s));
         rho_prev = rho;
     }
     return SEM_OK;
