@@ -101,6 +101,7 @@ struct KrylovScalars {
     double tol2;    // tol^2 (b, b)_W
     double rz2[2];  // (r, z)_W by iteration parity (written by one block while
                     // the other slot is read by all blocks of the same kernel)
+    double al2[2];  // alpha by iteration parity (coarse solve)
     int iters;
     int done;       // 1 once converged or failed; later kernels become no-ops
     int status;     // SEM_OK / SEM_EBREAKDOWN
@@ -178,13 +179,12 @@ struct Level {
     double sz_lmax = 0.0;  // lambda_max(M^{-1} A) estimate for the current key
     // the coarsest level's operator assembled on its free unique nodes (built
     // per (h1, h2) with the p-multigrid preconditioner): CSR cs_row [nf+1],
-    // cs_col / cs_val [nnz], inverse diagonal cs_dinv and unit weights cs_one
-    // [nf]; cs_uid [nL] the free node of each copy (-1 on Dirichlet copies),
-    // cs_rep [nf] one copy of each node; cs_bu / cs_xu [kMaxRhs][nf] the
-    // right-hand sides and solutions of the coarse solves on these nodes
+    // cs_col / cs_val [nnz], inverse diagonal cs_dinv [nf]; cs_uid [nL] the
+    // free node of each copy (-1 on Dirichlet copies), cs_rep [nf] one copy of
+    // each node; cs_xu [kMaxRhs][nf] the coarse solutions on these nodes
     int64_t cs_nf = 0, cs_nnz = 0;
     int32_t *cs_row = nullptr, *cs_col = nullptr, *cs_uid = nullptr, *cs_rep = nullptr;
-    double *cs_val = nullptr, *cs_dinv = nullptr, *cs_one = nullptr, *cs_bu = nullptr, *cs_xu = nullptr;
+    double *cs_val = nullptr, *cs_dinv = nullptr, *cs_xu = nullptr;
 };
 
 // Phase timers of a solve (sem_solve_opts.timers): a chain of events on the

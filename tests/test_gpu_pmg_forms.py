@@ -1,0 +1,45 @@
+"""V-cycle with other numbers of Chebyshev updates than the default two (the
+first, middle and last update move different vectors) and with a coarse solve
+run to convergence over many iterations, against the oracle's V-cycle with the
+same bounds as the default schedule's test: 5e-4 of the W-norm with the coarse
+tolerance 1e-2, 5e-5 (FP32 round-off of the smoothed levels) with 1e-12."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+from oracle import solvers  # noqa: E402
+from paper_2104_05829_amd import Sem, inputs  # noqa: E402
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+LIBRARY_START_SEED = 0x5EED5EED  # start vector of the library's Lanczos estimate
+
+
+def _mesh(shape, N, bc, deform=None):
+    xi, _ = oracle.gll(N)
+    return inputs.box_mesh(*shape, xi, deform=deform, amp=0.05, bc=bc)
+
+
+@pytest.mark.parametrize("degree", [1, 2, 3, 4])
+@pytest.mark.parametrize("levels,shape,bc,h2", [((7, 3, 1), (3, 3, 2), "dirichlet", 10.0),
+                                                ((2, 1), (7, 6, 5), "dirichlet", 1.0)])
+def test_vcycle_matches_oracle(levels, shape, bc, h2, degree):
+    print(f"[gpu] pmg forms {levels} {shape} {bc} degree={degree}", flush=True)
+    m = _mesh(shape, levels[0], bc, deform="cyclic")
+    mg = solvers.PMG(lambda n: _mesh(shape, n, bc), m, levels=levels, h1=1.0, h2=h2, degree=degree)
+    mg.bounds = [(0.1 * lam, 1.1 * lam) for lam in
+                 (solvers.lanczos_lambda_max(lv, 20, seed=LIBRARY_START_SEED) for lv in mg.levels[:-1])]
+    lv = mg.levels[0]
+    s = Sem(m, levels=levels)
+    r = lv.mask * oracle.qqt(m.gid, lv.B * inputs.gaussian_per_node(m.gid, 80))
+    for ctol, cmax, bar in ((1e-2, 20, 5e-4), (1e-12, 2000, 5e-5)):
+        mg.coarse_tol, mg.coarse_maxit = ctol, cmax
+        zo = mg.vcycle(r)
+        z = s.pmg_apply(torch.tensor(r, device="cuda"), h1=1.0, h2=h2, coarse_tol=ctol, coarse_maxit=cmax,
+                        cheb_degree=degree).cpu().numpy()
+        rel = np.sqrt(np.sum(lv.W * (z - zo) ** 2) / np.sum(lv.W * zo ** 2))
+        assert rel <= bar, (ctol, rel)
+    s.free()
