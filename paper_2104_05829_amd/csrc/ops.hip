@@ -16,16 +16,6 @@ namespace semx {
 // one-thread-per-segment pass.
 // ---------------------------------------------------------------------------
 
-// Workgroups are dispatched round-robin over the 8 XCDs, each with its own L2;
-// give XCD x the x-th contiguous range of workgroups so that neighbouring
-// segments (which share cache lines of the L-vector) meet in one L2.
-__device__ inline int64_t xcd_chunk_block(int64_t b, int64_t nb)
-{
-    const int64_t x = b % 8, q = b / 8;
-    const int64_t per = nb / 8, rem = nb % 8;
-    return x * per + (x < rem ? x : rem) + q;
-}
-
 constexpr int kGsWavesPerBlock = 4;
 
 // The reduction of a segment (gs_op of Sec. 3.2): the sum (the direct-

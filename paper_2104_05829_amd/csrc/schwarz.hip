@@ -455,203 +455,213 @@ int build_schwarz(Level &L, hipStream_t s)
 }
 
 // ------------------------------------------------------------------ kernels
-// Local FDM solves, EPB elements per workgroup, ne^2 threads per element.
-// Every 1D transform is applied by threads that each own one whole line of
-// the direction transformed: the c-lines by thread (a, b) in registers
-// (gathered inputs, and the final transform back), the b-lines by thread
-// (a, k) and the a-lines by thread (b, k), read from and written to two LDS
-// buffers, so a thread reads ne values per transform rather than ne^2, and the
-// forward a transform, the division by the eigenvalue sum and the transform
-// back along a run in one pass on the thread's row.  The rows of the
-// element's S matrices are read from LDS (every lane of the element reads the
-// same row).  Own points are read directly and written to acc; extension
-// points are gathered through the compact map and (ASM) written to U.  The
-// eigenbases and the extension map of an element are loaded once and serve
-// every vector of the batch in turn.  FP32.
+// Local FDM solves, a thread per line (a, b) of a vector.  Every 1D transform is
+// applied by threads that each own one whole line of the direction transformed:
+// the c-lines by thread (a, b) (gathered inputs, and the final transform back),
+// the b-lines by thread (a, k) and the a-lines by thread (b, k), each read from
+// and written back to its own place in one LDS buffer; the forward a transform,
+// the division by the eigenvalue sum and the transform back along a run in one
+// pass on the thread's row.  Own points go to acc, extension points (ASM) to U.
+// FP32.
+//
+// The transforms are products of an ne x ne matrix with the lines of a
+// wavefront, on v_mfma_f32_4x4x1 (16 blocks of 4 columns: a lane's column is its
+// line, so a lane feeds its own values and receives its own results).  One block
+// of the first operand is broadcast to its group of 2^CB blocks, so a register
+// holds 2^CB of the 4-row pieces of S and a matrix takes one to three registers.
+// A group's lines belong to one element: the whole wavefront (CB = 4) from
+// ne = 7 on (49 lines), 16 lanes (CB = 2) below, where an element fills less than
+// a wavefront (25 lines take 32 lanes, 36 take 48) and a workgroup holds several
+// (110592 elements, ne = 5: 81 us with a wavefront each, 62 us so).  The vectors
+// of a batch lie side by side in the lanes, as they fill wavefronts better (3 x
+// 100 lines take 5, one 2), but run one after the other at ne = 5 (LOOP), where
+// what a thread derives from its position weighs more than its lines (3 vectors
+// of 110592 elements: 168 us side by side, 140 us in turn; ne = 6, 64000
+// elements: 158 and 162).
+//
+// Before, the rows of S came from LDS for every product, and these reads (30
+// ds_read_b128 a wavefront and transform at ne = 10) bound the kernel: 65 us for
+// 3 vectors of 3315 elements at ne = 10 with r - t gathered (1 vector 27), 35 us
+// now (17).  Without the matrix instructions it takes 27 us, without the input
+// reads 30: the phases of few resident workgroups hardly overlap.  3 vectors at
+// ne = 6: 21 -> 13 us.  Workgroups of neighbouring elements share an L2: in plain
+// order the neighbours' points came over the fabric (53 against 45 us then).
+typedef float v4f __attribute__((ext_vector_type(4)));
+
 template <int NE>
 struct FdmShape {
-    static constexpr int NQ = NE - 2, NE2 = NE * NE, THREADS = 256;
-    static constexpr int EPB = THREADS / NE2;
+    static constexpr int NQ = NE - 2, NE2 = NE * NE;
+    static constexpr int MAX_THREADS = NE >= 7 ? (kMaxRhs * NE2 + 63) / 64 * 64 : 256;
     static constexpr int NEXT = NE * NE * NE - NQ * NQ * NQ;
-    static constexpr int LDP = NE + 1;
-    static constexpr int NEP = (NE + 3) & ~3;  // S rows padded to 16 bytes
+    static constexpr int LDP = NE + 1;            // pitch of the a-lines
+    static constexpr int CB = NE >= 7 ? 4 : 2;    // blocks that share an element: 2^CB
+    static constexpr int MB = (NE + 3) / 4;       // 4-row pieces of a column of S
+    static constexpr int SR = (NE * MB + (1 << CB) - 1) >> CB;  // registers of a matrix
+    static constexpr bool LOOP = NE < 6;
 };
 
+// y = S x on the line of every lane, columns in ascending order; s the pieces of
+// S: piece k MB + j in block (piece mod 2^CB) of s[piece / 2^CB], a row per lane
+template <int NE, int P = 0>
+__device__ __forceinline__ void fdm_product(const float (&s)[FdmShape<NE>::SR], const float (&x)[NE],
+                                            v4f (&y)[FdmShape<NE>::MB])
+{
+    constexpr int MB = FdmShape<NE>::MB, CB = FdmShape<NE>::CB;
+    if constexpr (P < NE * MB) {
+        if constexpr (P < MB) y[P] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        y[P % MB] = __builtin_amdgcn_mfma_f32_4x4x1f32(s[P >> CB], x[P / MB], y[P % MB], CB, P % (1 << CB), 0);
+        fdm_product<NE, P + 1>(s, x, y);
+    }
+}
+
+// epb elements of ln lanes a workgroup, the vectors of the batch side by side;
+// LOOP: one after the other
 template <int NE, bool EXT_OUT>
-__global__ void __launch_bounds__(FdmShape<NE>::THREADS)
-fdm_kernel(int64_t E, const int32_t *__restrict__ ix, const float *__restrict__ Sg,
+__global__ void __launch_bounds__(FdmShape<NE>::MAX_THREADS, FdmShape<NE>::LOOP ? 7 : 1)
+fdm_kernel(int64_t E, int ln, int epb, const int32_t *__restrict__ ix, const float *__restrict__ Sg,
            const float *__restrict__ lamg, const float *__restrict__ r, const float *__restrict__ t,
            int64_t ld, float *__restrict__ acc, float *__restrict__ U, float h1, float h2, VSet vs)
 {
     using F = FdmShape<NE>;
-    constexpr int NQ = F::NQ, NE2 = F::NE2, EPB = F::EPB, NEXT = F::NEXT, LDP = F::LDP, NEP = F::NEP;
-    constexpr int NP = NQ * NQ * NQ;
-    __shared__ __align__(16) float sS[EPB][3][NE][NEP];  // Sx, Sy, Sz of each element, rows [m][.]
-    __shared__ float sl[EPB][3][NE];                     // eigenvalues along x, y, z
-    __shared__ float sa[EPB][NE][NE][LDP];               // [c][b][a]
-    __shared__ float sb[EPB][NE][NE][LDP];
-    const int tid = threadIdx.x;
-    const int el = tid / NE2, ij = tid - el * NE2;
+    constexpr int NQ = F::NQ, NE2 = F::NE2, NEXT = F::NEXT, LDP = F::LDP, MB = F::MB, SR = F::SR;
+    constexpr int CB = F::CB, NP = NQ * NQ * NQ;
+    constexpr bool LOOP = F::LOOP;
+    extern __shared__ float fdm_lds[];  // lines [epb][ni][NE][NE][LDP], S [epb][3][NE][NE], lam [epb][3][NE]
+    const int ni = LOOP ? 1 : vs.n;     // vectors side by side
+    const int64_t e0 = xcd_chunk_block(blockIdx.x, gridDim.x) * epb;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int part = CB == 4 ? 0 : tid / ln, li = tid - part * ln;
+    const int fi = li / NE2, ij = li - fi * NE2;
+    const bool in = CB == 4 || (part < epb && e0 + part < E);
+    const bool act = in && fi < ni;
     const int a = ij % NE, b = ij / NE;  // also (x, k) of the line-owner stages
-    const bool lane = el < EPB;
     const bool acol = a == 0 || a == NE - 1 || b == 0 || b == NE - 1;  // border column
-    // extension slots of this column: ebase + c (border column), or ebase and
-    // ebase + 1 for c = 0 and c = ne-1 (inner column)
-    const int ebase = schwarz_ext_slot(NE, a, b, 0);
-    const int64_t groups = (E + EPB - 1) / EPB;
-    for (int64_t g = blockIdx.x; g < groups; g += gridDim.x) {
-        const int64_t e = g * EPB + el;
-        const bool act = lane && e < E;
-        __syncthreads();  // LDS of the previous group consumed
-        // the element's eigenbases and eigenvalues and this column's
-        // extension copies, once for every vector of the batch
-        int32_t q[NE];
+    // every lane of a group holds operands of its element, also without a line
+    const int el = in ? part : 0;
+    const int64_t e = e0 + el;
+    float *const sS = fdm_lds + epb * ni * NE2 * LDP, *const sl = sS + epb * 3 * NE2;
+    float *const sf = fdm_lds + (el * ni + (act ? fi : 0)) * NE2 * LDP;
+    {
+        const int ne = (int)min((int64_t)epb, E - e0);
+        for (int g = tid; g < ne * 3 * NE2; g += blockDim.x) sS[g] = Sg[e0 * 3 * NE2 + g];
+        for (int g = tid; g < ne * 3 * NE; g += blockDim.x) sl[g] = lamg[e0 * 3 * NE + g];
+    }
+    constexpr int KE = (NEXT + NE2 - 1) / NE2;
+    int32_t q[KE];
+#pragma unroll
+    for (int m = 0; m < KE; ++m) q[m] = ix[e * NEXT + min(ij + m * NE2, NEXT - 1)];
+    const int64_t own = e * NP + (acol ? 0 : (b - 1) * NQ + a - 1);
+    float *const cl = sf + b * LDP + a;             // column (a, b), step NE * LDP
+    float *const bl = sf + b * NE * LDP + a;        // line (a, k = b), step LDP
+    float *const al = sf + (b * NE + a) * LDP;      // row (b = a, k = b), step 1
+    // the matrix operands: every lane of every wavefront holds its pieces (the
+    // rows beyond ne feed results that nobody reads)
+    float fw[3][SR], bw[3][SR];  // S^T (to modes) and S (back)
+    const float *const le = sl + el * 3 * NE;
+    float lyz = 0.0f;  // of the row (b = a, k = b)
+    auto operands = [&]() {
+        const float *const Se = sS + el * 3 * NE2;
+#pragma unroll
+        for (int g = 0; g < SR; ++g) {
+            const int piece = (g << CB) + ((lane >> 2) & ((1 << CB) - 1));
+            const int k = piece / MB, j = (piece - k * MB) * 4 + (lane & 3);
+            const bool has = k < NE && j < NE;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                fw[d][g] = Se[d * NE2 + (has ? k * NE + j : 0)];
+                bw[d][g] = Se[d * NE2 + (has ? j * NE + k : 0)];
+            }
+        }
+        lyz = le[NE + a] + le[2 * NE + b];
+    };
+    if (LOOP) {
+        __syncthreads();
+        operands();
+    }
+    for (int f = act ? fi : 0;; ++f) {
+        const int64_t v = vs.at(f);
+        const float *const rv = r + v * ld, *const tv = t ? t + v * ld : nullptr;
+        // the extension points go through LDS in the order of their list, so that
+        // a wavefront's loads lie side by side; the own points straight into the
+        // column's registers.  Absent entries read the vector's first point and
+        // border columns the element's, so that no load waits for a branch.
+        float x[NE], tx[NE], xe[KE], te[KE];
+#pragma unroll
+        for (int c = 1; c < NE - 1; ++c) x[c] = rv[own + (c - 1) * NQ * NQ];
+#pragma unroll
+        for (int c = 1; c < NE - 1; ++c) tx[c] = tv ? tv[own + (c - 1) * NQ * NQ] : 0.0f;
+#pragma unroll
+        for (int m = 0; m < KE; ++m) xe[m] = rv[max(q[m], 0)];
+#pragma unroll
+        for (int m = 0; m < KE; ++m) te[m] = tv ? tv[max(q[m], 0)] : 0.0f;
+        if (LOOP && f > 0) __syncthreads();  // the last vector's lines consumed
+#pragma unroll
+        for (int m = 0; m < KE; ++m) {
+            const int slot = ij + m * NE2;
+            int pa = a, pb = b, pc = m * (NE - 1);  // the planes c = 0 and c = ne - 1
+            if (m >= 2) schwarz_ext_point(NE, slot, pa, pb, pc);
+            if (act && slot < NEXT) sf[(pc * NE + pb) * LDP + pa] = q[m] >= 0 ? xe[m] - te[m] : 0.0f;
+        }
+#pragma unroll
+        for (int c = 1; c < NE - 1; ++c) x[c] -= tx[c];
+        v4f y[MB];
+        __syncthreads();
+        if (!LOOP) operands();
+        x[0] = cl[0];
+        x[NE - 1] = cl[(NE - 1) * NE * LDP];
+        if (acol)
+#pragma unroll
+            for (int c = 1; c < NE - 1; ++c) x[c] = cl[c * NE * LDP];
+        fdm_product<NE>(fw[2], x, y);  // modes along c
+        if (act)
+#pragma unroll
+            for (int k = 0; k < NE; ++k) cl[k * NE * LDP] = y[k / 4][k % 4];
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < NE; ++m) x[m] = bl[m * LDP];
+        fdm_product<NE>(fw[1], x, y);  // along b
+        if (act)
+#pragma unroll
+            for (int m = 0; m < NE; ++m) bl[m * LDP] = y[m / 4][m % 4];
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < NE; ++m) x[m] = al[m];
+        fdm_product<NE>(fw[0], x, y);  // along a, divided by the eigenvalue sum, and back
+#pragma unroll
+        for (int i = 0; i < NE; ++i)
+            x[i] = y[i / 4][i % 4] * __builtin_amdgcn_rcpf(h1 * (le[i] + lyz) + h2);
+        fdm_product<NE>(bw[0], x, y);
+        if (act)
+#pragma unroll
+            for (int m = 0; m < NE; ++m) al[m] = y[m / 4][m % 4];
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < NE; ++m) x[m] = bl[m * LDP];
+        fdm_product<NE>(bw[1], x, y);  // back along b
+        if (act)
+#pragma unroll
+            for (int m = 0; m < NE; ++m) bl[m * LDP] = y[m / 4][m % 4];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NE; ++k) x[k] = cl[k * NE * LDP];
+        fdm_product<NE>(bw[2], x, y);  // back along c
         if (act) {
-            const float *Se = Sg + e * 3 * NE2;
-#pragma unroll
-            for (int d = 0; d < 3; ++d) sS[el][d][b][a] = Se[d * NE2 + ij];
-            if (ij < 3 * NE) (&sl[el][0][0])[ij] = lamg[e * 3 * NE + ij];
-            const int32_t *ixe = ix + e * NEXT;
+            float *const Ue = EXT_OUT ? U + v * E * NEXT + e * NEXT : nullptr;
             if (acol) {
+                if (EXT_OUT)
 #pragma unroll
-                for (int c = 0; c < NE; ++c) q[c] = ixe[ebase + c];
+                    for (int c = 0; c < NE; ++c) Ue[schwarz_ext_slot(NE, a, b, c)] = y[c / 4][c % 4];
             } else {
-                q[0] = ixe[ebase];
-                q[NE - 1] = ixe[ebase + 1];
+                float *const acce = acc + v * ld + own;
+#pragma unroll
+                for (int c = 1; c < NE - 1; ++c) acce[(c - 1) * NQ * NQ] = y[c / 4][c % 4];
+                if (EXT_OUT) {
+                    Ue[schwarz_ext_slot(NE, a, b, 0)] = y[0][0];
+                    Ue[schwarz_ext_slot(NE, a, b, NE - 1)] = y[(NE - 1) / 4][(NE - 1) % 4];
+                }
             }
         }
-        __syncthreads();  // sS, sl ready
-        for (int f = 0; f < vs.n; ++f) {
-            const int64_t v = vs.at(f);
-            const float *rv = r + v * ld;
-            const float *tv = t ? t + v * ld : nullptr;
-            float vv[NE];
-            if (act) {
-                auto gather = [&](int32_t qq) {
-                    return qq >= 0 ? (tv ? rv[qq] - tv[qq] : rv[qq]) : 0.0f;
-                };
-                if (acol) {
-#pragma unroll
-                    for (int c = 0; c < NE; ++c) vv[c] = gather(q[c]);
-                } else {
-                    const float *re = rv + e * NP + (b - 1) * NQ + (a - 1);
-                    const float *te = tv ? tv + e * NP + (b - 1) * NQ + (a - 1) : nullptr;
-                    vv[0] = gather(q[0]);
-#pragma unroll
-                    for (int c = 1; c < NE - 1; ++c)
-                        vv[c] = te ? re[(c - 1) * NQ * NQ] - te[(c - 1) * NQ * NQ] : re[(c - 1) * NQ * NQ];
-                    vv[NE - 1] = gather(q[NE - 1]);
-                }
-                // modes along c: w[k] = sum_c Sz[c][k] vv[c]
-                float w[NE];
-#pragma unroll
-                for (int k = 0; k < NE; ++k) w[k] = 0.0f;
-#pragma unroll
-                for (int c = 0; c < NE; ++c) {
-                    const float *Sr = &sS[el][2][c][0];
-#pragma unroll
-                    for (int k = 0; k < NE; ++k) w[k] += Sr[k] * vv[c];
-                }
-#pragma unroll
-                for (int k = 0; k < NE; ++k) sa[el][k][b][a] = w[k];
-            }
-            __syncthreads();
-            if (act) {
-                // modes along b on the line (a, k = b): y[j] = sum_m Sy[m][j] x[m]
-                const int k = b;
-                float x[NE], y[NE];
-#pragma unroll
-                for (int m = 0; m < NE; ++m) x[m] = sa[el][k][m][a];
-#pragma unroll
-                for (int j = 0; j < NE; ++j) y[j] = 0.0f;
-#pragma unroll
-                for (int m = 0; m < NE; ++m) {
-                    const float *Sr = &sS[el][1][m][0];
-#pragma unroll
-                    for (int j = 0; j < NE; ++j) y[j] += Sr[j] * x[m];
-                }
-#pragma unroll
-                for (int j = 0; j < NE; ++j) sb[el][k][j][a] = y[j];
-            }
-            __syncthreads();
-            if (act) {
-                // the row (b = a, k = b) along a: modes, division by the
-                // eigenvalue sum, and back
-                const int bb = a, k = b;
-                float x[NE], y[NE];
-#pragma unroll
-                for (int m = 0; m < NE; ++m) x[m] = sb[el][k][bb][m];
-#pragma unroll
-                for (int i = 0; i < NE; ++i) y[i] = 0.0f;
-#pragma unroll
-                for (int m = 0; m < NE; ++m) {
-                    const float *Sr = &sS[el][0][m][0];
-#pragma unroll
-                    for (int i = 0; i < NE; ++i) y[i] += Sr[i] * x[m];
-                }
-                const float lyz = sl[el][1][bb], lzk = sl[el][2][k];
-#pragma unroll
-                for (int i = 0; i < NE; ++i) y[i] *= __builtin_amdgcn_rcpf(h1 * (sl[el][0][i] + lyz + lzk) + h2);
-                // the rows of Sx are read again below rather than kept in
-                // registers from the forward pass (that would cost ne^2 VGPRs)
-                asm volatile("" ::: "memory");
-#pragma unroll
-                for (int i = 0; i < NE; ++i) {
-                    const float *Sr = &sS[el][0][i][0];
-                    float sum = 0.0f;
-#pragma unroll
-                    for (int m = 0; m < NE; ++m) sum += Sr[m] * y[m];
-                    sa[el][k][bb][i] = sum;
-                }
-            }
-            __syncthreads();
-            if (act) {
-                // back along b on the line (a, k = b)
-                const int k = b;
-                float x[NE];
-#pragma unroll
-                for (int m = 0; m < NE; ++m) x[m] = sa[el][k][m][a];
-#pragma unroll
-                for (int j = 0; j < NE; ++j) {
-                    const float *Sr = &sS[el][1][j][0];
-                    float sum = 0.0f;
-#pragma unroll
-                    for (int m = 0; m < NE; ++m) sum += Sr[m] * x[m];
-                    sb[el][k][j][a] = sum;
-                }
-            }
-            __syncthreads();
-            if (act) {
-                // back along c on the column (a, b), in registers
-                float w[NE];
-#pragma unroll
-                for (int k = 0; k < NE; ++k) w[k] = sb[el][k][b][a];
-                float *acce = acc + v * ld + e * NP + (b - 1) * NQ + (a - 1);
-                float *Ue = EXT_OUT ? U + v * E * NEXT + e * NEXT : nullptr;
-                auto line = [&](int c) {
-                    const float *Sr = &sS[el][2][c][0];
-                    float sum = 0.0f;
-#pragma unroll
-                    for (int k = 0; k < NE; ++k) sum += Sr[k] * w[k];
-                    return sum;
-                };
-                if (acol) {
-                    if (EXT_OUT)
-#pragma unroll
-                        for (int c = 0; c < NE; ++c) Ue[ebase + c] = line(c);
-                } else {
-#pragma unroll
-                    for (int c = 1; c < NE - 1; ++c) acce[(c - 1) * NQ * NQ] = line(c);
-                    if (EXT_OUT) {
-                        Ue[ebase] = line(0);
-                        Ue[ebase + 1] = line(NE - 1);
-                    }
-                }
-            }
-            // the next vector's first LDS writes (sa) follow this vector's
-            // last sa reads (before the barrier above); its sb writes follow
-            // a barrier every thread reaches after the reads of sb here
-        }
+        if (!LOOP || f + 1 >= vs.n) break;
     }
 }
 
@@ -696,18 +706,17 @@ int launch_schwarz(const Level &L, bool ras, const float *r, const float *t, flo
         set_error("Schwarz smoother not built on this level");
         return SEM_EINVAL;
     }
-    // one workgroup per EPB elements (a persistent grid capped at the
-    // resident count, or at 8 per CU, was slower: the last, partial round of
-    // workgroups leaves CUs idle)
 #define SEM_FDM(NE)                                                                                   \
     case NE: {                                                                                        \
-        const dim3 grid((unsigned)((L.E + FdmShape<NE>::EPB - 1) / FdmShape<NE>::EPB));              \
-        if (ras)                                                                                      \
-            hipLaunchKernelGGL((fdm_kernel<NE, false>), grid, dim3(FdmShape<NE>::THREADS), 0, s, L.E, \
-                               L.sz_ix, L.sz_S, L.sz_lam, r, t, L.nL, acc, U, (float)h1, (float)h2, vs); \
-        else                                                                                          \
-            hipLaunchKernelGGL((fdm_kernel<NE, true>), grid, dim3(FdmShape<NE>::THREADS), 0, s, L.E,  \
-                               L.sz_ix, L.sz_S, L.sz_lam, r, t, L.nL, acc, U, (float)h1, (float)h2, vs); \
+        using F = FdmShape<NE>;                                                                       \
+        const int grp = 4 << F::CB, ni = F::LOOP ? 1 : vs.n;                                          \
+        const int ln = (ni * F::NE2 + grp - 1) / grp * grp;                                           \
+        const int epb = F::CB < 4 ? std::max(1, 256 / ln) : 1;                                        \
+        const size_t lds = sizeof(float) * epb * (F::NE2 * (ni * F::LDP + 3) + 3 * NE);               \
+        auto kern = ras ? fdm_kernel<NE, false> : fdm_kernel<NE, true>;                               \
+        hipLaunchKernelGGL(kern, dim3((unsigned)((L.E + epb - 1) / epb)),                             \
+                           dim3((unsigned)((epb * ln + 63) / 64 * 64)), lds, s, L.E, ln, epb, L.sz_ix, \
+                           L.sz_S, L.sz_lam, r, t, L.nL, acc, U, (float)h1, (float)h2, vs);           \
         SEM_HIP(hipGetLastError());                                                                   \
         break;                                                                                        \
     }

@@ -342,18 +342,45 @@ template <typename TI>
 int launch_prolong_add(const Level &F, const Level &C, const TI *in, float *x, const VSet &vs,
                        hipStream_t s);
 
+// Workgroups are dispatched round-robin over the 8 XCDs, each with its own L2;
+// give XCD x the x-th contiguous range of workgroups so that neighbours (which
+// share cache lines of the L-vector) meet in one L2.
+__device__ inline int64_t xcd_chunk_block(int64_t b, int64_t nb)
+{
+    const int64_t x = b % 8, q = b / 8;
+    const int64_t per = nb / 8, rem = nb % 8;
+    return x * per + (x < rem ? x : rem) + q;
+}
+
 // Extended point (a, b, c) outside the element (some coordinate 0 or ne-1):
-// its slot in [0, n_ext).  Columns (a, b) on the border of the ne x ne square
-// hold ne slots each; inner columns hold their two end points.
+// its slot in [0, n_ext): the planes c = 0 and c = ne-1, then the 4 (ne-1)
+// border points of every plane between.
 __host__ __device__ inline int schwarz_ext_slot(int ne, int a, int b, int c)
 {
-    int col;
-    if (b == 0) col = a;
-    else if (b == ne - 1) col = ne + a;
-    else if (a == 0) col = 2 * ne + (b - 1);
-    else if (a == ne - 1) col = 2 * ne + (ne - 2) + (b - 1);
-    else return (4 * ne - 4) * ne + ((b - 1) * (ne - 2) + (a - 1)) * 2 + (c == ne - 1 ? 1 : 0);
-    return col * ne + c;
+    if (c == 0) return b * ne + a;
+    if (c == ne - 1) return (ne + b) * ne + a;
+    int p;
+    if (b == 0) p = a;
+    else if (b == ne - 1) p = ne + a;
+    else p = 2 * ne + (a != 0 ? ne - 2 : 0) + b - 1;
+    return 2 * ne * ne + (c - 1) * 4 * (ne - 1) + p;
+}
+
+// the extended point of a slot behind the two planes
+__host__ __device__ inline void schwarz_ext_point(int ne, int slot, int &a, int &b, int &c)
+{
+    const int ring = 4 * (ne - 1);
+    slot -= 2 * ne * ne;
+    c = 1 + slot / ring;
+    const int p = slot - (c - 1) * ring;
+    if (p < 2 * ne) {
+        b = p < ne ? 0 : ne - 1;
+        a = p < ne ? p : p - ne;
+    } else {
+        const bool hi = p >= 3 * ne - 2;
+        b = 1 + p - 2 * ne - (hi ? ne - 2 : 0);
+        a = hi ? ne - 1 : 0;
+    }
 }
 
 // overlapping Schwarz smoother of a level (schwarz.hip): build_schwarz fills

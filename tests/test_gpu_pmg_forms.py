@@ -2,7 +2,10 @@
 first, middle and last update move different vectors) and with a coarse solve
 run to convergence over many iterations, against the oracle's V-cycle with the
 same bounds as the default schedule's test: 5e-4 of the W-norm with the coarse
-tolerance 1e-2, 5e-5 (FP32 round-off of the smoothed levels) with 1e-12."""
+tolerance 1e-2, 5e-5 (FP32 round-off of the smoothed levels) with 1e-12.  Schwarz smoothing of
+every order with every number of vectors: the rows of a lockstep solve, whose
+lines share wavefronts, against the solves alone, iterations within 1 and
+solutions within 1e-7 of the largest value at a residual of 1e-9."""
 import numpy as np
 import pytest
 
@@ -42,4 +45,23 @@ def test_vcycle_matches_oracle(levels, shape, bc, h2, degree):
                         cheb_degree=degree).cpu().numpy()
         rel = np.sqrt(np.sum(lv.W * (z - zo) ** 2) / np.sum(lv.W * zo ** 2))
         assert rel <= bar, (ctol, rel)
+    s.free()
+
+
+@pytest.mark.parametrize("smoother", ["asm", "ras"])
+@pytest.mark.parametrize("N", [2, 3, 4, 5, 6, 7, 8])
+def test_schwarz_rows_match_single_solves(N, smoother):
+    print(f"[gpu] schwarz rows N={N} {smoother}", flush=True)
+    m = _mesh((4, 3, 3), N, "dirichlet", deform="cyclic")
+    s = Sem(m, levels=(N, 1))
+    B = torch.stack([s.rhs(torch.tensor(inputs.gaussian_per_node(m.gid, 90 + r), device="cuda"))
+                     for r in range(4)])
+    opts = dict(h2=5.0, tol=1e-9, maxit=200, precond="pmg", smoother=smoother, cheb_lo=0.25)
+    alone = [s.solve(B[r], **opts) for r in range(4)]
+    for nr in (1, 2, 3, 4):
+        X, sts, rc = s.solve_multi(B[:nr].clone(), **opts)
+        assert rc == 0 and all(st["converged"] and st["true_rel_res"] <= 1.5e-9 for st in sts), sts
+        for r in range(nr):
+            assert abs(sts[r]["iters"] - alone[r][1]["iters"]) <= 1
+            assert (X[r] - alone[r][0]).abs().max() <= 1e-7 * alone[r][0].abs().max()
     s.free()
