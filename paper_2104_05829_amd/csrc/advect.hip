@@ -489,6 +489,139 @@ __global__ void __launch_bounds__((AdvShape<NQ, M>::THREADS), 2)
     }
 }
 
+// The same for few elements, where one workgroup's chain of dependent steps (six
+// fields, two barriers each) is the time: three lane groups of an element take a
+// velocity component and a coordinate each, all six fields' rows are contracted at
+// once, the lines meet in LDS (in place of the rows) and each group walks a third
+// of the points.  N = 7, 27 / 216 / 512 elements: 14.6 / 16.0 / 21.9 us in turn,
+// 10.5 / 11.9 / 21.7 so (N = 5: 125 / 512 elements 10.7 / 11.5 and 6.8 / 9.6).
+template <int NQ, int M>
+__global__ void __launch_bounds__((3 * AdvShape<NQ, M>::THREADS), 1)
+    velocity_spread_kernel(int64_t E, const double *__restrict__ J, const double *__restrict__ Jd,
+                           const double *__restrict__ wq, const double *__restrict__ x,
+                           const double *__restrict__ y, const double *__restrict__ z,
+                           const double *__restrict__ cv, int64_t ldc, double *__restrict__ ct)
+{
+    using S = AdvShape<NQ, M>;
+    constexpr int NP = S::NP, MM = S::MM, M3 = S::M3, TH = S::THREADS, NR = NQ * NQ;
+    constexpr int ROWS = 6 * NP + 9 * NR * M, LINES = 12 * NQ * MM;
+    __shared__ double lds[ROWS > LINES ? ROWS : LINES];
+    double *const sU = lds, *const sP = lds + 6 * NP, *const sQ = sP + 6 * NR * M;
+    const int64_t e = blockIdx.x;
+    const int g = __builtin_amdgcn_readfirstlane(threadIdx.x / TH), t = threadIdx.x - g * TH;
+    const bool col = t < MM;
+    const int a = col ? t % M : 0, b = col ? t / M : 0;
+    const double wab = wq[a] * wq[b];
+    {
+        constexpr int PF = (6 * NP + 3 * TH - 1) / (3 * TH);
+        double u[PF];
+#pragma unroll
+        for (int m = 0; m < PF; ++m) {
+            const int i = min((int)threadIdx.x + m * 3 * TH, 6 * NP - 1), f = i / NP, q = i - f * NP;
+            const double *p = f < 3 ? cv + f * ldc : f == 3 ? x : f == 4 ? y : z;
+            u[m] = p[e * NP + q];
+        }
+#pragma unroll
+        for (int m = 0; m < PF; ++m) {
+            const int i = threadIdx.x + m * 3 * TH;
+            if (i < 6 * NP) sU[i] = u[m];
+        }
+    }
+    __syncthreads();
+    // over i on GLL rows (k, j) of every field: J u, and for a coordinate Jd u
+    for (int r = threadIdx.x; r < 6 * NR; r += 3 * TH) {
+        double v[NQ];
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) v[i] = sU[r * NQ + i];
+#pragma unroll
+        for (int a2 = 0; a2 < M; ++a2) {
+            double p = 0.0;
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) p += J[a2 * NQ + i] * v[i];
+            sP[r * M + a2] = p;
+        }
+        if (r >= 3 * NR) {
+#pragma unroll
+            for (int a2 = 0; a2 < M; ++a2) {
+                double q = 0.0;
+#pragma unroll
+                for (int i = 0; i < NQ; ++i) q += Jd[a2 * NQ + i] * v[i];
+                sQ[(r - 3 * NR) * M + a2] = q;
+            }
+        }
+    }
+    __syncthreads();
+    // over j on the columns: this group's velocity line and derivative lines
+    double Vf[NQ], Tf[3][NQ];
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) Vf[k] = Tf[0][k] = Tf[1][k] = Tf[2][k] = 0.0;
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) {
+        const double jb = J[b * NQ + j], jd = Jd[b * NQ + j];
+#pragma unroll
+        for (int k = 0; k < NQ; ++k) {
+            const int at = (k * NQ + j) * M + a;
+            const double p = sP[(3 + g) * NR * M + at], q = sQ[g * NR * M + at];
+            Vf[k] += jb * sP[g * NR * M + at];
+            Tf[0][k] += jb * q;
+            Tf[1][k] += jd * p;
+            Tf[2][k] += jb * p;
+        }
+    }
+    // (summed before the barrier: sunk behind it all the rows' values stay in
+    // registers, 150 of them spilled)
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) asm volatile("" : "+v"(Vf[k]), "+v"(Tf[0][k]), "+v"(Tf[1][k]), "+v"(Tf[2][k]));
+    __syncthreads();  // rows consumed: the lines take their place
+    double *const sV = lds, *const sT = lds + 3 * NQ * MM;
+    if (col)
+#pragma unroll
+        for (int k = 0; k < NQ; ++k) {
+            sV[(g * NQ + k) * MM + t] = Vf[k];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) sT[((g * 3 + q) * NQ + k) * MM + t] = Tf[q][k];
+        }
+    __syncthreads();
+    if (col) {
+        double T[3][3][NQ];
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+#pragma unroll
+                for (int k = 0; k < NQ; ++k) T[d][q][k] = sT[((d * 3 + q) * NQ + k) * MM + t];
+        double *ce = ct + e * 3 * M3 + t;
+#pragma unroll 1
+        for (int c = M * g / 3; c < M * (g + 1) / 3; ++c) {
+            const double *Jc = J + c * NQ, *Jdc = Jd + c * NQ;
+            double X[3][3], v[3];  // X[d][q] = dx_d/dr_q
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                X[d][0] = X[d][1] = X[d][2] = v[d] = 0.0;
+#pragma unroll
+                for (int k = 0; k < NQ; ++k) {
+                    X[d][0] += Jc[k] * T[d][0][k];
+                    X[d][1] += Jc[k] * T[d][1][k];
+                    X[d][2] += Jdc[k] * T[d][2][k];
+                    v[d] += Jc[k] * sV[(d * NQ + k) * MM + t];
+                }
+            }
+            const double rho = wab * wq[c];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                const int q1 = (q + 1) % 3, q2 = (q + 2) % 3;
+                double s = 0.0;
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    const int d1 = (d + 1) % 3, d2 = (d + 2) % 3;
+                    s += (X[d1][q1] * X[d2][q2] - X[d2][q1] * X[d1][q2]) * v[d];
+                }
+                ce[q * M3 + c * MM] = rho * s;
+            }
+        }
+    }
+}
+
 int rule_default(int N) { return (3 * N + 2) / 2; }
 
 // automatic choice: the 3D thread block up to this M, the 2D one above.  On
@@ -512,9 +645,16 @@ int launch_velocity(sem_handle h, int M, const double *J, const double *Jd, cons
     // 292 / 313 / 313 us, two waves a SIMD; M = 8 149 / 111 / 115, M = 7 99 / 76 / 77)
     const int64_t cap = (int64_t)(L.n_cu > 0 ? L.n_cu : 256) * (M >= 10 ? 4 : 8);
     const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(L.E, cap)));
+    // up to two elements a CU take the spread form: beyond, its six wavefronts of an
+    // element only queue (1000 elements, N = 7: 29 us in turn, four rounds spread)
+    const bool few = !bad && L.E <= 2 * (int64_t)(L.n_cu > 0 ? L.n_cu : 256);
 #define SEM_VEL(NQ_, M_)                                                                            \
     if (L.nq == NQ_ && M == M_) {                                                                   \
-        if (bad)                                                                                    \
+        if (few)                                                                                    \
+            hipLaunchKernelGGL((velocity_spread_kernel<NQ_, M_>), dim3((unsigned)L.E),              \
+                               dim3(3 * AdvShape<NQ_, M_>::THREADS), 0, s, L.E, J, Jd, wq, h->cx, h->cy, h->cz, \
+                               c, ldc, ct);                                                         \
+        else if (bad)                                                                                    \
             hipLaunchKernelGGL((velocity_kernel<NQ_, M_, true>), grid, dim3(AdvShape<NQ_, M_>::THREADS), 0, \
                                s, L.E, J, Jd, wq, h->cx, h->cy, h->cz, c, ldc, ct, bad);            \
         else                                                                                        \
