@@ -642,8 +642,9 @@ int launch_velocity(sem_handle h, int M, const double *J, const double *Jd, cons
 {
     const Level &L = h->lv[0];
     // as many workgroups as are resident (24^3 elements, 4 / 8 / 16 per CU: M = 11
-    // 292 / 313 / 313 us, two waves a SIMD; M = 8 149 / 111 / 115, M = 7 99 / 76 / 77)
-    const int64_t cap = (int64_t)(L.n_cu > 0 ? L.n_cu : 256) * (M >= 10 ? 4 : 8);
+    // 292 / 313 / 313 us, two waves a SIMD; M = 8 149 / 111 / 115, M = 7 99 / 76 / 77;
+    // 8 / 16 / 32 per CU at 35^3, M = 5: 138 / 129 / 123, at 40^3, M = 4: 141 / 132 / 117)
+    const int64_t cap = (int64_t)(L.n_cu > 0 ? L.n_cu : 256) * (M >= 10 ? 4 : M >= 7 ? 8 : 32);
     const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(L.E, cap)));
     // up to two elements a CU take the spread form: beyond, its six wavefronts of an
     // element only queue (1000 elements, N = 7: 29 us in turn, four rounds spread)
