@@ -158,7 +158,7 @@ __device__ inline bool pcg_direction(const PcgDir &d, int64_t v, int tid, bool r
         rz = sh[0];
         rr = sh[1];
     }
-    if (done) return false;
+    if (ended_before(done, d.stamp)) return false;
     const bool bad = !isfinite(rz) || !isfinite(rr);
     const bool stop = bad || rr <= tol2 || d.iter >= maxit;
     *beta = rz / rz_old;
@@ -168,7 +168,7 @@ __device__ inline bool pcg_direction(const PcgDir &d, int64_t v, int tid, bool r
         sc->rz = rz;
         sc->rz2[d.parity ^ 1] = rz;
         if (bad) sc->status = SEM_EBREAKDOWN;
-        if (stop) sc->done = 1;
+        if (stop) sc->done = d.stamp;
     }
     return !stop;
 }
@@ -238,12 +238,15 @@ ax_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
     const int fs = NW == 1 ? 0 : (int)threadIdx.x >> 6;
     const int tid = NW == 1 ? (int)threadIdx.x : (int)threadIdx.x & 63;
     if (NW > 1 && tid >= S::THREADS) return;
+    bool dirn = false;
+    if constexpr (DOT) dirn = dir.sc != nullptr;
     int64_t v[NI];
     bool live[NI], any = false;
 #pragma unroll
     for (int q = 0; q < NI; ++q) {
         v[q] = vs.at(fs * NI + q);
-        live[q] = skip == nullptr || skip[v[q] * skip_stride] == 0;
+        const int done = skip == nullptr ? 0 : skip[v[q] * skip_stride];
+        live[q] = dirn ? !ended_before(done, dir.stamp) : done == 0;
         any = any || live[q];
     }
     if (!any) return;  // uniform over the wavefronts of these fields
@@ -270,8 +273,6 @@ ax_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
     constexpr int CH = 4;
     T rn[AHEAD ? NQ : 1];
     double rr[AHEAD ? NQ : 1], dv[AHEAD ? NQ : 1];
-    bool dirn = false;
-    if constexpr (DOT) dirn = dir.sc != nullptr;
     auto load_column = [&](int64_t o) {
 #pragma unroll
         for (int k = 0; k < (AHEAD ? NQ : 1); ++k) rn[k] = u[v[0] * ldu + o + k * TPE];

@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "../../include/sem.h"
+#include "krylov_end.h"
 
 namespace semx {
 
@@ -103,7 +104,8 @@ struct KrylovScalars {
                     // the other slot is read by all blocks of the same kernel)
     double al2[2];  // alpha by iteration parity (coarse solve)
     int iters;
-    int done;       // 1 once converged or failed; later kernels become no-ops
+    int done;       // 0, or once converged or failed what ended it: 1 the start, else
+                    // the stamp of a launch (krylov_end.h); later kernels become no-ops
     int status;     // SEM_OK / SEM_EBREAKDOWN
     int maxit;
 };
@@ -120,6 +122,7 @@ struct PcgDir {
     const double *r = nullptr, *Dinv = nullptr;
     double *p = nullptr;
     int parity = 0, iter = 0;     // of the iteration the update belongs to (1-based)
+    int stamp = 0;                // of the operator launch
 };
 
 // One polynomial order of the discretisation on the handle's mesh.

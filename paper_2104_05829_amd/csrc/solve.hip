@@ -8,7 +8,7 @@
 // All vectors are replicated L-vectors; inner products over unique free nodes
 // are L-space sums weighted by the counting weight W (0 on Dirichlet copies).
 // The iteration scalars live on the device (KrylovScalars); kernels after
-// convergence see `done` and return, so batches of iterations are enqueued
+// convergence see `done` (krylov_end.h) and return, so batches of iterations are enqueued
 // without a host round trip per iteration.
 #include <algorithm>
 #include <chrono>
@@ -318,7 +318,7 @@ __global__ void fin_init_kernel(VSet vs, const double *partial, int64_t pst, int
 // (W r Dinv r, W r r).  rz2[parity] is the current (r, z).
 template <bool MC>
 __global__ void pcg_update_fused_kernel(int64_t n, VSet vs, int64_t ld, int64_t ldx,
-                                        KrylovScalars *sc, int parity,
+                                        KrylovScalars *sc, int parity, int stamp,
                                         const double *__restrict__ pax, int64_t pst_ax, int64_t nbax,
                                         const double *__restrict__ p, const double *__restrict__ w,
                                         const double *__restrict__ Dinv,
@@ -328,7 +328,7 @@ __global__ void pcg_update_fused_kernel(int64_t n, VSet vs, int64_t ld, int64_t 
 {
     const int64_t v = vsel(vs);
     sc += v;
-    if (sc->done) return;
+    if (ended_before(sc->done, stamp)) return;
     p += v * ld;
     w += v * ld;
     r += v * ld;
@@ -341,7 +341,7 @@ __global__ void pcg_update_fused_kernel(int64_t n, VSet vs, int64_t ld, int64_t 
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             sc->pw = pw;
             sc->status = SEM_EBREAKDOWN;
-            sc->done = 1;
+            sc->done = stamp;
         }
         return;
     }
@@ -371,7 +371,7 @@ __global__ void pcg_update_fused_kernel(int64_t n, VSet vs, int64_t ld, int64_t 
 template <int PPT>
 __global__ void __launch_bounds__(kRB)
 pcg_update_few_kernel(int64_t n, VSet vs, int64_t ld, int64_t ldx, KrylovScalars *sc, int parity,
-                      const double *__restrict__ pax, int64_t pst_ax, int64_t nbax,
+                      int stamp, const double *__restrict__ pax, int64_t pst_ax, int64_t nbax,
                       const double *__restrict__ p, const double *__restrict__ w,
                       const int32_t *__restrict__ nb8, const uint8_t *__restrict__ cnt8,
                       const double *__restrict__ Dinv, const double *__restrict__ W,
@@ -421,13 +421,13 @@ pcg_update_few_kernel(int64_t n, VSet vs, int64_t ld, int64_t ldx, KrylovScalars
     }
     double res[1];
     sum_partials<1>(pax + v * pst_ax, nbax, res);
-    if (done) return;
+    if (ended_before(done, stamp)) return;
     const double pw = res[0];
     if (!(pw > 0.0) || !isfinite(pw)) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             sc->pw = pw;
             sc->status = SEM_EBREAKDOWN;
-            sc->done = 1;
+            sc->done = stamp;
         }
         return;
     }
@@ -455,7 +455,7 @@ pcg_update_few_kernel(int64_t n, VSet vs, int64_t ld, int64_t ldx, KrylovScalars
 // partial (W r r)
 template <bool PAIR, bool MC>
 __global__ void fcg_update_fused_kernel(int64_t n, VSet vs, int64_t ld, int64_t ldx,
-                                        KrylovScalars *sc, int parity,
+                                        KrylovScalars *sc, int parity, int stamp,
                                         const double *__restrict__ pax, int64_t pst_ax, int64_t nbax,
                                         const double *__restrict__ p, const double *__restrict__ w,
                                         const double *__restrict__ W, const uint8_t *__restrict__ mc,
@@ -464,7 +464,7 @@ __global__ void fcg_update_fused_kernel(int64_t n, VSet vs, int64_t ld, int64_t 
 {
     const int64_t v = vsel(vs);
     sc += v;
-    if (sc->done) return;
+    if (ended_before(sc->done, stamp)) return;
     p += v * ld;
     w += v * ld;
     r += v * ld;
@@ -478,7 +478,7 @@ __global__ void fcg_update_fused_kernel(int64_t n, VSet vs, int64_t ld, int64_t 
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             sc->pw = pw;
             sc->status = SEM_EBREAKDOWN;
-            sc->done = 1;
+            sc->done = stamp;
         }
         return;
     }
@@ -553,13 +553,13 @@ __global__ void dot_zw_kernel(int64_t n, VSet vs, int64_t ld, const KrylovScalar
 // the FP32 V-cycle output, zero on Dirichlet copies (mask W32 > 0).
 template <bool PAIR, bool MC>
 __global__ void fcg_p_fused_kernel(int64_t n, VSet vs, int64_t ld, KrylovScalars *sc, int parity,
-                                   const double *__restrict__ pz, int64_t pst, int64_t nbz,
+                                   int stamp, const double *__restrict__ pz, int64_t pst, int64_t nbz,
                                    const float *__restrict__ z, const float *__restrict__ W32,
                                    const uint8_t *__restrict__ mc, double *__restrict__ p, int first)
 {
     const int64_t v = vsel(vs);
     sc += v;
-    if (sc->done) return;
+    if (ended_before(sc->done, stamp)) return;
     z += v * ld;
     p += v * ld;
     double res[2];
@@ -574,7 +574,7 @@ __global__ void fcg_p_fused_kernel(int64_t n, VSet vs, int64_t ld, KrylovScalars
         sc->rz2[parity ^ 1] = zr;
         if (bad) {
             sc->status = SEM_EBREAKDOWN;
-            sc->done = 1;
+            sc->done = stamp;
         }
     }
     if (bad) return;
@@ -732,11 +732,11 @@ __global__ void wresid_fused_kernel(int64_t n, VSet vs, int64_t ld, const float 
 // flexible CG convergence decision after the update (one block per vector):
 // iteration count, (r, r)_W, done
 __global__ void fin_conv_kernel(VSet vs, const double *partial, int64_t pst, int64_t nb,
-                                KrylovScalars *sc)
+                                KrylovScalars *sc, int stamp)
 {
     const int64_t v = vsel(vs);
     sc += v;
-    if (sc->done) return;
+    if (ended_before(sc->done, stamp)) return;
     double res[1];
     sum_partials<1>(partial + v * pst, nb, res);
     if (threadIdx.x == 0) {
@@ -744,9 +744,9 @@ __global__ void fin_conv_kernel(VSet vs, const double *partial, int64_t pst, int
         sc->rr = res[0];
         if (!isfinite(res[0])) {
             sc->status = SEM_EBREAKDOWN;
-            sc->done = 1;
+            sc->done = stamp;
         } else if (res[0] <= sc->tol2 || sc->iters >= sc->maxit) {
-            sc->done = 1;
+            sc->done = stamp;
         }
     }
 }
@@ -1353,12 +1353,12 @@ static PcgBufs ws_bufs(sem_handle h, const Level &L)
 
 // Convergence decision after the last update of a batch of iterations (one
 // block per vector), for the host; the next operator takes it again by itself.
-__global__ void pcg_decide_kernel(VSet vs, KrylovScalars *sc, int iter, const double *__restrict__ pu,
-                                  int64_t pst, int64_t nbu)
+__global__ void pcg_decide_kernel(VSet vs, KrylovScalars *sc, int iter, int stamp,
+                                  const double *__restrict__ pu, int64_t pst, int64_t nbu)
 {
     const int64_t v = vsel(vs);
     sc += v;
-    if (sc->done) return;
+    if (ended_before(sc->done, stamp)) return;
     double res[2];
     sum_partials<2>(pu + v * pst, nbu, res);
     if (threadIdx.x == 0) {
@@ -1367,7 +1367,7 @@ __global__ void pcg_decide_kernel(VSet vs, KrylovScalars *sc, int iter, const do
         sc->rr = res[1];
         sc->rz = res[0];
         if (bad) sc->status = SEM_EBREAKDOWN;
-        if (bad || res[1] <= sc->tol2 || iter >= sc->maxit) sc->done = 1;
+        if (bad || res[1] <= sc->tol2 || iter >= sc->maxit) sc->done = stamp;
     }
 }
 
@@ -1403,6 +1403,7 @@ static int pcg_iterations(sem_handle h, const Level &L, const VSet &vs, const do
             dir.p = kv.p;
             dir.parity = parity ^ 1;
             dir.iter = it - 1;
+            dir.stamp = end_stamp(it, kEndOperator);
         }
         SEM_TRY(launch_ax_multi<double>(L, L.G, L.B, L.D, kv.p, n, kv.w, n, vs, h1, h2, k,
                                         pb.partial_ax, pb.pst_ax, &nbax, s, skip, kScStride, dir));
@@ -1414,20 +1415,24 @@ static int pcg_iterations(sem_handle h, const Level &L, const VSet &vs, const do
         }
         if (few) {
             auto kern = ppt == 2 ? pcg_update_few_kernel<2> : pcg_update_few_kernel<1>;
-            hipLaunchKernelGGL(kern, dim3((unsigned)nbv, (unsigned)vs.n), dim3(kRB), 0, s, n, vs, n, kv.ldx, kv.sc, parity, (const double *)pb.partial_ax, pb.pst_ax, nbax,
-                               (const double *)kv.p, (const double *)kv.w, (const int32_t *)L.nb8,
-                               apart ? (const uint8_t *)nullptr : L.cnt8, pb.Dinv, L.W, kv.x, kv.r, pb.partial, pb.pst);
+            hipLaunchKernelGGL(kern, dim3((unsigned)nbv, (unsigned)vs.n), dim3(kRB), 0, s, n, vs, n, kv.ldx,
+                               kv.sc, parity, end_stamp(it, kEndUpdate), (const double *)pb.partial_ax,
+                               pb.pst_ax, nbax, (const double *)kv.p, (const double *)kv.w,
+                               (const int32_t *)L.nb8, apart ? (const uint8_t *)nullptr : L.cnt8, pb.Dinv,
+                               L.W, kv.x, kv.r, pb.partial, pb.pst);
             SEM_HIP(hipGetLastError());
         } else {
             auto kern = L.mc ? pcg_update_fused_kernel<true> : pcg_update_fused_kernel<false>;
-            LAUNCH_B(kern, n, vs, s, n, vs, n, kv.ldx, kv.sc, parity, (const double *)pb.partial_ax,
-                     pb.pst_ax, nbax, (const double *)kv.p, (const double *)kv.w, pb.Dinv, L.W,
-                     (const uint8_t *)L.mc, kv.x, kv.r, pb.partial, pb.pst);
+            LAUNCH_B(kern, n, vs, s, n, vs, n, kv.ldx, kv.sc, parity, end_stamp(it, kEndUpdate),
+                     (const double *)pb.partial_ax, pb.pst_ax, nbax, (const double *)kv.p,
+                     (const double *)kv.w, pb.Dinv, L.W, (const uint8_t *)L.mc, kv.x, kv.r, pb.partial,
+                     pb.pst);
         }
         if (timed) SEM_TRY(clock_mark(ws, kPhaseVec, s));
     }
-    LAUNCH_1B(pcg_decide_kernel, vs, s, vs, kv.sc, first_iter + iters - 1, (const double *)pb.partial,
-              pb.pst, (int64_t)nbv);
+    const int last = first_iter + iters - 1;
+    LAUNCH_1B(pcg_decide_kernel, vs, s, vs, kv.sc, last, end_stamp(last, kEndDecide),
+              (const double *)pb.partial, pb.pst, (int64_t)nbv);
     return SEM_OK;
 }
 
@@ -1571,15 +1576,15 @@ __global__ void csr_spmv_dots_kernel(int64_t nf, VSet vs, int64_t ld, const int3
 // beta and alpha, then p = u + beta p, s = w + beta s (s = A p), x += alpha p,
 // r -= alpha s, u = Dinv r.  Every block sums the partials in the same order;
 // block 0 notes the scalars in the slots of this parity, all read the other's.
-__global__ void coarse_step_kernel(int64_t nf, VSet vs, int64_t ld, KrylovScalars *sc, int it, double tol,
-                                   const double *__restrict__ partial, int64_t pst, int64_t nb,
+__global__ void coarse_step_kernel(int64_t nf, VSet vs, int64_t ld, KrylovScalars *sc, int it, int stamp,
+                                   double tol, const double *__restrict__ partial, int64_t pst, int64_t nb,
                                    const double *__restrict__ Dinv, const double *__restrict__ w,
                                    double *__restrict__ u, double *__restrict__ p, double *__restrict__ s,
                                    double *__restrict__ x, double *__restrict__ r)
 {
     const int64_t v = vsel(vs);
     sc += v;
-    if (sc->done) return;
+    if (ended_before(sc->done, stamp)) return;
     const int par = it & 1;
     const bool first = it == 1;
     const double g_old = sc->rz2[par ^ 1], al_old = sc->al2[par ^ 1], tol2_old = sc->tol2;
@@ -1597,7 +1602,7 @@ __global__ void coarse_step_kernel(int64_t nf, VSet vs, int64_t ld, KrylovScalar
         sc->rr = rr;
         if (brk) sc->status = SEM_EBREAKDOWN;
         if (stop || brk) {
-            sc->done = 1;
+            sc->done = stamp;
         } else {
             sc->iters = it;
             sc->tol2 = tol2;
@@ -1749,9 +1754,10 @@ static int coarse_csr_solve(sem_handle h, const Level &L, const VSet &vs, double
                            (const int32_t *)L.cs_col, (const double *)L.cs_val, (const double *)cu,
                            (const double *)w.c_r, w.c_w, w.partial, w.pst, (const KrylovScalars *)w.sc_c);
         SEM_HIP(hipGetLastError());
-        hipLaunchKernelGGL(coarse_step_kernel, gv, dim3(kRB), 0, s, nf, vs, nf, w.sc_c, it, cfg.coarse_tol,
-                           (const double *)w.partial, w.pst, (int64_t)nbax, (const double *)L.cs_dinv,
-                           (const double *)w.c_w, cu, w.c_p, cs, L.cs_xu, w.c_r);
+        hipLaunchKernelGGL(coarse_step_kernel, gv, dim3(kRB), 0, s, nf, vs, nf, w.sc_c, it,
+                           end_stamp(it, kEndUpdate), cfg.coarse_tol, (const double *)w.partial, w.pst,
+                           (int64_t)nbax, (const double *)L.cs_dinv, (const double *)w.c_w, cu, w.c_p, cs,
+                           L.cs_xu, w.c_r);
         SEM_HIP(hipGetLastError());
     }
     LAUNCH_B(csr_scatter_kernel, n, vs, s, n, vs, (const int32_t *)L.cs_uid, (const double *)L.cs_xu, nf, x, n);
@@ -2343,7 +2349,7 @@ int pcg_solve(sem_handle h, int nv, const double *b, double *x, int64_t ld, cons
             LAUNCH_B(dots, n, act, s, n, act, n, (const KrylovScalars *)w.sc, F.W, fmc,
                      (const float *)z32, (const double *)w.r, (const double *)w.r, w.partial,
                      w.pst);
-            LAUNCH_B(direct, n, act, s, n, act, n, w.sc, 1,
+            LAUNCH_B(direct, n, act, s, n, act, n, w.sc, 1, end_stamp(0, kEndDirection),
                         (const double *)w.partial, w.pst, (int64_t)nbv, (const float *)z32, F.W32,
                         fmc, w.p, 1);
             SEM_TRY(clock_mark(w, kPhaseVec, s));
@@ -2358,11 +2364,11 @@ int pcg_solve(sem_handle h, int nv, const double *b, double *x, int64_t ld, cons
             SEM_TRY(clock_mark(w, kPhaseAx, s));
             SEM_TRY(launch_gs_multi<double>(F, w.w, n, act, s, skip, kScStride));
             SEM_TRY(clock_mark(w, kPhaseGs, s));
-            LAUNCH_B(update, n, act, s, n, act, n, ld, w.sc, parity,
+            LAUNCH_B(update, n, act, s, n, act, n, ld, w.sc, parity, end_stamp(it + 1, kEndUpdate),
                         (const double *)w.partial_ax, w.pst_ax, nbax, (const double *)w.p,
                         (const double *)w.w, F.W, fmc, x, w.r, r32, w.partial, w.pst);
             LAUNCH_1B(fin_conv_kernel, act, s, act, (const double *)w.partial, w.pst, (int64_t)nbv,
-                      w.sc);
+                      w.sc, end_stamp(it + 1, kEndDecide));
             SEM_TRY(clock_mark(w, kPhaseVec, s));
             // one host synchronisation per iteration: outer scalars, and the
             // coarse-solve counts of the V-cycle that preceded this update
@@ -2377,7 +2383,7 @@ int pcg_solve(sem_handle h, int nv, const double *b, double *x, int64_t ld, cons
             LAUNCH_B(dots, n, act, s, n, act, n, (const KrylovScalars *)w.sc, F.W, fmc,
                      (const float *)z32, (const double *)w.w, (const double *)w.r, w.partial,
                      w.pst);
-            LAUNCH_B(direct, n, act, s, n, act, n, w.sc, parity,
+            LAUNCH_B(direct, n, act, s, n, act, n, w.sc, parity, end_stamp(it + 1, kEndDirection),
                         (const double *)w.partial, w.pst, (int64_t)nbv, (const float *)z32, F.W32,
                         fmc, w.p, 0);
             SEM_TRY(clock_mark(w, kPhaseVec, s));
