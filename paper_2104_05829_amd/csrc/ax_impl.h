@@ -439,7 +439,7 @@ ax_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
 template <int NQ>
 struct AxSplitShape {
     static constexpr int TPE = NQ * NQ, NP = TPE * NQ;
-    static constexpr int KS = NP <= 1024 ? NQ : (NQ == 11 ? 8 : NQ == 12 ? 6 : NQ <= 14 ? 5 : 4);
+    static constexpr int KS = NP <= 1024 ? NQ : (NQ == 11 ? 8 : 6);
     static constexpr int KPT = (NQ + KS - 1) / KS;             // points per thread
     static constexpr int EPB = NP <= 128 ? 256 / NP : 1;       // elements per block
     static constexpr int THREADS = EPB * TPE * KS;
@@ -624,7 +624,7 @@ inline bool ax_spread(const Level &L, int nf, bool dot)
     const int64_t points = L.nL, blocks = points / (AxSplitShape<NQ>::EPB * AxSplitShape<NQ>::NP) + 1;
     // the buffer of partial sums is sized by the CUs
     if (dot && blocks > (int64_t)(L.n_cu > 0 ? L.n_cu : 256) * kAxMaxBlocksPerCU) return false;
-    return NQ <= 12 && (dot ? points <= (1 << 17) : points * nf <= (1 << 18));
+    return dot ? points <= (1 << 17) : points * nf <= (1 << 18);
 }
 
 // the compiled forms: mass term, coefficient (one field), partial sums (FP64)
@@ -703,9 +703,10 @@ static int ax_dispatch(const Level &L, const T *G, const T *B, const T *D, const
                        double *partial, int64_t pst, int64_t *nblocks, hipStream_t s, const int *skip,
                        int skip_stride, const PcgDir &dir)
 {
-    if (ax_spread<NQ>(L, vs.n, partial != nullptr))
-        return ax_split_launch<NQ, T>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, k, partial, pst, nblocks, s,
-                                      skip, skip_stride, dir);
+    if constexpr (NQ <= 12)
+        if (ax_spread<NQ>(L, vs.n, partial != nullptr))
+            return ax_split_launch<NQ, T>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, k, partial, pst, nblocks, s,
+                                          skip, skip_stride, dir);
 #define SEM_AX_NF(NW, NI)                                                                      \
     return ax_launch<NQ, T, NW, NI>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, k, partial, pst,  \
                                     nblocks, s, skip, skip_stride, dir)
