@@ -19,7 +19,7 @@
 // coefficients of the plane) then lives in SGPRs for one plane, where holding
 // all (N+1)^2 spilled them.  The next plane's G (and B, k) is loaded while the
 // current one is computed, across elements too; the grid is persistent.
-// D^T comes from the rows of D: GLL quadrature sums the product of two degree-N
+// Where registers are short D^T comes from the rows of D: GLL quadrature sums the product of two degree-N
 // derivatives exactly, so rho_i D[i][l] + rho_l D[l][i] is 0 but at the end
 // points (-1 for i = l = 0, +1 for i = l = N), and
 //   sum_l D[l][i] f_l = -rho_i sum_l D[i][l] (f_l / rho_l)  +- f_i / rho_i at the ends.
@@ -56,6 +56,46 @@ constexpr int ax_min_waves()
 {
     if (sizeof(T) == 4 || NQ <= 10) return 1;
     return NQ <= 13 ? 3 : 2;
+}
+
+// Waves per SIMD the compiler may aim at.  FP64 Poisson at N = 6 fits four if
+// every load waits for its use (0.45 M points 7.7 us; with three 7.2).
+template <int NQ, typename T, bool HELM>
+constexpr int ax_max_waves()
+{
+    return sizeof(T) == 8 && NQ == 7 && !HELM ? 3 : 8;
+}
+
+// Whether D^T has register rows of its own or is formed from the rows of D.  Own
+// rows round least: against FP64, FP32 rms error over N = 2 .. 8 5.0e-8 .. 7.4e-8
+// with them, 5.4e-8 .. 8.5e-8 without (from the rows of D N = 5 lost most, 6.5e-8
+// against 8.4e-8; a sum that runs on through all three directions 8.1e-8).  FP32
+// has the registers for it up to N = 7; beyond, two rows are the faster form
+// (0.96 M points: N = 8 9.1 / 9.4 us, N = 10 8.5 / 10.4) at 7.6e-8 to 1.2e-7, below
+// the 1.0e-7 to 1.5e-7 of the running sum.  FP64: up to N = 3 (64000 elements
+// 39.7 -> 38.2 us).
+template <int NQ, typename T>
+constexpr bool ax_dt_rows()
+{
+    return NQ <= (sizeof(T) == 4 ? 8 : 4);
+}
+
+// Points up to which a single field is computed in two phases, all planes
+// forward, then all planes back, instead of plane by plane: one chain of LDS
+// accesses an element in place of N + 1, and every factor of it on its way at
+// once, at the price of a second full plane set in LDS and registers.  us, by
+// planes / in two phases: FP32 N = 2, 0.29 M points 3.6 / 3.0, 7 M 54.8 / 50.8; N = 3,
+// 0.11 M 2.8 / 2.6, 0.88 M 4.6 / 4.5, 2.5 M 12.9 / 14.3; N = 5, 0.29 M 4.4 / 3.9, 0.88 M
+// 6.9 / 6.4, 2.6 M 16.4 / 17.3 over and over on one mesh and 30.3 / 28.9 with QQ^T on
+// three meshes in turn, 3.8 M 26.0 / 24.2, 7 M 51.7 / 53.1; N = 6, 0.45 M 4.9 / 4.6,
+// 0.94 M 8.1 / 8.8; N = 7, 0.88 M 6.0 / 6.6.  FP64 N = 1 and 2: 0.09 M 3.7 / 3.2, 0.88 M
+// 12.0 / 11.9, 4 M with the mass term 48.0 / 44.4; N = 3, 0.88 M 10.4 / 10.9.
+template <int NQ, typename T>
+constexpr int64_t ax_two_phase_points()
+{
+    if (NQ <= 3) return INT64_MAX;
+    if (sizeof(T) == 8) return 0;
+    return NQ <= 5 ? 1200000 : NQ == 6 ? 4500000 : NQ == 7 ? 600000 : 0;
 }
 
 template <bool ONE_WAVE>
@@ -173,24 +213,45 @@ __device__ inline bool pcg_direction(const PcgDir &d, int64_t v, int tid, bool r
     return !stop;
 }
 
-// One element column's constants: its rows of D and the end-point terms of D^T.
+// One element column's constants: its rows of D, and its rows of D^T or what
+// forms them from those of D.
 template <int NQ, typename T>
 struct AxCol {
+    static constexpr bool DT = ax_dt_rows<NQ, T>();
     T Di[NQ], Dj[NQ];
-    T rhoi, rhoj, ri, rj, bi, bj;  // weights, their inverses, end-point terms
-    __device__ inline AxCol(const T *__restrict__ Dg, int i, int j)
+    T Ti[DT ? NQ : 1], Tj[DT ? NQ : 1];  // rows of D^T
+    T rhoi, rhoj, ri, rj, bi, bj;        // weights, their inverses, end-point terms
+    // D with rows of ld, the weights rho
+    __device__ inline AxCol(const T *D, int ld, const T *rho, int i, int j)
     {
 #pragma unroll
         for (int l = 0; l < NQ; ++l) {
-            Di[l] = Dg[i * NQ + l];
-            Dj[l] = Dg[j * NQ + l];
+            Di[l] = D[i * ld + l];
+            Dj[l] = D[j * ld + l];
+            if constexpr (DT) {
+                Ti[l] = D[l * ld + i];
+                Tj[l] = D[l * ld + j];
+            }
         }
-        rhoi = Dg[NQ * NQ + i];  // the weights follow D in its buffer
-        rhoj = Dg[NQ * NQ + j];
+        rhoi = rho[i];
+        rhoj = rho[j];
         ri = T(1) / rhoi;
         rj = T(1) / rhoj;
         bi = i == 0 ? -ri : (i == NQ - 1 ? ri : T(0));
         bj = j == 0 ? -rj : (j == NQ - 1 ? rj : T(0));
+    }
+    // a flux as it is left for the others, and the rows that contract it
+    __device__ inline T out_r(T wr) const { return DT ? wr : wr * ri; }
+    __device__ inline T out_s(T ws) const { return DT ? ws : ws * rj; }
+    __device__ inline T back_r(int l) const
+    {
+        if constexpr (DT) return Ti[l];
+        else return Di[l];
+    }
+    __device__ inline T back_s(int l) const
+    {
+        if constexpr (DT) return Tj[l];
+        else return Dj[l];
     }
 };
 
@@ -203,24 +264,28 @@ __device__ inline void ax_flux(const T (&g)[6], T ur, T us, T ut, T &wr, T &ws, 
     wt = g[2] * ur + g[4] * us + g[5] * ut;
 }
 
-// the r and s parts of a point's result (ar, as: the rows of D over the scaled
-// fluxes) with the mass term
+// the r and s parts of a point's result (ar, as: the back rows over the fluxes
+// left) with the mass term
 template <int NQ, typename T, bool HELM>
 __device__ inline T ax_rs_part(const AxCol<NQ, T> &C, T wr, T ws, T ar, T as, T h1, T h2, T b, T u)
 {
-    T acc = (C.bi * wr - C.rhoi * ar) + (C.bj * ws - C.rhoj * as);
+    T acc;
+    if constexpr (AxCol<NQ, T>::DT) acc = ar + as;
+    else acc = (C.bi * wr - C.rhoi * ar) + (C.bj * ws - C.rhoj * as);
     acc *= h1;
     if constexpr (HELM) acc += h2 * b * u;
     return acc;
 }
 
 // A wavefront (or, for N > 7, a workgroup) computes NI fields of its element
-// plane by plane, and a workgroup holds NW wavefronts with fields of their own.
+// plane by plane, or (TWO) all planes forward, then all planes back, and a
+// workgroup holds NW wavefronts with fields of their own.
 // nvb: number of partial sums of u.w; record vb covers the element groups vb,
 // vb + nvb, ...  With several fields fewer workgroups than nvb may run, each
 // taking records in turn, so a field's records are those of a single-field call.
-template <int NQ, typename T, bool HELM, bool VARK, bool DOT, int NW, int NI>
-__global__ void __launch_bounds__((AxShape<NQ>::threads(NW)), (ax_min_waves<NQ, T>()))
+template <int NQ, typename T, bool HELM, bool VARK, bool DOT, int NW, int NI, bool TWO>
+__global__ void __launch_bounds__((AxShape<NQ>::threads(NW)))
+__attribute__((amdgpu_waves_per_eu(ax_min_waves<NQ, T>(), ax_max_waves<NQ, T, HELM>())))
 ax_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
           const T *__restrict__ kc, const T *__restrict__ Dg, T h1, T h2,
           const T *u, int64_t ldu, T *__restrict__ w, int64_t ldw, VSet vs,
@@ -231,8 +296,11 @@ ax_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
     constexpr int TPE = S::TPE, EPB = S::EPB, LD = S::LD;
     constexpr int NP = NQ * NQ * NQ;
     __shared__ T su[NW][NI][EPB][NQ][NQ][LD];
-    __shared__ T sr[NW][2][NI][EPB][NQ][LD];
-    __shared__ T ss[NW][2][NI][EPB][NQ][LD];
+    static_assert(!TWO || (S::ONE_WAVE && ax_dt_rows<NQ, T>()), "two phases: one wavefront, rows of D^T");
+    // flux planes: two buffers of one each way, or of all planes the s flux (the r
+    // flux takes u's place, which the wavefront has read by then)
+    __shared__ T sr[NW][TWO ? 1 : 2][NI][EPB][TWO ? 1 : NQ][LD];
+    __shared__ T ss[NW][TWO ? NQ : 2][NI][EPB][NQ][LD];
 
     // the wavefront's slot (NW > 1: 64 lanes each), lane in it
     const int fs = NW == 1 ? 0 : (int)threadIdx.x >> 6;
@@ -254,11 +322,11 @@ ax_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
     const int ij = (EPB == 1) ? tid : tid - el * TPE;
     const int i = ij % NQ;
     const int j = ij / NQ;
-    const AxCol<NQ, T> C(Dg, i, j);
+    const AxCol<NQ, T> C(Dg, NQ, Dg + NQ * NQ, i, j);  // the weights follow D in its buffer
 
     const int64_t groups = (E + EPB - 1) / EPB;
     T gn[6], bn = T(0), kn = T(0);
-    {
+    if constexpr (!TWO) {
         const int64_t e0 = (int64_t)blockIdx.x * EPB + el;
         const int64_t b0 = (e0 < E ? e0 : 0) * NP + ij;
         load_g6(G + b0 * 6, gn);
@@ -269,7 +337,8 @@ ax_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
     // allow they are loaded ahead of their element, the first ahead of the sums
     // that give beta (512 elements, N = 7: 10.6 -> 9.5 us); else a few planes at a
     // time, since all three lines in flight would spill.
-    constexpr bool AHEAD = DOT && NQ <= 8 && NI == 1;
+    // In two phases the FP32 column is too (N = 5, 2.6 M points 29.8 -> 28.9).
+    constexpr bool AHEAD = (DOT || (TWO && sizeof(T) == 4)) && NQ <= 8 && NI == 1;
     constexpr int CH = 4;
     T rn[AHEAD ? NQ : 1];
     double rr[AHEAD ? NQ : 1], dv[AHEAD ? NQ : 1];
@@ -354,68 +423,122 @@ ax_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
                     su[fs][q][el][k][j][i] = ru[q][k];
                     rw[q][k] = T(0);
                 }
+            // two phases: every factor of the element is on its way before the
+            // lanes meet (left behind, the loads are put off to save registers)
+            T ga[TWO ? NQ : 1][6], ba[TWO ? NQ : 1], ca[TWO ? NQ : 1];
+            if constexpr (TWO)
+#pragma unroll
+                for (int k = 0; k < NQ; ++k) {
+                    load_g6(G + (base + k * TPE) * 6, ga[k]);
+                    ba[k] = ca[k] = T(0);
+                    if constexpr (HELM) ba[k] = B[base + k * TPE];
+                    if constexpr (VARK) ca[k] = kc[base + k * TPE];
+                }
             // wavefronts with fields of their own meet once per element, which
             // keeps the factors that one of them fetched in L1 for the others
             block_sync<S::ONE_WAVE && NW == 1>();
 
-#pragma unroll 1
-            for (int k = 0; k < NQ; ++k) {
-                T gg[6];
-                const T bb = bn, c = kn;
-#pragma unroll
-                for (int q = 0; q < 6; ++q) gg[q] = gn[q];
-                {  // the next plane's factors, loaded while this one is computed
-                    const int64_t nx = k + 1 < NQ ? base + (k + 1) * TPE : nbase;
-                    load_g6(G + nx * 6, gn);
-                    if constexpr (HELM) bn = B[nx];
-                    if constexpr (VARK) kn = kc[nx];
-                }
-                if constexpr (VARK)
-#pragma unroll
-                    for (int q = 0; q < 6; ++q) gg[q] *= c;
-                const T *dk = Dg + k * NQ;
-                T wr[NI], ws[NI], uk[NI];
-#pragma unroll
-                for (int q = 0; q < NI; ++q) {
-                    T ur = 0, us = 0, ut = 0, wt;
-#pragma unroll
-                    for (int l = 0; l < NQ; ++l) {
-                        ur += C.Di[l] * su[fs][q][el][k][j][l];
-                        us += C.Dj[l] * su[fs][q][el][k][l][i];
-                        ut += dk[l] * ru[q][l];
-                    }
-                    ax_flux(gg, ur, us, ut, wr[q], ws[q], wt);
-                    sr[fs][k & 1][q][el][j][i] = wr[q] * C.ri;
-                    ss[fs][k & 1][q][el][j][i] = ws[q] * C.rj;
-                    uk[q] = su[fs][q][el][k][j][i];
-#pragma unroll
-                    for (int m = 0; m < NQ; ++m) rw[q][m] += dk[m] * wt;
-                }
-                // past this barrier plane k of u has been read by every thread;
-                // the other pair of flux planes is written before the next one
-                block_sync<S::ONE_WAVE>();
-#pragma unroll
-                for (int q = 0; q < NI; ++q) {
-                    T ar = 0, as = 0;
-#pragma unroll
-                    for (int l = 0; l < NQ; ++l) {
-                        ar += C.Di[l] * sr[fs][k & 1][q][el][j][l];
-                        as += C.Dj[l] * ss[fs][k & 1][q][el][l][i];
-                    }
-                    // read again by this thread only
-                    su[fs][q][el][k][j][i] =
-                        ax_rs_part<NQ, T, HELM>(C, wr[q], ws[q], ar, as, h1, h2, bb, uk[q]);
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < NI; ++q)
+            if constexpr (TWO) {
 #pragma unroll
                 for (int k = 0; k < NQ; ++k) {
-                    const T out = su[fs][q][el][k][j][i] + h1 * rw[q][k];
-                    if (active && (NI == 1 || live[q])) w[v[q] * ldw + base + k * TPE] = out;
-                    if constexpr (DOT)
-                        if (active) dot[q] += (double)ru[q][k] * (double)out;
+                    T gg[6];
+#pragma unroll
+                    for (int q = 0; q < 6; ++q) gg[q] = VARK ? ga[k][q] * ca[k] : ga[k][q];
+                    const T *dk = Dg + k * NQ;
+#pragma unroll
+                    for (int q = 0; q < NI; ++q) {
+                        T ur = 0, us = 0, ut = 0, wr, ws, wt;
+#pragma unroll
+                        for (int l = 0; l < NQ; ++l) {
+                            ur += C.Di[l] * su[fs][q][el][k][j][l];
+                            us += C.Dj[l] * su[fs][q][el][k][l][i];
+                            ut += dk[l] * ru[q][l];
+                        }
+                        ax_flux(gg, ur, us, ut, wr, ws, wt);
+                        su[fs][q][el][k][j][i] = wr;  // plane k of u has been read
+                        ss[fs][k][q][el][j][i] = ws;
+#pragma unroll
+                        for (int m = 0; m < NQ; ++m) rw[q][m] += dk[m] * wt;
+                    }
                 }
+                block_sync<S::ONE_WAVE>();
+#pragma unroll
+                for (int k = 0; k < NQ; ++k)
+#pragma unroll
+                    for (int q = 0; q < NI; ++q) {
+                        T ar = 0, as = 0;
+#pragma unroll
+                        for (int l = 0; l < NQ; ++l) {
+                            ar += C.back_r(l) * su[fs][q][el][k][j][l];
+                            as += C.back_s(l) * ss[fs][k][q][el][l][i];
+                        }
+                        const T out = ax_rs_part<NQ, T, HELM>(C, T(0), T(0), ar, as, h1, h2, ba[k],
+                                                              ru[q][k]) + h1 * rw[q][k];
+                        if (active && (NI == 1 || live[q])) w[v[q] * ldw + base + k * TPE] = out;
+                        if constexpr (DOT)
+                            if (active) dot[q] += (double)ru[q][k] * (double)out;
+                    }
+                block_sync<S::ONE_WAVE>();  // the next element's u takes their place
+            } else {
+#pragma unroll 1
+                for (int k = 0; k < NQ; ++k) {
+                    T gg[6];
+                    const T bb = bn, c = kn;
+#pragma unroll
+                    for (int q = 0; q < 6; ++q) gg[q] = gn[q];
+                    {  // the next plane's factors, loaded while this one is computed
+                        const int64_t nx = k + 1 < NQ ? base + (k + 1) * TPE : nbase;
+                        load_g6(G + nx * 6, gn);
+                        if constexpr (HELM) bn = B[nx];
+                        if constexpr (VARK) kn = kc[nx];
+                    }
+                    if constexpr (VARK)
+#pragma unroll
+                        for (int q = 0; q < 6; ++q) gg[q] *= c;
+                    const T *dk = Dg + k * NQ;
+                    T wr[NI], ws[NI], uk[NI];
+#pragma unroll
+                    for (int q = 0; q < NI; ++q) {
+                        T ur = 0, us = 0, ut = 0, wt;
+#pragma unroll
+                        for (int l = 0; l < NQ; ++l) {
+                            ur += C.Di[l] * su[fs][q][el][k][j][l];
+                            us += C.Dj[l] * su[fs][q][el][k][l][i];
+                            ut += dk[l] * ru[q][l];
+                        }
+                        ax_flux(gg, ur, us, ut, wr[q], ws[q], wt);
+                        sr[fs][k & 1][q][el][j][i] = C.out_r(wr[q]);
+                        ss[fs][k & 1][q][el][j][i] = C.out_s(ws[q]);
+                        uk[q] = su[fs][q][el][k][j][i];
+#pragma unroll
+                        for (int m = 0; m < NQ; ++m) rw[q][m] += dk[m] * wt;
+                    }
+                    // past this barrier plane k of u has been read by every thread;
+                    // the other pair of flux planes is written before the next one
+                    block_sync<S::ONE_WAVE>();
+#pragma unroll
+                    for (int q = 0; q < NI; ++q) {
+                        T ar = 0, as = 0;
+#pragma unroll
+                        for (int l = 0; l < NQ; ++l) {
+                            ar += C.back_r(l) * sr[fs][k & 1][q][el][j][l];
+                            as += C.back_s(l) * ss[fs][k & 1][q][el][l][i];
+                        }
+                        // read again by this thread only
+                        su[fs][q][el][k][j][i] =
+                            ax_rs_part<NQ, T, HELM>(C, wr[q], ws[q], ar, as, h1, h2, bb, uk[q]);
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < NI; ++q)
+#pragma unroll
+                    for (int k = 0; k < NQ; ++k) {
+                        const T out = su[fs][q][el][k][j][i] + h1 * rw[q][k];
+                        if (active && (NI == 1 || live[q])) w[v[q] * ldw + base + k * TPE] = out;
+                        if constexpr (DOT)
+                            if (active) dot[q] += (double)ru[q][k] * (double)out;
+                    }
+            }
             if constexpr (AHEAD)
                 if (gx < groups) load_column(nbase);
         }
@@ -473,7 +596,6 @@ ax_split_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
     const int64_t e = (int64_t)blockIdx.x * EPB + el;
     const bool active = e < E;
     const int64_t base = (active ? e : 0) * NP + ij;
-    const AxCol<NQ, T> C(Dg, i, j);
     T uu[KPT], g[KPT][6], bb[HELM ? KPT : 1], cc[VARK ? KPT : 1], wr[KPT], ws[KPT];
     double rr[DOT ? KPT : 1], dv[DOT ? KPT : 1];
     bb[0] = cc[0] = T(0);
@@ -514,6 +636,7 @@ ax_split_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
         if (k < NQ) su[el][k][j][i] = uu[p];
     }
     block_sync<(S::THREADS <= 64)>();
+    const AxCol<NQ, T> C(&sD[0][0], NQ + 1, Dg + NQ * NQ, i, j);
 #pragma unroll
     for (int p = 0; p < KPT; ++p) {
         const int k = kg + p * KS;
@@ -530,8 +653,8 @@ ax_split_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
 #pragma unroll
                 for (int q = 0; q < 6; ++q) g[p][q] *= cc[p];
             ax_flux(g[p], ur, us, ut, wr[p], ws[p], wt);
-            sr[el][k][j][i] = wr[p] * C.ri;
-            ss[el][k][j][i] = ws[p] * C.rj;
+            sr[el][k][j][i] = C.out_r(wr[p]);
+            ss[el][k][j][i] = C.out_s(ws[p]);
             st[el][k][j][i] = wt;
         }
     }
@@ -544,8 +667,8 @@ ax_split_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
             T ar = 0, as = 0, at = 0;
 #pragma unroll
             for (int l = 0; l < NQ; ++l) {
-                ar += C.Di[l] * sr[el][k][j][l];
-                as += C.Dj[l] * ss[el][k][l][i];
+                ar += C.back_r(l) * sr[el][k][j][l];
+                as += C.back_s(l) * ss[el][k][l][i];
                 at += sD[l][k] * st[el][l][j][i];
             }
             const T out = ax_rs_part<NQ, T, HELM>(C, wr[p], ws[p], ar, as, h1, h2, bb[HELM ? p : 0],
@@ -564,35 +687,41 @@ ax_split_kernel(int64_t E, const T *__restrict__ G, const T *__restrict__ B,
 }
 
 // Several fields of elements of one wavefront (N <= 7): with `inside`, one
-// wavefront computes all of them plane by plane, the factors in registers; else
+// wavefront computes all of them, the factors in registers; else
 // each has a wavefront of its own and the factors come from the caches for the
 // others, more wavefronts but G read once per field from L1 / L2.  Operator and
 // QQ^T together, us, the per-field loop of before / inside / a wavefront each:
 // three FP64 fields at N = 7, 16^3 elements 75 / 71 / 64, 32^3 574 / 564 / 572,
 // N = 5, 30^3 274 / 241 / 270; FP32 16^3 43 / 40 / 39, 32^3 331 / 326 / 344.  Four
-// FP64 fields inside leave one wave per SIMD (24^3: 327 / 353 / 311).  The line
-// lies where the FP64 factors fill half the Infinity Cache.
-template <typename T>
+// FP64 fields inside leave one wave per SIMD (N = 7, 24^3: 327 / 353 / 311) but at
+// N <= 4 (N = 4, 3 M points: inside / a wavefront each 148 / 168).  The line
+// lies where the FP64 factors fill half the Infinity Cache, and at N = 1 and 2,
+// whose registers hold a whole element of every field, far lower (N = 2, two
+// phases, three FP64 fields: 0.09 M points 4.8 / 4.6, operator alone, 0.88 M 33.4 /
+// 35.4, FP32 23.2 / 25.0).
+template <int NQ, typename T>
 inline bool ax_fields_inside(int64_t points, int nf)
 {
-    return points > 2500000 && nf <= (sizeof(T) == 4 ? 4 : 3);
+    if (NQ <= 3) return NQ == 2 || points > 150000;
+    return points > 2500000 && nf <= (sizeof(T) == 4 || NQ <= 5 ? 4 : 3);
 }
 
 // Workgroups per CU of the persistent grid.  One field (operator alone, N = 7,
 // us; 16^3 / 32^3 elements): FP64 Poisson 4, 6, 8, 12: 23.8 / 221, 21.9 / 201,
 // 21.0 / 202, 21.0 / 209; with the mass term 6, 8, 12: 22.7 / 226, 22.8 / 228,
 // 22.7 / 237, and with QQ^T following 31.7 / 298, 32.1 / 302, 32.0 / 309; N = 5
-// with the mass term and QQ^T, 20^3 / 40^3, 6, 8, 10, 12: 33.7 / 287, 29.8 / 266,
-// 29.8 / 255, 28.9 / 257; FP32 8, 12, 16: - / 171, 167, 167 (N = 5, 23^3: 29.9,
-// 27.3, 26.6).  Several fields: a persistent grid whose last workgroups find no
-// room (three wavefronts each do not pack the SIMDs evenly after a preceding
-// kernel) runs a second round, 32^3 with QQ^T at 4 per CU 710 against 590 at 3;
-// many short workgroups (48 per CU inside, 24 else) have no such round.  With
-// partial sums there are at most as many workgroups as records.
+// with the mass term and QQ^T, 20^3 / 40^3, 6, 8, 10, 12: 33.7 / 287, 29.8 /
+// 266, 29.8 / 255, 28.9 / 257; FP32 8, 12, 16: - / 171, 167, 167 (N = 5, 23^3:
+// 29.9, 27.3, 26.6); N = 2, 0.15 M elements with k 10, 16: 59.6, 56.6.  Several
+// fields: a persistent grid whose last workgroups find no room (three wavefronts
+// each do not pack the SIMDs evenly after a preceding kernel) runs a second
+// round, 32^3 with QQ^T at 4 per CU 710 against 590 at 3; many short workgroups
+// (48 per CU inside, 24 else) have no such round.  With partial sums there are
+// at most as many workgroups as records.
 template <int NQ, typename T>
 inline int ax_blocks_per_cu(int nf, bool inside, bool dot)
 {
-    if (nf == 1) return sizeof(T) == 4 ? 16 : (NQ == 8 ? 6 : (NQ < 8 ? 10 : 8));
+    if (nf == 1) return sizeof(T) == 4 ? 16 : (NQ == 8 ? 6 : (NQ <= 3 ? 16 : NQ < 8 ? 10 : 8));
     if (inside) return dot ? 7 : 48;
     return 24;
 }
@@ -608,23 +737,44 @@ inline int64_t balanced_grid(int64_t groups, int64_t cap)
     return (groups + per - 1) / per;
 }
 
-// The spread form is used up to 2^18 points over all fields and N = 11 (us,
-// column form against spread form, each launch in a replayed graph: N = 7,
-// 64 elements 6.1 / 3.6, 216 with the mass term 5.2 / 3.9, 512 with k 5.8 / 5.7,
-// 729 6.3 / 7.5; N = 5, 1000 elements 5.3 / 4.7; N = 3, 4096 3.9 / 4.1; N = 9,
-// 216 9.1 / 6.7, 343 10.2 / 11.2; N = 11, 216 12.6 / 11.8; N = 13, 27
-// 13.8 / 22.4; three fields at N = 7, 64 6.5 / 3.9, 216 7.0 / 7.3).  The two
-// forms give the same bits per point.  Their partial sums cover different
-// points, and a batch has to have those of its single fields: with partial
-// sums the line lies at 2^17 points for any number of fields (with the direction
-// update, 512 elements at N = 7: 10.6 / 13.2).
-template <int NQ>
-inline bool ax_spread(const Level &L, int nf, bool dot)
+// Elements per CU, over all fields, up to which the spread form is taken: what is
+// resident at once, one workgroup an element from N = 5 on, more elements in one
+// below.  us, column form / spread form: FP64 N = 4, 720 elements 4.5 / 3.8, 2184
+// 5.2 / 5.4; N = 5, 990 5.6 / 5.2, 1716 6.8 / 7.3; N = 6, 504 5.4 / 4.7, 720 with the mass
+// term 5.7 / 6.3; N = 7, 210 5.5 / 4.4, 504 6.1 / 6.1, 720 6.4 / 7.8; N = 8, 504 9.5 / 7.7,
+// 720 10.5 / 11.1; N = 9, 210 9.8 / 6.9, 336 10.9 / 11.7; FP32 N = 6, 720 4.2 / 4.0; N = 8,
+// 504 6.1 / 4.9; N = 10, 210 7.2 / 5.0.  Where a single field goes in two phases at the
+// smallest sizes it needs none (N = 2, 3360 elements 3.2 / 3.7); several fields do
+// (FP32 N = 3, three fields of 504: 3.7 / 3.1, two of 1716 3.8 / 3.4; N = 2, two of 2184
+// 3.6 / 3.3, FP64 4.0 / 3.6).
+template <int NQ, typename T>
+constexpr int ax_spread_per_cu(int nf)
 {
-    const int64_t points = L.nL, blocks = points / (AxSplitShape<NQ>::EPB * AxSplitShape<NQ>::NP) + 1;
-    // the buffer of partial sums is sized by the CUs
-    if (dot && blocks > (int64_t)(L.n_cu > 0 ? L.n_cu : 256) * kAxMaxBlocksPerCU) return false;
-    return dot ? points <= (1 << 17) : points * nf <= (1 << 18);
+    if (nf == 1 && NQ <= (sizeof(T) == 4 ? 4 : 3)) return 0;
+    if (NQ == 2) return 0;
+    if (NQ == 3) return sizeof(T) == 4 ? 36 : 28;
+    if (NQ == 4 && sizeof(T) == 4) return 16;
+    return NQ <= 5 ? 8 : NQ == 6 ? 4 : NQ == 7 && sizeof(T) == 4 ? 3 : NQ <= 9 ? 2 : NQ <= 12 ? 1 : 0;
+}
+
+// The two forms give the same bits per point.  Their partial sums cover different
+// points, and a batch has to have those of its single fields: with partial sums
+// the line does not depend on the number of fields.  It then lies lower for some
+// orders, as every workgroup adds up the records of the update for itself (a
+// Jacobi-PCG iteration, us, column / spread: N = 4, 1716 elements 20.2 / 21.0; N = 5,
+// 990 20.7 / 22.1; N = 7, 504 19.7 / 20.2; N = 8, 336 24.6 / 25.7; but N = 6, 336
+// 16.8 / 16.3; N = 9, 210 25.1 / 21.7; N = 10, 210 27.4 / 25.9).
+template <int NQ, typename T>
+inline bool ax_spread(const Level &L, int nf, bool helm, bool vark, bool dot)
+{
+    static_assert(ax_spread_per_cu<NQ, T>(1) < kAxMaxBlocksPerCU, "the buffer of partial sums");
+    // single FP64 fields in forms that spill: N = 10 with k, 120 elements 11.6 / 16.3; N = 11 with the
+    // mass term 11.7 / 13.3
+    if (sizeof(T) == 8 && !dot && nf == 1 && ((NQ >= 11 && vark) || (NQ >= 12 && helm))) return false;
+    constexpr int half = NQ == 5 || NQ == 6 || NQ == 8 || NQ == 9 ? 2 : 1;
+    const int64_t cu = L.n_cu > 0 ? L.n_cu : 256;
+    if (dot) return L.E * half <= cu * ax_spread_per_cu<NQ, T>(1);
+    return L.E * nf <= cu * ax_spread_per_cu<NQ, T>(nf);
 }
 
 // the compiled forms: mass term, coefficient (one field), partial sums (FP64)
@@ -670,7 +820,7 @@ static int ax_split_launch(const Level &L, const T *G, const T *B, const T *D, c
 
 // One launch for the NF vectors of vs (one, or up to kMaxRhs with nq <= 8).
 // Every field's arithmetic is that of a single-field call.
-template <int NQ, typename T, int NW, int NI>
+template <int NQ, typename T, int NW, int NI, bool TWO>
 static int ax_launch(const Level &L, const T *G, const T *B, const T *D, const T *u, int64_t ldu,
                      T *w, int64_t ldw, const VSet &vs, double h1, double h2, const T *k,
                      double *partial, int64_t pst, int64_t *nblocks, hipStream_t s, const int *skip,
@@ -688,7 +838,7 @@ static int ax_launch(const Level &L, const T *G, const T *B, const T *D, const T
     if (nb == 0) return SEM_OK;
     const dim3 grid((unsigned)nb), block(S::threads(NW));
 #define SEM_AX_LAUNCH(H, V, P)                                                                 \
-    hipLaunchKernelGGL((ax_kernel<NQ, T, H, V, P, NW, NI>), grid, block, 0, s, L.E, G, B, k,  \
+    hipLaunchKernelGGL((ax_kernel<NQ, T, H, V, P, NW, NI, TWO>), grid, block, 0, s, L.E, G, B, k, \
                        D, (T)h1, (T)h2, u, ldu, w, ldw, vs, partial, pst, dot ? nvb : nb,     \
                        skip, skip_stride, dir)
     SEM_AX_FORMS(NF == 1)
@@ -703,34 +853,43 @@ static int ax_dispatch(const Level &L, const T *G, const T *B, const T *D, const
                        double *partial, int64_t pst, int64_t *nblocks, hipStream_t s, const int *skip,
                        int skip_stride, const PcgDir &dir)
 {
-    if constexpr (NQ <= 12)
-        if (ax_spread<NQ>(L, vs.n, partial != nullptr))
+    if constexpr (ax_spread_per_cu<NQ, T>(2) > 0)
+        if (ax_spread<NQ, T>(L, vs.n, h2 != 0.0, k != nullptr, partial != nullptr))
             return ax_split_launch<NQ, T>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, k, partial, pst, nblocks, s,
                                           skip, skip_stride, dir);
-#define SEM_AX_NF(NW, NI)                                                                      \
-    return ax_launch<NQ, T, NW, NI>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, k, partial, pst,  \
-                                    nblocks, s, skip, skip_stride, dir)
-    if (vs.n == 1) SEM_AX_NF(1, 1);
+#define SEM_AX_NF(NW, NI, TWO)                                                                 \
+    return ax_launch<NQ, T, NW, NI, TWO>(L, G, B, D, u, ldu, w, ldw, vs, h1, h2, k, partial,  \
+                                         pst, nblocks, s, skip, skip_stride, dir)
+    constexpr int64_t two = ax_two_phase_points<NQ, T>();
+    if (vs.n == 1) {
+        if constexpr (two > 0)
+            if (L.nL <= two) SEM_AX_NF(1, 1, true);
+        if constexpr (two < INT64_MAX) SEM_AX_NF(1, 1, false);
+    }
     if constexpr (NQ <= 8) {
         if (k == nullptr) {
-            if (ax_fields_inside<T>(L.nL, vs.n)) {
-                if (vs.n == 2) SEM_AX_NF(1, 2);
-                if (vs.n == 3) SEM_AX_NF(1, 3);
-                if constexpr (sizeof(T) == 4)
-                    if (vs.n == 4) SEM_AX_NF(1, 4);
+            if (ax_fields_inside<NQ, T>(L.nL, vs.n)) {
+                // up to N = 3 in two phases (3 M points, two FP64 fields at N = 3 by
+                // planes / in two phases 83.0 / 80.0, three 117 / 114)
+                if (vs.n == 2) SEM_AX_NF(1, 2, NQ <= 4);
+                if (vs.n == 3) SEM_AX_NF(1, 3, NQ <= 4);
+                if constexpr (sizeof(T) == 4 || NQ <= 5)
+                    if (vs.n == 4) SEM_AX_NF(1, 4, NQ <= 4);
             }
-            if (vs.n == 2) SEM_AX_NF(2, 1);
-            if (vs.n == 3) SEM_AX_NF(3, 1);
-            if (vs.n == 4) SEM_AX_NF(4, 1);
+            if constexpr (NQ > 2) {
+                if (vs.n == 2) SEM_AX_NF(2, 1, false);
+                if (vs.n == 3) SEM_AX_NF(3, 1, false);
+                if (vs.n == 4) SEM_AX_NF(4, 1, false);
+            }
         }
     }
 #undef SEM_AX_NF
-    // one field at a time (variable coefficient, or elements wider than a wavefront)
+    // one field at a time (several with variable coefficient, or elements wider than a wavefront)
     for (int q = 0; q < vs.n; ++q) {
         VSet one{0, 0u};
         one.push(vs.at(q));
-        SEM_TRY((ax_launch<NQ, T, 1, 1>(L, G, B, D, u, ldu, w, ldw, one, h1, h2, k, partial, pst, nblocks,
-                                     s, skip, skip_stride, dir)));
+        SEM_TRY((ax_launch<NQ, T, 1, 1, (two == INT64_MAX)>(L, G, B, D, u, ldu, w, ldw, one, h1, h2, k, partial,
+                                                            pst, nblocks, s, skip, skip_stride, dir)));
     }
     return SEM_OK;
 }
