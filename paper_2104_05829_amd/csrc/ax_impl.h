@@ -27,6 +27,8 @@
 // SIMD at N = 7 and 2-3 up to N = 15 (four rows: 1-2 from N = 11 on).
 // Bytes per point (FP64 Poisson): u 8 + G 48 + w 8 = 64 (+8 for B, +8 for k).
 #pragma once
+#include <algorithm>
+
 #include "sem_internal.h"
 
 // FMA contraction within single expressions only: the single-vector and the
@@ -147,10 +149,10 @@ __device__ inline double ax_block_sum(double x, int tid, double *sh)
     return x;
 }
 
-// Decision and beta after an update (PcgDir), the same in every workgroup: the
-// first N = min(64, THREADS) lanes of the block (or of a field's wavefront) add
-// the records t, t + N, ... in order, eight loads in flight, then halve.
-// False: the vector's iteration has ended.  record: this block notes it.
+// Decision and beta after an update (PcgDir), the same in every workgroup, from
+// the sum of its records by the first N = min(64, THREADS) lanes of the block (or
+// of a field's wavefront).  False: the vector's iteration has ended.  record: this
+// block notes it.
 template <int THREADS>
 __device__ inline bool pcg_direction(const PcgDir &d, int64_t v, int tid, bool record, double *sh, double *beta)
 {
@@ -160,35 +162,7 @@ __device__ inline bool pcg_direction(const PcgDir &d, int64_t v, int tid, bool r
     const double tol2 = sc->tol2, rz_old = sc->rz2[d.parity];
     const int maxit = sc->maxit, done = sc->done;
     double rz = 0.0, rr = 0.0;
-    if (tid < N) {
-        const double2 *pr = reinterpret_cast<const double2 *>(d.pu + v * d.pst);
-        int64_t b = tid;
-        for (; b + 7 * N < d.nb; b += 8 * N) {
-            double2 x[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) x[q] = pr[b + q * N];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                rz += x[q].x;
-                rr += x[q].y;
-            }
-        }
-        for (; b < d.nb; b += N) {
-            const double2 x = pr[b];
-            rz += x.x;
-            rr += x.y;
-        }
-#pragma unroll
-        for (int st = 32; st >= 1; st >>= 1) {
-            const double a = __shfl_down(rz, st, 64), c = __shfl_down(rr, st, 64);
-            if (tid + st < N) {
-                rz += a;
-                rr += c;
-            }
-        }
-        rz = __shfl(rz, 0, 64);
-        rr = __shfl(rr, 0, 64);
-    }
+    if (tid < N) pcg_sum_records(d.pu + v * d.pst, d.nb, tid, N, rz, rr);
     if constexpr (THREADS > 64) {
         if (tid == 0) {
             sh[0] = rz;
@@ -892,6 +866,16 @@ static int ax_dispatch(const Level &L, const T *G, const T *B, const T *D, const
                                                             pst, nblocks, s, skip, skip_stride, dir)));
     }
     return SEM_OK;
+}
+
+// lanes that sum an update's records in an operator with a direction update
+template <int NQ>
+static int ax_direction_lanes_nq(const Level &L, double h2, const double *k)
+{
+    int threads = AxShape<NQ>::THREADS;
+    if constexpr (ax_spread_per_cu<NQ, double>(1) > 0)
+        if (ax_spread<NQ, double>(L, 1, h2 != 0.0, k != nullptr, true)) threads = AxSplitShape<NQ>::THREADS;
+    return std::min(64, threads);
 }
 
 template <typename T>

@@ -313,6 +313,44 @@ int launch_ax_multi(const Level &L, const T *G, const T *B, const T *D, const T 
                     int64_t pst, int64_t *nblocks, hipStream_t s, const int *skip, int skip_stride,
                     const PcgDir &dir = PcgDir{});
 
+// lanes that sum an update's records in the operator that has `dir`
+int ax_direction_lanes(const Level &L, double h2, const double *k);
+
+// Sum of nb records (rz, rr) by n <= 64 lanes of one wavefront: lane t adds the
+// records t, t + n, ... in order, eight loads in flight, then the lanes halve; the
+// sums are returned to all of them.
+__device__ inline void pcg_sum_records(const double *records, int64_t nb, int t, int n, double &rz, double &rr)
+{
+    const double2 *pr = reinterpret_cast<const double2 *>(records);
+    rz = rr = 0.0;
+    int64_t b = t;
+    for (; b + 7 * n < nb; b += 8 * n) {
+        double2 x[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) x[q] = pr[b + q * n];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            rz += x[q].x;
+            rr += x[q].y;
+        }
+    }
+    for (; b < nb; b += n) {
+        const double2 x = pr[b];
+        rz += x.x;
+        rr += x.y;
+    }
+#pragma unroll
+    for (int st = 32; st >= 1; st >>= 1) {
+        const double a = __shfl_down(rz, st, 64), c = __shfl_down(rr, st, 64);
+        if (t + st < n) {
+            rz += a;
+            rr += c;
+        }
+    }
+    rz = __shfl(rz, 0, 64);
+    rr = __shfl(rr, 0, 64);
+}
+
 template <typename T>
 int launch_gs_multi(const Level &L, T *v, int64_t ld, const VSet &vs, hipStream_t s,
                     const int *skip, int skip_stride);

@@ -1352,22 +1352,24 @@ static PcgBufs ws_bufs(sem_handle h, const Level &L)
 }
 
 // Convergence decision after the last update of a batch of iterations (one
-// block per vector), for the host; the next operator takes it again by itself.
+// wavefront per vector), for the host.  The next operator takes it again by
+// itself: the records are summed in its order, by `lanes`, so that both agree and
+// where a batch ends does not show in the result.
 __global__ void pcg_decide_kernel(VSet vs, KrylovScalars *sc, int iter, int stamp,
-                                  const double *__restrict__ pu, int64_t pst, int64_t nbu)
+                                  const double *__restrict__ pu, int64_t pst, int64_t nbu, int lanes)
 {
     const int64_t v = vsel(vs);
     sc += v;
-    if (ended_before(sc->done, stamp)) return;
-    double res[2];
-    sum_partials<2>(pu + v * pst, nbu, res);
+    if (ended_before(sc->done, stamp) || (int)threadIdx.x >= lanes) return;
+    double rz, rr;
+    pcg_sum_records(pu + v * pst, nbu, threadIdx.x, lanes, rz, rr);
     if (threadIdx.x == 0) {
-        const bool bad = !isfinite(res[0]) || !isfinite(res[1]);
+        const bool bad = !isfinite(rz) || !isfinite(rr);
         sc->iters = iter;
-        sc->rr = res[1];
-        sc->rz = res[0];
+        sc->rr = rr;
+        sc->rz = rz;
         if (bad) sc->status = SEM_EBREAKDOWN;
-        if (bad || res[1] <= sc->tol2 || iter >= sc->maxit) sc->done = stamp;
+        if (bad || rr <= sc->tol2 || iter >= sc->maxit) sc->done = stamp;
     }
 }
 
@@ -1431,8 +1433,10 @@ static int pcg_iterations(sem_handle h, const Level &L, const VSet &vs, const do
         if (timed) SEM_TRY(clock_mark(ws, kPhaseVec, s));
     }
     const int last = first_iter + iters - 1;
-    LAUNCH_1B(pcg_decide_kernel, vs, s, vs, kv.sc, last, end_stamp(last, kEndDecide),
-              (const double *)pb.partial, pb.pst, (int64_t)nbv);
+    hipLaunchKernelGGL(pcg_decide_kernel, dim3(1, (unsigned)vs.n), dim3(64), 0, s, vs, kv.sc, last,
+                       end_stamp(last, kEndDecide), (const double *)pb.partial, pb.pst, (int64_t)nbv,
+                       ax_direction_lanes(L, h2, k));
+    SEM_HIP(hipGetLastError());
     return SEM_OK;
 }
 
