@@ -323,21 +323,15 @@ __device__ inline void pcg_sum_records(const double *records, int64_t nb, int t,
 {
     const double2 *pr = reinterpret_cast<const double2 *>(records);
     rz = rr = 0.0;
-    int64_t b = t;
-    for (; b + 7 * n < nb; b += 8 * n) {
-        double2 x[8];
+    for (int64_t b = t; b < nb; b += 8 * n) {
+        double2 x[8];  // records past the last add nothing
 #pragma unroll
-        for (int q = 0; q < 8; ++q) x[q] = pr[b + q * n];
+        for (int q = 0; q < 8; ++q) x[q] = b + q * n < nb ? pr[b + q * n] : make_double2(0.0, 0.0);
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             rz += x[q].x;
             rr += x[q].y;
         }
-    }
-    for (; b < nb; b += n) {
-        const double2 x = pr[b];
-        rz += x.x;
-        rr += x.y;
     }
 #pragma unroll
     for (int st = 32; st >= 1; st >>= 1) {

@@ -1377,10 +1377,10 @@ __global__ void pcg_decide_kernel(VSet vs, KrylovScalars *sc, int iter, int stam
 // on level L for the batch vs: operator with the direction update and decision
 // of the iteration before and the partial sums of (p, A_L p), QQ^T, update with
 // alpha -- three kernels per iteration (two where the update sums the copies
-// itself), and one for the decision of the last
+// itself), and with `decide` one for the decision of the last
 static int pcg_iterations(sem_handle h, const Level &L, const VSet &vs, const double *k, double h1,
                           double h2, const KrylovVecs &kv, const PcgBufs &pb, int first_iter,
-                          int iters, hipStream_t s, bool timed = false)
+                          int iters, bool decide, hipStream_t s, bool timed = false)
 {
     Workspace &ws = h->ws;
     const int64_t n = L.nL;
@@ -1432,6 +1432,7 @@ static int pcg_iterations(sem_handle h, const Level &L, const VSet &vs, const do
         }
         if (timed) SEM_TRY(clock_mark(ws, kPhaseVec, s));
     }
+    if (!decide) return SEM_OK;
     const int last = first_iter + iters - 1;
     hipLaunchKernelGGL(pcg_decide_kernel, dim3(1, (unsigned)vs.n), dim3(64), 0, s, vs, kv.sc, last,
                        end_stamp(last, kEndDecide), (const double *)pb.partial, pb.pst, (int64_t)nbv,
@@ -1768,14 +1769,16 @@ static int coarse_csr_solve(sem_handle h, const Level &L, const VSet &vs, double
     return SEM_OK;
 }
 
-// Jacobi-PCG iterations in batches of check_every until every vector of `all`
-// is done, the next batch enqueued before the host reads the scalars of the
-// one before: the GPU does not wait for the host (64 elements at N = 7: 19 us
-// of every batch of eight, 88 us of kernels), and the batch enqueued past the
-// end finds the flags set.  On return host_sc holds the final scalars.
+// Jacobi-PCG iterations in batches of check_every (the last one ends at maxit)
+// until every vector of `all` is done.  A start that has converged already takes
+// no iteration.  Before the host waits for a batch's scalars it enqueues the first
+// two iterations of the next one, which cover its round trip (64 elements at
+// N = 7: 19 us; an iteration 11 us); a whole batch ahead covered no more, and its
+// kernels past the end cost 45 us.  On return host_sc holds the final scalars.
 static int pcg_batches(sem_handle h, const Level &F, const VSet &all, const sem_solve_opts *o,
                        const SolveCfg &cfg, const KrylovVecs &kv, hipStream_t s)
 {
+    constexpr int kAhead = 2;
     Workspace &w = h->ws;
     const size_t bytes = kMaxRhs * sizeof(KrylovScalars);
     for (auto &e : w.chk)
@@ -1787,22 +1790,36 @@ static int pcg_batches(sem_handle h, const Level &F, const VSet &all, const sem_
         return SEM_OK;
     };
     VSet act = all;
-    int it = 0, q = 0;
-    SEM_TRY(post(q));  // the scalars of the start
-    for (;;) {
-        SEM_TRY(pcg_iterations(h, F, act, o->k, o->h1, o->h2, kv, ws_bufs(h, F), it + 1, cfg.check_every, s));
-        it += cfg.check_every;
-        SEM_TRY(post(q ^ 1));
+    auto look = [&](int q) -> int {  // the vectors of act that go on
         SEM_HIP(hipEventSynchronize(w.chk[q]));
         VSet left{0, 0u};
         for (int m = 0; m < act.n; ++m)
             if (!slot[q][act.at(m)].done) left.push(act.at(m));
-        if (left.n == 0) break;
         act = left;
+        return SEM_OK;
+    };
+    auto iterate = [&](int first, int n, bool decide) -> int {
+        return pcg_iterations(h, F, act, o->k, o->h1, o->h2, kv, ws_bufs(h, F), first, n, decide, s);
+    };
+    auto batch = [&](int it) { return std::min(cfg.check_every, cfg.maxit - it); };  // after `it` iterations
+    int it = 0, ahead = 0, q = 0;
+    bool whole = false;  // the iterations ahead are a whole batch, its scalars posted too
+    SEM_TRY(post(q));
+    SEM_TRY(look(q));
+    while (act.n > 0) {
+        const int n = batch(it);
+        if (!whole) SEM_TRY(iterate(it + ahead + 1, n - ahead, true));
+        it += n;
         q ^= 1;
+        if (!whole) SEM_TRY(post(q));
+        const int next = batch(it);
+        ahead = std::min(kAhead, next);
+        whole = ahead > 0 && ahead == next;
+        if (ahead > 0) SEM_TRY(iterate(it + 1, ahead, whole));
+        if (whole) SEM_TRY(post(q ^ 1));
+        SEM_TRY(look(q));
     }
-    // the copy still in flight ends with the same scalars
-    SEM_HIP(hipEventSynchronize(w.chk[q ^ 1]));
+    if (whole) SEM_HIP(hipEventSynchronize(w.chk[q ^ 1]));  // the copy in flight: the same scalars
     if (q != 0) std::copy(slot[1], slot[1] + kMaxRhs, slot[0]);
     return SEM_OK;
 }
@@ -1827,7 +1844,7 @@ static int vcycle(sem_handle h, int l, const VSet &vs, const SolveCfg &cfg, hipS
         const PcgBufs pb = ws_bufs(h, L);
         SEM_TRY(pcg_start(L, vs, nullptr, cfg.h1, cfg.h2, b, n, kv, pb, true, cfg.coarse_tol,
                           cfg.coarse_maxit, BbRef{}, s));
-        SEM_TRY(pcg_iterations(h, L, vs, nullptr, cfg.h1, cfg.h2, kv, pb, 1, cfg.coarse_maxit, s));
+        SEM_TRY(pcg_iterations(h, L, vs, nullptr, cfg.h1, cfg.h2, kv, pb, 1, cfg.coarse_maxit, true, s));
         SEM_TRY(clock_mark(w, kPhaseCoarse, s));
         return SEM_OK;
     }
@@ -2308,7 +2325,7 @@ int pcg_solve(sem_handle h, int nv, const double *b, double *x, int64_t ld, cons
             int it = 0;
             while (act.n > 0) {
                 SEM_TRY(pcg_iterations(h, F, act, o->k, o->h1, o->h2, kv, ws_bufs(h, F), it + 1,
-                                       cfg.check_every, s, true));
+                                       cfg.check_every, true, s, true));
                 it += cfg.check_every;
                 SEM_TRY(sync_point(false));
                 act = live_set(w, act);
@@ -2613,7 +2630,7 @@ static int pcg_solve_noalloc(sem_handle h, const double *b, double *x, const sem
     KrylovScalars hs{};
     SEM_TRY(read_one_scalar(sc, &hs, s));
     for (int it = 0; !hs.done; it += check) {
-        SEM_TRY(pcg_iterations(h, F, one, o->k, o->h1, o->h2, kv, pb, it + 1, check, s));
+        SEM_TRY(pcg_iterations(h, F, one, o->k, o->h1, o->h2, kv, pb, it + 1, check, true, s));
         SEM_TRY(read_one_scalar(sc, &hs, s));
     }
     const auto t2 = clk::now();
