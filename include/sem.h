@@ -208,7 +208,11 @@ typedef struct {
                             Jacobi. */
     int timers;          /* 1: time the solver's phases with HIP events on `stream` (fills
                             the ms_ax .. ms_coarse fields of the stats); adds event records
-                            between kernels and no host synchronisation.  0: off (fields 0) */
+                            between kernels and no host synchronisation.  With Jacobi on up
+                            to 2^18 points, whose updates otherwise sum the copies of a node
+                            themselves, QQ^T also runs as a pass of its own, for ms_gs (same
+                            iterates, two kernels per iteration become three).  0: off
+                            (fields 0) */
 } sem_solve_opts;
 
 typedef struct {

@@ -937,6 +937,17 @@ static int clock_begin(Workspace &w, bool on)
     return SEM_OK;
 }
 
+// charge the intervals between the first n events, which the stream has reached
+static int clock_charge(PhaseClock &c, int n)
+{
+    for (int i = 1; i < n; ++i) {
+        float ms = 0.0f;
+        SEM_HIP(hipEventElapsedTime(&ms, c.ev[i - 1], c.ev[i]));
+        if (c.ph[i] >= 0) c.ms[c.ph[i]] += ms;
+    }
+    return SEM_OK;
+}
+
 // Charge the intervals of the current chain; the stream has reached its last
 // event (after a host synchronisation), or `wait` waits for it.  The chain
 // restarts empty: the idle time of the host round trip is charged to nothing.
@@ -945,12 +956,23 @@ static int clock_flush(Workspace &w, bool wait)
     PhaseClock &c = w.clk;
     if (!c.on || c.n == 0) return SEM_OK;
     if (wait) SEM_HIP(hipEventSynchronize(c.ev[c.n - 1]));
-    for (int i = 1; i < c.n; ++i) {
-        float ms = 0.0f;
-        SEM_HIP(hipEventElapsedTime(&ms, c.ev[i - 1], c.ev[i]));
-        if (c.ph[i] >= 0) c.ms[c.ph[i]] += ms;
-    }
+    SEM_TRY(clock_charge(c, c.n));
     c.n = 0;
+    return SEM_OK;
+}
+
+// The same up to the n-th event, which the chain goes on from: the stream has work
+// behind it.  Returns in *gone how many events left the chain.
+static int clock_flush_to(Workspace &w, int n, int *gone)
+{
+    PhaseClock &c = w.clk;
+    *gone = 0;
+    if (!c.on || n < 2) return SEM_OK;
+    SEM_TRY(clock_charge(c, n));
+    *gone = n - 1;
+    std::rotate(c.ev.begin(), c.ev.begin() + *gone, c.ev.end());
+    std::rotate(c.ph.begin(), c.ph.begin() + *gone, c.ph.end());
+    c.n -= *gone;
     return SEM_OK;
 }
 
@@ -960,9 +982,11 @@ static int clock_mark(Workspace &w, int p, hipStream_t s)
 {
     PhaseClock &c = w.clk;
     if (!c.on) return SEM_OK;
-    if (c.n == (int)c.ev.size()) {  // pool used up: charge it, continue the chain from here
-        SEM_TRY(clock_flush(w, true));
-        p = -1;
+    if (c.n == (int)c.ev.size()) {  // more phases between two looks of the host than ever before
+        hipEvent_t e = nullptr;
+        SEM_HIP(hipEventCreate(&e));
+        c.ev.push_back(e);
+        c.ph.push_back(-1);
     }
     SEM_HIP(hipEventRecord(c.ev[c.n], s));
     c.ph[c.n] = c.n == 0 ? -1 : p;
@@ -1438,6 +1462,7 @@ static int pcg_iterations(sem_handle h, const Level &L, const VSet &vs, const do
                        end_stamp(last, kEndDecide), (const double *)pb.partial, pb.pst, (int64_t)nbv,
                        ax_direction_lanes(L, h2, k));
     SEM_HIP(hipGetLastError());
+    if (timed) SEM_TRY(clock_mark(ws, kPhaseVec, s));
     return SEM_OK;
 }
 
@@ -1784,7 +1809,9 @@ static int pcg_batches(sem_handle h, const Level &F, const VSet &all, const sem_
     for (auto &e : w.chk)
         if (!e) SEM_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     KrylovScalars *slot[2] = {w.host_sc, w.host_sc + kMaxRhs};
+    int marks[2] = {};  // phase boundaries ahead of each slot's copy
     auto post = [&](int q) -> int {
+        marks[q] = w.clk.n;
         SEM_HIP(hipMemcpyAsync(slot[q], w.sc, bytes, hipMemcpyDeviceToHost, s));
         SEM_HIP(hipEventRecord(w.chk[q], s));
         return SEM_OK;
@@ -1796,16 +1823,21 @@ static int pcg_batches(sem_handle h, const Level &F, const VSet &all, const sem_
         for (int m = 0; m < act.n; ++m)
             if (!slot[q][act.at(m)].done) left.push(act.at(m));
         act = left;
+        int gone = 0;
+        SEM_TRY(clock_flush_to(w, marks[q], &gone));
+        marks[q ^ 1] -= gone;
         return SEM_OK;
     };
     auto iterate = [&](int first, int n, bool decide) -> int {
-        return pcg_iterations(h, F, act, o->k, o->h1, o->h2, kv, ws_bufs(h, F), first, n, decide, s);
+        return pcg_iterations(h, F, act, o->k, o->h1, o->h2, kv, ws_bufs(h, F), first, n, decide, s, true);
     };
     auto batch = [&](int it) { return std::min(cfg.check_every, cfg.maxit - it); };  // after `it` iterations
     int it = 0, ahead = 0, q = 0;
     bool whole = false;  // the iterations ahead are a whole batch, its scalars posted too
     SEM_TRY(post(q));
     SEM_TRY(look(q));
+    SEM_TRY(clock_flush(w, false));
+    SEM_TRY(clock_mark(w, -1, s));  // the host's look at the start is no phase's time
     while (act.n > 0) {
         const int n = batch(it);
         if (!whole) SEM_TRY(iterate(it + ahead + 1, n - ahead, true));
@@ -2319,20 +2351,7 @@ int pcg_solve(sem_handle h, int nv, const double *b, double *x, int64_t ld, cons
         SEM_TRY(pcg_start(F, all, o->k, o->h1, o->h2, bs, ldbs, kv, ws_bufs(h, F), zero, o->tol,
                           o->maxit, ref, s));
         SEM_TRY(clock_mark(w, kPhaseVec, s));
-        if (w.clk.on) {
-            SEM_TRY(sync_point(false));
-            VSet act = live_set(w, all);
-            int it = 0;
-            while (act.n > 0) {
-                SEM_TRY(pcg_iterations(h, F, act, o->k, o->h1, o->h2, kv, ws_bufs(h, F), it + 1,
-                                       cfg.check_every, true, s, true));
-                it += cfg.check_every;
-                SEM_TRY(sync_point(false));
-                act = live_set(w, act);
-            }
-        } else {
-            SEM_TRY(pcg_batches(h, F, all, o, cfg, kv, s));
-        }
+        SEM_TRY(pcg_batches(h, F, all, o, cfg, kv, s));
     } else {
         // r = b - A x ; z = M r ; p = z ; rz = (z, r)
         const double *Ax = nullptr;

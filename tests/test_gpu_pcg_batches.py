@@ -96,3 +96,28 @@ def test_batch_lengths_and_limits(nf):
                 ref = (got, X)
             assert got == ref[0] and torch.equal(X, ref[1]), (maxit, every, got, ref[0])
     s.free()
+
+
+@pytest.mark.parametrize("shape,every", [((4, 4, 4), 2), ((4, 4, 4), 8), ((9, 9, 9), 2), ((4, 4, 4), 400)])
+def test_timers_leave_the_launch_sequence_alone(shape, every):
+    """With timers the host still works ahead of the stream: apart from its look
+    at the start (some 20 us) the phases follow each other without a gap, so
+    they add up to all but a few percent of a solve of milliseconds.  400: more
+    phase boundaries between two looks than the event pool starts with."""
+    print(f"[gpu] pcg timers {shape} every={every}", flush=True)
+    xi, _ = oracle.gll(7)
+    m = inputs.box_mesh(*shape, xi, deform="cyclic", amp=0.05)
+    s = Sem(m)
+    b = s.rhs(_dev(inputs.gaussian_per_node(m.gid, 8)))
+    kw = dict(h2=10.0, tol=1e-9, check_every=every, maxit=2000)
+    x0, st0, _ = s.solve(b, **kw)
+    part = 0.0
+    for _ in range(3):
+        x1, st1, _ = s.solve(b, timers=1, **kw)
+        assert torch.equal(x0, x1) and st0["iters"] == st1["iters"] and st0["rel_res"] == st1["rel_res"]
+        total = st1["ms_ax"] + st1["ms_gs"] + st1["ms_vec"]
+        assert min(st1["ms_ax"], st1["ms_gs"], st1["ms_vec"]) > 0.0 and total <= st1["ms_solve"] * 1.05 + 0.05
+        part = max(part, total / st1["ms_solve"])
+    print(f"  phases {part:.3f} of the solve", flush=True)
+    assert part >= 0.85
+    s.free()
