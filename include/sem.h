@@ -149,8 +149,10 @@ SEM_API int sem_gs(sem_handle h, double *v, int op, void *stream);
  * geometric factors of an element serve every component):
  *   w_r = h1 A_L u_r + h2 B_L u_r for
  * r = 0 .. nrhs-1, with u_r = u + r*ld and w_r = w + r*ld (device L-vectors,
- * FP64, ld >= n_local when nrhs > 1, u and w not overlapping).  The geometric factors of an
- * element serve every field of a batch of up to SEM_MAX_RHS at once.  Each w_r is
+ * FP64, ld >= n_local when nrhs > 1, u and w not overlapping).  One launch serves every
+ * field of a batch of up to SEM_MAX_RHS, each element's geometric factors fetched once for
+ * all of them, up to N = 7, and on meshes of few elements up to N = 11; beyond, each field
+ * is a launch of its own.  Each w_r is
  * bit-identical to sem_ax(u_r) with k = NULL.  nrhs >= 1.
  */
 SEM_API int sem_ax_multi(sem_handle h, int nrhs, const double *u, double *w, int64_t ld, double h1,
