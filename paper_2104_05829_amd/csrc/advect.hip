@@ -340,79 +340,148 @@ __global__ void __launch_bounds__((Adv3Shape<NQ, M>::THREADS))
 // on 32^3 elements); formed here from the 12 KB of coordinates they cost
 // arithmetic that hides behind the 44 KB left.
 // Lane t = a + M b owns the Gauss column (b, a) as in the advection kernel.  The
-// three velocity components, then the three coordinates go through LDS one after
-// another (contraction over i on GLL rows, over j on the column); a column keeps
-// its nine derivative lines along k in registers, its three velocity lines in
-// LDS, and walks the M points: derivatives, the three cofactor rows as cross
-// products, and their products with the velocity.
+// velocity components and the coordinates are contracted over i on their GLL
+// rows, a row per lane straight from memory, and over j on the columns, through
+// LDS; a column keeps the nine derivative lines along k in registers, its three
+// velocity lines in LDS, and walks the M points: derivatives, the three cofactor
+// rows as cross products, and their products with the velocity.
+// From M = 9 on an element has two wavefronts or three, and two of them share the
+// rows of a round: two velocity components, halves of the third, then J and Jd of
+// a coordinate: five rounds of half the rows where one wavefront took six alone
+// (N = 6, 343 / 4096 elements: 16.4 / 66.7 -> 14.7 / 59.2 us; at N = 7, where the
+// points are most of the time, 19.2 / 83.4 -> 19.1 / 82.5).  Up to M = 5 a wavefront
+// takes several elements, whose columns and rows fill its lanes (N = 1, 13824
+// elements 14.8 -> 4.1; N = 2 28.8 -> 11.5; N = 3 39.5 -> 24.2).
+// EW: elements of EW wavefront groups side by side.  Two workgroups of two
+// wavefronts on a CU share two of its SIMDs, one workgroup of four takes all (N = 6,
+// 343 elements 14.7 -> 13.7, N = 7 19.2 -> 18.2).
 // CHECK: no velocity, bad |= 1 where det dx/dr <= 0.
-template <int NQ, int M, bool CHECK>
-__global__ void __launch_bounds__((AdvShape<NQ, M>::THREADS), 2)
+template <int NQ, int M>
+struct VelShape {
+    static constexpr int MM = M * M;
+    static constexpr int EPB = MM <= 32 ? 64 / MM : 1;  // elements of a workgroup
+    static constexpr int COLS = EPB * MM, ROWS = EPB * NQ * NQ;
+    static constexpr int THREADS = (COLS + 63) / 64 * 64;
+    static constexpr bool DUO = THREADS > 64;
+    static_assert(ROWS <= 64, "a row per lane of one wavefront");
+};
+
+template <int NQ, int M, bool CHECK, int EW>
+__global__ void __launch_bounds__((EW * VelShape<NQ, M>::THREADS), 2)
     velocity_kernel(int64_t E, const double *__restrict__ J, const double *__restrict__ Jd,
                     const double *__restrict__ wq, const double *__restrict__ x,
                     const double *__restrict__ y, const double *__restrict__ z,
                     const double *__restrict__ cv, int64_t ldc, double *__restrict__ ct, int *bad)
 {
-    using S = AdvShape<NQ, M>;
-    constexpr int NP = S::NP, MM = S::MM, M3 = S::M3, TH = S::THREADS;
-    constexpr int F0 = CHECK ? 3 : 0, PFN = (NP + TH - 1) / TH;
-    __shared__ double sU[NP];
-    __shared__ double sP[NQ * NQ * M], sQ[NQ * NQ * M];
-    __shared__ double sV[CHECK ? 1 : 3 * NQ][MM];
+    using S = VelShape<NQ, M>;
+    constexpr int MM = S::MM, M3 = MM * M, TH = S::THREADS, EPB = S::EPB, ROWS = S::ROWS;
+    // at N = 7 the rows come through LDS, since a row each of the coming round does
+    // not fit beside the lines (36 registers spilled, 24^3 elements 283 -> 360 us)
+    constexpr bool DUO = S::DUO, STAGE = NQ >= 8, PAIR = DUO && !STAGE && !CHECK;
+    constexpr int NP = NQ * NQ * NQ, PFN = STAGE ? (NP + TH - 1) / TH : NQ;
+    constexpr int ROUNDS = CHECK ? 3 : PAIR ? 5 : 6;
+    __shared__ double sU_[EW][STAGE ? NP : 1];
+    __shared__ double sP_[EW][ROWS * M], sQ_[EW][ROWS * M];
+    __shared__ double sV_[EW][CHECK ? 1 : 3 * NQ][S::COLS];
     __shared__ double sJ[M][NQ + 1], sJd[M][NQ + 1];
-    const int t = threadIdx.x;
-    const bool col = t < MM;
-    const int a = col ? t % M : 0, b = col ? t / M : 0;
-    for (int i = t; i < M * NQ; i += TH) {
+    static_assert(EW == 1 || DUO, "several elements of several wavefronts");
+    const int ew = EW == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / TH);
+    const int t = threadIdx.x - ew * TH, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    double *const sU = sU_[ew], *const sP = sP_[ew], *const sQ = sQ_[ew];
+    double(*const sV)[S::COLS] = sV_[ew];
+    const int el = EPB == 1 ? 0 : t / MM, tc = t - el * MM;
+    const bool col = t < S::COLS;
+    const int a = col ? tc % M : 0, b = col ? tc / M : 0;
+    const int at0 = (col ? el : 0) * NQ * NQ * M + a;  // of the column's element in sP, sQ
+    for (int i = threadIdx.x; i < M * NQ; i += EW * TH) {
         sJ[i / NQ][i % NQ] = J[i];
         sJd[i / NQ][i % NQ] = Jd[i];
     }
     const double wab = wq[a] * wq[b];
-    double un[PFN];
-    auto fetch = [&](int f, int64_t e) {
-        const double *p = (f < 3 ? cv + f * ldc : f == 3 ? x : f == 4 ? y : z) + e * NP;
-#pragma unroll
-        for (int q = 0; q < PFN; ++q) {
-            const int i = t + q * TH;
-            un[q] = i < NP ? p[i] : 0.0;
-        }
-    };
-    if (blockIdx.x < E) fetch(F0, blockIdx.x);
-    for (int64_t e = blockIdx.x; e < E; e += gridDim.x) {
-        double T[3][3][NQ];  // T[d][q]: line of dx_d/dr_q before the k contraction
-#pragma unroll
-        for (int f = F0; f < 6; ++f) {
+    // Workgroup g's elements lie 8 apart: each is on the XCD, whose L2 then holds its
+    // ct, where the advection kernel of one element a workgroup will read it (N = 6,
+    // 512 elements, both kernels: 29.7 us with neighbours, 25.6 so; N = 3, 4096: 22.9 /
+    // 19.1)
+    constexpr int W = EPB * EW;
+    auto elem = [](int64_t g, int slot) { return (g >> 3) * (8 * W) + (g & 7) + 8 * slot; };
+    const int64_t groups = E / (8 * W) * 8 + min(E % (8 * W), (int64_t)8);
+    double un[PFN];  // the row of the coming round, or the lane's part of the field
+    const int er = EPB == 1 ? 0 : lane / (NQ * NQ), row = lane - er * (NQ * NQ);  // element slot, row in it
+    auto fetch = [&](int r, int64_t g) {
+        const int f = CHECK ? 3 + r : !PAIR ? r : r == 0 ? (wv == 1 ? 1 : 0) : r + 1;
+        const double *p = f < 3 ? cv + f * ldc : f == 3 ? x : f == 4 ? y : z;
+        const int64_t e = elem(g, ew + er);
+        const bool in = W == 1 || e < E;
+        if constexpr (STAGE) {
 #pragma unroll
             for (int q = 0; q < PFN; ++q) {
                 const int i = t + q * TH;
-                if (i < NP) sU[i] = un[q];
+                un[q] = in && i < NP ? p[e * NP + i] : 0.0;
             }
-            if (f < 5)
-                fetch(f + 1, e);
-            else if (e + gridDim.x < E)
-                fetch(F0, e + gridDim.x);
-            __syncthreads();  // also: the columns of the field before are done with sP, sQ
+        } else {
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) un[i] = in && lane < ROWS ? p[e * NP + row * NQ + i] : 0.0;
+        }
+    };
+    if (blockIdx.x < groups) fetch(0, blockIdx.x);
+    for (int64_t g = blockIdx.x; g < groups; g += gridDim.x) {
+        double T[3][3][NQ];  // T[d][q]: line of dx_d/dr_q before the k contraction
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            const bool coord = CHECK || r >= (PAIR ? 2 : 3), pair = PAIR && r == 0;
+            const int d = CHECK ? r : PAIR ? (r < 2 ? 2 * r : r - 2) : r % 3;  // component
+            auto next = [&]() {
+                if (r + 1 < ROUNDS)
+                    fetch(r + 1, g);
+                else if (g + gridDim.x < groups)
+                    fetch(0, g + gridDim.x);
+            };
+            if constexpr (STAGE) {
+#pragma unroll
+                for (int q = 0; q < PFN; ++q)
+                    if (t + q * TH < NP) sU[t + q * TH] = un[q];
+                next();
+            }
+            __syncthreads();  // the columns of the round before are done with sP, sQ
             // over i on GLL rows (k, j): J u, and for a coordinate Jd u
-            if (t < NQ * NQ) {
-                double r[NQ];
+            if (lane < ROWS && wv < 2) {
+                double v[NQ];
 #pragma unroll
-                for (int i = 0; i < NQ; ++i) r[i] = sU[t * NQ + i];
+                for (int i = 0; i < NQ; ++i) v[i] = STAGE ? sU[STAGE ? lane * NQ + i : 0] : un[STAGE ? 0 : i];
+                if constexpr (DUO) {
+                    const double *Jm = coord && wv == 1 ? Jd : J;
+                    double *dst = (wv == 1 && (pair || coord) ? sQ : sP) + lane * M;
+                    // a single component: half of the Gauss points each, all in sP
+                    constexpr int H = (M + 1) / 2;
+                    const int n0 = !pair && !coord && wv == 1 ? H : 0;
+                    const int n1 = !pair && !coord && wv == 0 ? H : M;
+// (unrolled by the 11 points of N = 7: 24^3 elements 307 us, by more 283)
+#pragma unroll 16
+                    for (int a2 = n0; a2 < n1; ++a2) {
+                        double p = 0.0;
 #pragma unroll
-                for (int a2 = 0; a2 < M; ++a2) {
-                    double p = 0.0, q = 0.0;
-#pragma unroll
-                    for (int i = 0; i < NQ; ++i) {
-                        p += J[a2 * NQ + i] * r[i];
-                        if (f >= 3) q += Jd[a2 * NQ + i] * r[i];
+                        for (int i = 0; i < NQ; ++i) p += Jm[a2 * NQ + i] * v[i];
+                        dst[a2] = p;
                     }
-                    sP[t * M + a2] = p;
-                    if (f >= 3) sQ[t * M + a2] = q;
+                } else {
+#pragma unroll
+                    for (int a2 = 0; a2 < M; ++a2) {
+                        double p = 0.0, q = 0.0;
+#pragma unroll
+                        for (int i = 0; i < NQ; ++i) {
+                            p += J[a2 * NQ + i] * v[i];
+                            if (coord) q += Jd[a2 * NQ + i] * v[i];
+                        }
+                        sP[lane * M + a2] = p;
+                        if (coord) sQ[lane * M + a2] = q;
+                    }
                 }
             }
+            if constexpr (!STAGE) next();  // behind the rows: one row each in registers
             __syncthreads();
             if (col) {
-                if (f >= 3) {
-                    double(&Tf)[3][NQ] = T[f < 3 ? 0 : f - 3];
+                if (coord) {
+                    double(&Tf)[3][NQ] = T[d];
 #pragma unroll
                     for (int k = 0; k < NQ; ++k) Tf[0][k] = Tf[1][k] = Tf[2][k] = 0.0;
 #pragma unroll
@@ -420,29 +489,38 @@ __global__ void __launch_bounds__((AdvShape<NQ, M>::THREADS), 2)
                         const double jb = sJ[b][j], jd = sJd[b][j];
 #pragma unroll
                         for (int k = 0; k < NQ; ++k) {
-                            const double p = sP[(k * NQ + j) * M + a], q = sQ[(k * NQ + j) * M + a];
+                            const int at = at0 + (k * NQ + j) * M;
+                            const double p = sP[at], q = sQ[at];
                             Tf[0][k] += jb * q;
                             Tf[1][k] += jd * p;
                             Tf[2][k] += jb * p;
                         }
                     }
                 } else {
-                    double Vf[NQ];
+                    double V0[NQ], V1[NQ];
 #pragma unroll
-                    for (int k = 0; k < NQ; ++k) Vf[k] = 0.0;
+                    for (int k = 0; k < NQ; ++k) V0[k] = V1[k] = 0.0;
 #pragma unroll
                     for (int j = 0; j < NQ; ++j) {
                         const double jb = sJ[b][j];
 #pragma unroll
-                        for (int k = 0; k < NQ; ++k) Vf[k] += jb * sP[(k * NQ + j) * M + a];
+                        for (int k = 0; k < NQ; ++k) {
+                            const int at = at0 + (k * NQ + j) * M;
+                            V0[k] += jb * sP[at];
+                            if (pair) V1[k] += jb * sQ[at];
+                        }
                     }
 #pragma unroll
-                    for (int k = 0; k < NQ; ++k) sV[CHECK ? 0 : f * NQ + k][t] = Vf[k];
+                    for (int k = 0; k < NQ; ++k) {
+                        sV[CHECK ? 0 : d * NQ + k][t] = V0[k];
+                        if (pair) sV[CHECK ? 0 : NQ + k][t] = V1[k];
+                    }
                 }
             }
         }
-        if (col) {
-            double *ce = CHECK ? nullptr : ct + e * 3 * M3 + t;
+        const int64_t e = elem(g, ew + el);
+        if (col && (W == 1 || e < E)) {
+            double *ce = CHECK ? nullptr : ct + e * 3 * M3 + tc;
 #pragma unroll 1
             for (int c = 0; c < M; ++c) {
                 const double *Jc = J + c * NQ, *Jdc = Jd + c * NQ;
@@ -643,29 +721,51 @@ int launch_velocity(sem_handle h, int M, const double *J, const double *Jd, cons
     const Level &L = h->lv[0];
     // as many workgroups as are resident (24^3 elements, 4 / 8 / 16 per CU: M = 11
     // 292 / 313 / 313 us, two waves a SIMD; M = 8 149 / 111 / 115, M = 7 99 / 76 / 77;
-    // 8 / 16 / 32 per CU at 35^3, M = 5: 138 / 129 / 123, at 40^3, M = 4: 141 / 132 / 117)
-    const int64_t cap = (int64_t)(L.n_cu > 0 ? L.n_cu : 256) * (M >= 10 ? 4 : M >= 7 ? 8 : 32);
-    const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(L.E, cap)));
-    // up to two elements a CU take the spread form: beyond, its six wavefronts of an
-    // element only queue (1000 elements, N = 7: 29 us in turn, four rounds spread)
-    const bool few = !bad && L.E <= 2 * (int64_t)(L.n_cu > 0 ? L.n_cu : 256);
+    // one element a workgroup, 8 / 16 / 32 per CU at 35^3, M = 5: 138 / 129 / 123, at
+    // 40^3, M = 4: 141 / 132 / 117)
+    const int64_t cu = L.n_cu > 0 ? L.n_cu : 256;
+    const int64_t cap = cu * (M >= 10 ? 4 : M >= 7 ? 8 : 32);
+    // The spread form's three lane groups of an element pay while they are resident
+    // (us, spread / in turn: N = 3, 729 elements 5.8 / 6.1, 1000 6.6 / 6.3; N = 4, 1000 8.9 /
+    // 9.4, 1331 12.7 / 11.7; N = 5, 512 8.7 / 10.0, 576 12.0 / 10.6; N = 6, 216 9.4 / 11.4,
+    // 294 16.1 / 13.6; N = 7, 216 10.9 / 14.6, 294 18.9 / 17.9).
+    // At M = 12 its nine wavefronts an element leave too few registers (68 spilled, 27
+    // elements 26.2 us, 15.4 in turn).
+    const int64_t few = bad || M > 11 ? 0 : cu * (L.nq <= 4 ? 3 : L.nq == 5 ? 4 : L.nq == 6 ? 2 : 1);
+    // Two elements a workgroup where one each leaves SIMDs idle: up to two elements
+    // a CU (at M = 12 three wavefronts each spread by themselves, 343 elements 22.1 /
+    // 24.1), and in the second round of a grid that the cap cuts (N = 6, 1331 elements
+    // 30.0 / 26.4 us, N = 7 39.5 / 37.1; else the longer barriers lose: 576 22.2 / 25.8).
+    const bool two = !bad && M <= 11 && ((L.E > cu && L.E <= 2 * cu) || (L.E > 5 * cu && L.E <= 6 * cu));
+#define SEM_VEL_FORM(NQ_, M_, CHECK_, EW_)                                                          \
+    {                                                                                               \
+        using S = VelShape<NQ_, M_>;                                                                \
+        constexpr int64_t W = 8 * S::EPB * (EW_);                                                   \
+        const int64_t groups = L.E / W * 8 + std::min<int64_t>(L.E % W, 8);                         \
+        const dim3 grid((unsigned)std::max<int64_t>(1, std::min(groups, cap / (EW_))));             \
+        hipLaunchKernelGGL((velocity_kernel<NQ_, M_, CHECK_, (EW_)>), grid, dim3((EW_) * S::THREADS), 0, s, \
+                           L.E, J, Jd, wq, h->cx, h->cy, h->cz, c, ldc, ct, bad);                   \
+    }
 #define SEM_VEL(NQ_, M_)                                                                            \
     if (L.nq == NQ_ && M == M_) {                                                                   \
-        if (few)                                                                                    \
-            hipLaunchKernelGGL((velocity_spread_kernel<NQ_, M_>), dim3((unsigned)L.E),              \
-                               dim3(3 * AdvShape<NQ_, M_>::THREADS), 0, s, L.E, J, Jd, wq, h->cx, h->cy, h->cz, \
+        constexpr bool duo = VelShape<NQ_, M_>::DUO && M_ <= 11;                                    \
+        constexpr int ms = std::min(M_, 11);                                                        \
+        if (L.E <= few)                                                                             \
+            hipLaunchKernelGGL((velocity_spread_kernel<NQ_, ms>), dim3((unsigned)L.E),              \
+                               dim3(3 * AdvShape<NQ_, ms>::THREADS), 0, s, L.E, J, Jd, wq, h->cx, h->cy, h->cz, \
                                c, ldc, ct);                                                         \
-        else if (bad)                                                                                    \
-            hipLaunchKernelGGL((velocity_kernel<NQ_, M_, true>), grid, dim3(AdvShape<NQ_, M_>::THREADS), 0, \
-                               s, L.E, J, Jd, wq, h->cx, h->cy, h->cz, c, ldc, ct, bad);            \
+        else if (bad)                                                                               \
+            SEM_VEL_FORM(NQ_, M_, true, 1)                                                          \
+        else if (duo && two)                                                                        \
+            SEM_VEL_FORM(NQ_, M_, false, duo ? 2 : 1)                                               \
         else                                                                                        \
-            hipLaunchKernelGGL((velocity_kernel<NQ_, M_, false>), grid, dim3(AdvShape<NQ_, M_>::THREADS), 0, \
-                               s, L.E, J, Jd, wq, h->cx, h->cy, h->cz, c, ldc, ct, bad);            \
+            SEM_VEL_FORM(NQ_, M_, false, 1)                                                         \
         SEM_HIP(hipGetLastError());                                                                 \
         return SEM_OK;                                                                              \
     }
     SEM_ADV_PAIRS(SEM_VEL)
 #undef SEM_VEL
+#undef SEM_VEL_FORM
     set_error("advection: no kernel for N = %d, M = %d", L.N, M);
     return SEM_EINVAL;
 }
