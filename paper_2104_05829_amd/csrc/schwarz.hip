@@ -665,6 +665,138 @@ fdm_kernel(int64_t E, int ln, int epb, const int32_t *__restrict__ ix, const flo
     }
 }
 
+// The same on the vector unit, for ne <= 6, where an element's 25 or 36 lines fill
+// half and three quarters of their lane groups and 5 or 6 rows two 4-row pieces of
+// a product: the lines of 10 or 7 elements side by side in the lanes, rows of S from
+// LDS, two line buffers in turn; the eigenbases are loaded once for a batch.  Every
+// sum runs in the order of the matrix form, so the bits are the same.  Many
+// elements gain from it, whose blocks in flight hide the reads of S; few gain from
+// the matrix form's shorter chain (us, matrix / vector unit, one vector: ne = 6, 343
+// elements 5.2 / 6.3, 2744 7.5 / 7.4, 13824 17.0 / 15.8, 64000 61.5 / 55.3; ne = 5, 2744 5.6 /
+// 6.2, 13824 10.9 / 10.7, 110592 56.0 / 50.6; three vectors: ne = 6, 2744 10.1 / 12.4, 13824
+// 25.7 / 26.7, 29791 50.4 / 46.4; ne = 5, 2744 8.2 / 9.8, 13824 17.2 / 17.0, 110592 98.2 / 92.5).
+template <int NE>
+struct FdmRowsShape {
+    static constexpr int NE2 = NE * NE, THREADS = 256, EPB = THREADS / NE2;
+    static constexpr int NEP = (NE + 3) & ~3;  // rows of S padded to 16 bytes
+};
+
+template <int NE, bool EXT_OUT>
+__global__ void __launch_bounds__(FdmRowsShape<NE>::THREADS)
+fdm_rows_kernel(int64_t E, const int32_t *__restrict__ ix, const float *__restrict__ Sg,
+                const float *__restrict__ lamg, const float *__restrict__ r, const float *__restrict__ t,
+                int64_t ld, float *__restrict__ acc, float *__restrict__ U, float h1, float h2, VSet vs)
+{
+    using F = FdmRowsShape<NE>;
+    constexpr int NQ = NE - 2, NE2 = F::NE2, EPB = F::EPB, NEP = F::NEP;
+    constexpr int NEXT = FdmShape<NE>::NEXT, LDP = NE + 1, NP = NQ * NQ * NQ;
+    __shared__ __align__(16) float sS[EPB][3][NE][NEP];  // Sx, Sy, Sz, rows [m][.]
+    __shared__ float sl[EPB][3][NE];                     // eigenvalues along x, y, z
+    __shared__ float sa[EPB][NE][NE][LDP], sb[EPB][NE][NE][LDP];  // [c][b][a]
+    const int tid = threadIdx.x;
+    const int el = tid / NE2, ij = tid - el * NE2;
+    const int a = ij % NE, b = ij / NE;  // also (x, k) of the line-owner stages
+    const bool acol = a == 0 || a == NE - 1 || b == 0 || b == NE - 1;  // border column
+    const int64_t e = xcd_chunk_block(blockIdx.x, gridDim.x) * EPB + el;
+    const bool act = el < EPB && e < E;
+    // the element's eigenbases and eigenvalues and this column's extension
+    // copies, once for every vector of the batch
+    int32_t q[NE];
+    if (act) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) sS[el][d][b][a] = Sg[(e * 3 + d) * NE2 + ij];
+        if (ij < 3 * NE) (&sl[el][0][0])[ij] = lamg[e * 3 * NE + ij];
+        const int32_t *ixe = ix + e * NEXT;
+#pragma unroll
+        for (int c = 0; c < NE; ++c)
+            if (acol || c == 0 || c == NE - 1) q[c] = ixe[schwarz_ext_slot(NE, a, b, c)];
+    }
+    __syncthreads();
+    // y[j] = sum_m S[m][j] x[m], and the sum over a row of S
+    auto forward = [&](int d, const float (&x)[NE], float (&y)[NE]) {
+#pragma unroll
+        for (int j = 0; j < NE; ++j) y[j] = 0.0f;
+#pragma unroll
+        for (int m = 0; m < NE; ++m) {
+            const float *Sr = &sS[el][d][m][0];
+#pragma unroll
+            for (int j = 0; j < NE; ++j) y[j] += Sr[j] * x[m];
+        }
+    };
+    auto back = [&](int d, int j, const float (&x)[NE]) {
+        const float *Sr = &sS[el][d][j][0];
+        float sum = 0.0f;
+#pragma unroll
+        for (int m = 0; m < NE; ++m) sum += Sr[m] * x[m];
+        return sum;
+    };
+    for (int f = 0; f < vs.n; ++f) {
+        const int64_t v = vs.at(f);
+        const float *rv = r + v * ld, *tv = t ? t + v * ld : nullptr;
+        float x[NE], y[NE];
+        if (act) {
+            const int64_t own = e * NP + (b - 1) * NQ + (a - 1);
+#pragma unroll
+            for (int c = 0; c < NE; ++c) {
+                if (acol || c == 0 || c == NE - 1)
+                    x[c] = q[c] >= 0 ? (tv ? rv[q[c]] - tv[q[c]] : rv[q[c]]) : 0.0f;
+                else
+                    x[c] = tv ? rv[own + (c - 1) * NQ * NQ] - tv[own + (c - 1) * NQ * NQ] : rv[own + (c - 1) * NQ * NQ];
+            }
+            forward(2, x, y);  // modes along c on the column (a, b)
+#pragma unroll
+            for (int k = 0; k < NE; ++k) sa[el][k][b][a] = y[k];
+        }
+        __syncthreads();
+        if (act) {  // along b on the line (a, k = b)
+#pragma unroll
+            for (int m = 0; m < NE; ++m) x[m] = sa[el][b][m][a];
+            forward(1, x, y);
+#pragma unroll
+            for (int j = 0; j < NE; ++j) sb[el][b][j][a] = y[j];
+        }
+        __syncthreads();
+        if (act) {  // the row (b = a, k = b) along a, divided by the eigenvalue sum, and back
+#pragma unroll
+            for (int m = 0; m < NE; ++m) x[m] = sb[el][b][a][m];
+            forward(0, x, y);
+            const float lyz = sl[el][1][a] + sl[el][2][b];
+#pragma unroll
+            for (int i = 0; i < NE; ++i) y[i] *= __builtin_amdgcn_rcpf(h1 * (sl[el][0][i] + lyz) + h2);
+            // the rows of Sx are read again below rather than kept in
+            // registers from the forward pass (that would cost ne^2 VGPRs)
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int i = 0; i < NE; ++i) sa[el][b][a][i] = back(0, i, y);
+        }
+        __syncthreads();
+        if (act) {  // back along b
+#pragma unroll
+            for (int m = 0; m < NE; ++m) x[m] = sa[el][b][m][a];
+#pragma unroll
+            for (int j = 0; j < NE; ++j) sb[el][b][j][a] = back(1, j, x);
+        }
+        __syncthreads();
+        if (act) {  // back along c on the column, in registers
+#pragma unroll
+            for (int k = 0; k < NE; ++k) x[k] = sb[el][k][b][a];
+            float *acce = acc + v * ld + e * NP + (b - 1) * NQ + (a - 1);
+            float *Ue = EXT_OUT ? U + v * E * NEXT + e * NEXT : nullptr;
+#pragma unroll
+            for (int c = EXT_OUT ? 0 : 1; c < NE - (EXT_OUT ? 0 : 1); ++c) {
+                const float o = back(2, c, x);
+                if (!acol && c > 0 && c < NE - 1)
+                    acce[(c - 1) * NQ * NQ] = o;
+                else if (EXT_OUT)
+                    Ue[schwarz_ext_slot(NE, a, b, c)] = o;
+            }
+        }
+        // the next vector's first LDS writes (sa) follow this vector's last sa
+        // reads (before the barrier above); its sb writes follow a barrier every
+        // thread reaches after the reads of sb here
+    }
+}
+
 // Extension values of the neighbours' local solutions added into the copies
 // that receive them, every vector of the batch in one pass over the lists: a
 // thread holds the first kAsmRegs source indices of its copy in registers
@@ -698,6 +830,9 @@ __global__ void asm_ext_kernel(int64_t nrc, const int32_t *__restrict__ rc,
     }
 }
 
+// elements from which the vector-unit form is taken (ne <= 6)
+static bool fdm_rows(int64_t E, int nv) { return E >= (nv == 1 ? 6000 : 16000); }
+
 int launch_schwarz(const Level &L, bool ras, const float *r, const float *t, float *U, float *acc,
                    const VSet &vs, double h1, double h2, hipStream_t s)
 {
@@ -706,8 +841,18 @@ int launch_schwarz(const Level &L, bool ras, const float *r, const float *t, flo
         set_error("Schwarz smoother not built on this level");
         return SEM_EINVAL;
     }
-#define SEM_FDM(NE)                                                                                   \
+#define SEM_FDM_ROWS(NE)                                                                              \
+    if (fdm_rows(L.E, vs.n)) {                                                                        \
+        using F = FdmRowsShape<NE>;                                                                   \
+        auto kern = ras ? fdm_rows_kernel<NE, false> : fdm_rows_kernel<NE, true>;                     \
+        hipLaunchKernelGGL(kern, dim3((unsigned)((L.E + F::EPB - 1) / F::EPB)), dim3(F::THREADS), 0, s, L.E, \
+                           L.sz_ix, L.sz_S, L.sz_lam, r, t, L.nL, acc, U, (float)h1, (float)h2, vs);  \
+        SEM_HIP(hipGetLastError());                                                                   \
+        break;                                                                                        \
+    }
+#define SEM_FDM(NE, ROWS)                                                                             \
     case NE: {                                                                                        \
+        ROWS                                                                                          \
         using F = FdmShape<NE>;                                                                       \
         const int grp = 4 << F::CB, ni = F::LOOP ? 1 : vs.n;                                          \
         const int ln = (ni * F::NE2 + grp - 1) / grp * grp;                                           \
@@ -721,10 +866,12 @@ int launch_schwarz(const Level &L, bool ras, const float *r, const float *t, flo
         break;                                                                                        \
     }
     switch (L.sz_ne) {
-        SEM_FDM(5) SEM_FDM(6) SEM_FDM(7) SEM_FDM(8) SEM_FDM(9) SEM_FDM(10) SEM_FDM(11)
+        SEM_FDM(5, SEM_FDM_ROWS(5)) SEM_FDM(6, SEM_FDM_ROWS(6))
+        SEM_FDM(7, ) SEM_FDM(8, ) SEM_FDM(9, ) SEM_FDM(10, ) SEM_FDM(11, )
     default: set_error("Schwarz smoother: unsupported order N = %d", L.N); return SEM_EINVAL;
     }
 #undef SEM_FDM
+#undef SEM_FDM_ROWS
     if (!ras && L.sz_nrc > 0) {
         const int64_t ldU = L.E * (int64_t)L.sz_next;
         const int64_t groups = (L.sz_nrc + 255) / 256;
