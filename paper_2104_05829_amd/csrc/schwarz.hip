@@ -475,9 +475,9 @@ int build_schwarz(Level &L, hipStream_t s)
 // (110592 elements, ne = 5: 81 us with a wavefront each, 62 us so).  The vectors
 // of a batch lie side by side in the lanes, as they fill wavefronts better (3 x
 // 100 lines take 5, one 2), but run one after the other at ne = 5 (LOOP), where
-// what a thread derives from its position weighs more than its lines (3 vectors
-// of 110592 elements: 168 us side by side, 140 us in turn; ne = 6, 64000
-// elements: 158 and 162).
+// what a thread derives from its position weighs more than its lines: 5832 elements,
+// one vector 6.8 us in turn / 7.2 side by side, two 9.9 / 10.2, three 13.4 / 12.2; 8000 7.9 /
+// 8.5, 11.9 / 12.1, 15.0 / 14.4.  (Of 343 elements three vectors take 8.7 / 4.8.)
 //
 // Before, the rows of S came from LDS for every product, and these reads (30
 // ds_read_b128 a wavefront and transform at ne = 10) bound the kernel: 65 us for
@@ -671,10 +671,11 @@ fdm_kernel(int64_t E, int ln, int epb, const int32_t *__restrict__ ix, const flo
 // LDS, two line buffers in turn; the eigenbases are loaded once for a batch.  Every
 // sum runs in the order of the matrix form, so the bits are the same.  Many
 // elements gain from it, whose blocks in flight hide the reads of S; few gain from
-// the matrix form's shorter chain (us, matrix / vector unit, one vector: ne = 6, 343
-// elements 5.2 / 6.3, 2744 7.5 / 7.4, 13824 17.0 / 15.8, 64000 61.5 / 55.3; ne = 5, 2744 5.6 /
-// 6.2, 13824 10.9 / 10.7, 110592 56.0 / 50.6; three vectors: ne = 6, 2744 10.1 / 12.4, 13824
-// 25.7 / 26.7, 29791 50.4 / 46.4; ne = 5, 2744 8.2 / 9.8, 13824 17.2 / 17.0, 110592 98.2 / 92.5).
+// the matrix form's shorter chain (us with r - t, matrix / vector unit, one vector: ne = 6,
+// 343 elements 5.2 / 6.6, 5832 10.8 / 10.8, 13824 17.3 / 16.8, 64000 61.5 / 58.0; ne = 5, 2744
+// 5.7 / 6.3, 8000 7.9 / 8.9, 13824 11.4 / 11.1, 110592 58.2 / 52.9; three vectors: ne = 6, 2744
+// 11.4 / 15.3, 13824 30.9 / 33.7, 29791 63.8 / 60.5, 64000 147 / 130; ne = 5, 2744 9.8 / 12.8,
+// 13824 20.9 / 20.2, 110592 125 / 120).
 template <int NE>
 struct FdmRowsShape {
     static constexpr int NE2 = NE * NE, THREADS = 256, EPB = THREADS / NE2;
@@ -830,8 +831,11 @@ __global__ void asm_ext_kernel(int64_t nrc, const int32_t *__restrict__ rc,
     }
 }
 
-// elements from which the vector-unit form is taken (ne <= 6)
-static bool fdm_rows(int64_t E, int nv) { return E >= (nv == 1 ? 6000 : 16000); }
+// elements from which the vector-unit form is taken (ne <= 6), figures at fdm_rows_kernel
+static bool fdm_rows(int ne, int64_t E, int nv)
+{
+    return E >= (ne == 5 ? 13000 : nv == 1 ? 6000 : 22000);
+}
 
 int launch_schwarz(const Level &L, bool ras, const float *r, const float *t, float *U, float *acc,
                    const VSet &vs, double h1, double h2, hipStream_t s)
@@ -842,7 +846,7 @@ int launch_schwarz(const Level &L, bool ras, const float *r, const float *t, flo
         return SEM_EINVAL;
     }
 #define SEM_FDM_ROWS(NE)                                                                              \
-    if (fdm_rows(L.E, vs.n)) {                                                                        \
+    if (fdm_rows(NE, L.E, vs.n)) {                                                                    \
         using F = FdmRowsShape<NE>;                                                                   \
         auto kern = ras ? fdm_rows_kernel<NE, false> : fdm_rows_kernel<NE, true>;                     \
         hipLaunchKernelGGL(kern, dim3((unsigned)((L.E + F::EPB - 1) / F::EPB)), dim3(F::THREADS), 0, s, L.E, \
