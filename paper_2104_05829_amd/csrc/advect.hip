@@ -337,8 +337,10 @@ __global__ void __launch_bounds__((Adv3Shape<NQ, M>::THREADS))
 // the Gauss points from the element's coordinates and velocity alone.  The
 // metric factors rho~ |det X| dr_q/dx_d are 72 M^3 bytes an element when kept
 // (96 KB at M = 11, of 140 KB that the transform then moved: 0.955 ms = 4.8 TB/s
-// on 32^3 elements); formed here from the 12 KB of coordinates they cost
-// arithmetic that hides behind the 44 KB left.
+// on 32^3 elements); formed here from the 12 KB of coordinates the transform takes
+// 0.68 to 0.74 ms: the LDS is busy for half of it, the FP64 units for 40%, the 57 KB
+// left an element are half of it at the copy rate, and two waves a SIMD overlap
+// little.
 // Lane t = a + M b owns the Gauss column (b, a) as in the advection kernel.  The
 // velocity components and the coordinates are contracted over i on their GLL
 // rows, a row per lane straight from memory, and over j on the columns, through
